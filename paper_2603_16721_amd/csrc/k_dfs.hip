@@ -1000,6 +1000,11 @@ hipError_t launch_make_items(const Problem& P, const Work& w, bool seed, hipStre
   return hipGetLastError();
 }
 
+hipError_t launch_pair_hist(const Work& w, hipStream_t s) {
+  k_pair_hist<<<256, 256, 0, s>>>(w);
+  return hipGetLastError();
+}
+
 hipError_t launch_seed_select(const Problem& P, const Work& w, hipStream_t s) {
   (void)P;
   k_begin_bound_lists<<<1, 1, 0, s>>>(w);

@@ -1,0 +1,1139 @@
+// Rounds of a greedy run under score-bound pruning, as a lazy best-first
+// search over the pairs of the run's first round (h = 2..9).
+//
+// A combination's score S = p*TP + q*TN can only fall while the cover grows
+// (TP counts uncovered samples, TN does not change), so an upper bound on the
+// scores below a pair stays one for the rest of the run.  The non-empty pairs
+// of the starting mask are listed once, each with such a bound (p*C_T + q*N_n
+// to begin with), and a round only opens the pairs whose bound still reaches
+// the best combination found so far; an opened pair leaves a tighter bound
+// behind (the best leaf scored or the largest bound pruned below it).  What a
+// round costs is then the pairs whose bounds have come into reach, not the
+// cohort: one launch, no re-packing, no pair table, no work lists.
+//
+// Everything lives in the run's own index space: the genes and samples that
+// are active / uncovered at its start (rows TA, re-packed once), plus the
+// transposed bit matrix B (one row of genes per sample).  Below a pair the
+// candidates are counted 64 genes per lane at a time: the B rows of the
+// prefix's samples are added up in bit slices, and one comparison of the
+// slices with the least useful TP keeps the candidates that can matter.  A
+// short list of those (their samples compressed to one 64-bit mask) is then
+// searched from LDS.
+//
+// Pairs are dealt to the waves in order of their first counts, one each in
+// turn; a wave owns its share for the whole run (no queue, no atomics), 64
+// pairs to a chunk with the chunk's largest bound beside it.  Each round a
+// wave re-evaluates the best leaf it knows, publishes it, and then opens its
+// pairs from the largest bounds down.  The last block to finish takes the
+// argmax, writes the round's record and updates the cover.
+#include "dfs_core.h"
+#include "pdfs_dev.h"
+#include "slot_reduce.h"
+
+namespace pdfs {
+
+namespace {
+
+__device__ __forceinline__ int popc64(uint64_t x) { return __popcll((unsigned long long)x); }
+
+__device__ __forceinline__ int wave_sum(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return uniform(v);
+}
+
+__device__ __forceinline__ int wave_min(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+  return uniform(v);
+}
+
+// Sum of v over the lanes below this one.
+__device__ __forceinline__ int wave_before(int v, int lane) {
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += x;
+  }
+  return incl - v;
+}
+
+// |Ta & Tb & U| of one pair per lane, u in LDS; loads of four words in flight.
+__device__ __forceinline__ int pair_count(const uint64_t* __restrict__ ra,
+                                          const uint64_t* __restrict__ rb, const uint64_t* u,
+                                          int w64) {
+  int ct = 0, k = 0;
+  for (; k + 4 <= w64; k += 4) {
+    uint64_t x[4], y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = ra[k + i];
+      y[i] = rb[k + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ct += popc64(x[i] & y[i] & u[k + i]);
+  }
+  for (; k < w64; ++k) ct += popc64(ra[k] & rb[k] & u[k]);
+  return ct;
+}
+
+// ------------------------------------------------------------- run start
+// One wave per 64 genes x 64 samples: the rows' word transposed by ballots.
+// The first block also starts the run's control words.
+__global__ __launch_bounds__(256) void k_lazy_begin(Problem P, Work w, LazyWork L) {
+  RoundState* st = w.st;
+  if (st->done) return;
+  const int lane = threadIdx.x & 63;
+  const int nA = st->nA;
+  if (blockIdx.x == 0) {
+    const int n_unc = st->n_unc;
+    for (int k = threadIdx.x; k < kMaxW64; k += 256) {
+      const int lo = 64 * k;
+      L.Uc[k] = n_unc - lo >= 64 ? ~0ull : (n_unc > lo ? (1ull << (n_unc - lo)) - 1ull : 0ull);
+    }
+    if (threadIdx.x == 0) L.uncs[0] = n_unc;
+    for (int v = threadIdx.x; v <= kMaxCount; v += 256) L.cursor[v] = 0u;
+    for (int i = threadIdx.x; i < kLazyCtl; i += 256) L.ctl[i] = 0u;
+    if (threadIdx.x < kIncShards) L.shard[threadIdx.x * kCursorStride] = 0ull;
+    if (threadIdx.x == 0 && st->n_pairs > w.pair_cap) {
+      // n_pairs keeps the count emitted; the run stops before its first round
+      st->overflow |= kOverflowPairs;
+      st->done = 1;
+    }
+  }
+  const uint64_t* T = reinterpret_cast<const uint64_t*>(w.TA);
+  const int tiles = L.gw * w.w64;
+  const int waves = gridDim.x * (kBlock / kWave);
+  for (int t = blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6); t < tiles; t += waves) {
+    const int gq = t / w.w64, sw = t % w.w64;
+    const int g = gq * 64 + lane;
+    const uint64_t x = g < nA ? T[(size_t)g * w.w64 + sw] : 0ull;
+    uint64_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+      const unsigned long long col = __ballot((x >> j) & 1ull);
+      mine = lane == j ? col : mine;
+    }
+    L.B[(size_t)(sw * 64 + lane) * L.gw + gq] = mine;
+  }
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < L.nw; i += gridDim.x * kBlock)
+    L.pool[i].s = -1;
+}
+
+// The pair list in order of falling count, dealt one by one to the waves: the
+// pair of rank r is entry r / nw of wave r % nw.  A block takes kDeal pairs,
+// counts them in LDS, reserves its stretch of every bin with one atomic and
+// places them (the order inside a bin is of no consequence).
+constexpr int kDeal = 4096;
+
+__global__ __launch_bounds__(256) void k_lazy_deal(Problem P, Work w, LazyWork L) {
+  __shared__ uint32_t cnt[kMaxCount + 1];
+  __shared__ uint32_t base[kMaxCount + 1];
+  __shared__ uint32_t part[kBlock];
+  RoundState* st = w.st;
+  if (st->done) return;
+  const unsigned long long np = st->n_pairs < w.pair_cap ? st->n_pairs : w.pair_cap;
+  const int tid = threadIdx.x;
+  constexpr int kPer = (kMaxCount + kBlock) / kBlock;   // bins per thread, from the top
+  uint32_t sum = 0;
+  for (int k = 0; k < kPer; ++k) {
+    const int v = kMaxCount - tid * kPer - k;
+    if (v >= 0) sum += w.hist[v];
+  }
+  part[tid] = sum;
+  __syncthreads();
+  for (int o = 1; o < kBlock; o <<= 1) {
+    const uint32_t add = tid >= o ? part[tid - o] : 0u;
+    __syncthreads();
+    part[tid] += add;
+    __syncthreads();
+  }
+  uint32_t run = part[tid] - sum;
+  for (int k = 0; k < kPer; ++k) {
+    const int v = kMaxCount - tid * kPer - k;
+    if (v >= 0) {
+      base[v] = run;
+      run += w.hist[v];
+    }
+  }
+  const int chunks = L.seg / kWave;
+  for (unsigned long long i0 = (unsigned long long)blockIdx.x * kDeal; i0 < np;
+       i0 += (unsigned long long)gridDim.x * kDeal) {
+    __syncthreads();
+    for (int v = tid; v <= kMaxCount; v += kBlock) cnt[v] = 0u;
+    __syncthreads();
+    unsigned long long e[kDeal / kBlock];
+    uint32_t rk[kDeal / kBlock];
+#pragma unroll
+    for (int u = 0; u < kDeal / kBlock; ++u) {
+      const unsigned long long i = i0 + (unsigned long long)u * kBlock + tid;
+      e[u] = i < np ? w.pairs[i] : 0ull;
+    }
+#pragma unroll
+    for (int u = 0; u < kDeal / kBlock; ++u)
+      rk[u] = e[u] ? atomicAdd(&cnt[(e[u] >> 32) & 0xffff], 1u) : 0u;
+    __syncthreads();
+    for (int v = tid; v <= kMaxCount; v += kBlock) {
+      const uint32_t n = cnt[v];
+      cnt[v] = n ? base[v] + atomicAdd(&L.cursor[v], n) : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kDeal / kBlock; ++u) {
+      if (!e[u]) continue;
+      const int ct = (int)((e[u] >> 32) & 0xffff);
+      const uint32_t r = cnt[ct] + rk[u];
+      const uint32_t wv = r % (uint32_t)L.nw, slot = r / (uint32_t)L.nw;
+      if (slot >= (uint32_t)L.seg) continue;   // r < pair_cap <= nw * seg
+      const uint32_t sb = (uint32_t)(P.p * ct + P.q * P.n_normal);
+      L.list[(size_t)wv * L.seg + slot] = (e[u] & 0xffffffffull) | ((unsigned long long)sb << 32);
+      // ranks fall in count, so a chunk's first entry holds its largest bound
+      if (slot % kWave == 0) L.cmax[(size_t)wv * chunks + slot / kWave] = (int32_t)sb;
+    }
+  }
+}
+
+// ------------------------------------------------------------- one round
+// A wave's share of LDS: level lists (candidates with their samples as a mask
+// over the pair's at most 64 samples), the prefix's sample ids, intersections
+// per depth of the general walk, the prefix and the best leaf's tuple.
+struct WaveLds {
+  uint64_t* mask;    // [levels][cap]
+  uint64_t* y;       // [kMaxH][kMaxW64]
+  uint16_t* idx;     // [levels][cap]
+  uint16_t* smp;     // [kMaxCount]
+  uint16_t* pre;     // [kMaxH + 1] prefix (active indices, ascending)
+  uint16_t* tup;     // [kMaxH + 1] best leaf's tuple
+};
+
+constexpr int kLazyCap(int h) { return h <= 5 ? 256 : 128; }
+constexpr int kLazyLevels(int h) { return h <= 4 ? 1 : h - 3; }
+
+size_t lazy_wave_bytes(int h) {
+  const size_t lv = (size_t)kLazyLevels(h), cap = (size_t)kLazyCap(h);
+  size_t b = lv * cap * 8 + (size_t)kMaxH * kMaxW64 * 8 + lv * cap * 2 + kMaxCount * 2 +
+             2 * (kMaxH + 1) * 2;
+  return (b + 15) / 16 * 16;
+}
+
+__device__ __forceinline__ WaveLds wave_lds(char* p, int h) {
+  const int lv = h <= 4 ? 1 : h - 3, cap = h <= 5 ? 256 : 128;
+  WaveLds s;
+  s.mask = reinterpret_cast<uint64_t*>(p);
+  s.y = s.mask + lv * cap;
+  s.idx = reinterpret_cast<uint16_t*>(s.y + kMaxH * kMaxW64);
+  s.smp = s.idx + lv * cap;
+  s.pre = s.smp + kMaxCount;
+  s.tup = s.pre + kMaxH + 1;
+  return s;
+}
+
+// Samples of y (lane k < w64 holds word k) as ids in smp; returns how many.
+__device__ __forceinline__ int list_samples(uint64_t y, uint16_t* smp, int lane) {
+  const int c = popc64(y);
+  int pos = wave_before(c, lane);
+  const int m = uniform(__shfl(pos + c, 63, 64));
+  wave_lds_sync();   // earlier reads of the list are done
+  while (y) {
+    smp[pos++] = (uint16_t)(lane * 64 + __builtin_ctzll(y));
+    y &= y - 1;
+  }
+  wave_lds_sync();
+  return m;
+}
+
+// Bit-sliced count: slice k of s holds bit k of, for each of the 64 genes of
+// word wd, the number of listed samples that carry it.
+template <int NB>
+__device__ __forceinline__ void slice_count(const uint64_t* __restrict__ B, int gw,
+                                            const uint16_t* smp, int m, int wd, bool on,
+                                            uint64_t (&s)[NB]) {
+#pragma unroll
+  for (int k = 0; k < NB; ++k) s[k] = 0;
+  auto add = [&](uint64_t x) {
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const uint64_t c = s[k] & x;
+      s[k] ^= x;
+      x = c;
+    }
+  };
+  int j = 0;
+  for (; j + 4 <= m; j += 4) {   // four rows in flight
+    uint64_t x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint64_t* row = B + (size_t)uniform(smp[j + u]) * gw;
+      x[u] = on ? row[wd] : 0ull;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) add(x[u]);
+  }
+  for (; j < m; ++j) {
+    const uint64_t* row = B + (size_t)uniform(smp[j]) * gw;
+    add(on ? row[wd] : 0ull);
+  }
+}
+
+// Genes of the word whose count is at least `need` (wave-uniform, >= 1).
+template <int NB>
+__device__ __forceinline__ uint64_t slices_ge(const uint64_t (&s)[NB], int need) {
+  if (need >> NB) return 0ull;
+  uint64_t ge = ~0ull;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) ge = ((need >> k) & 1) ? (s[k] & ge) : (s[k] | ge);
+  return ge;
+}
+
+template <int NB>
+__device__ __forceinline__ int slice_at(const uint64_t (&s)[NB], int bit) {
+  int c = 0;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) c |= (int)((s[k] >> bit) & 1ull) << k;
+  return c;
+}
+
+// Largest count over the genes `in` of all lanes; in is cut to the genes that
+// reach it.
+template <int NB>
+__device__ __forceinline__ int slices_max(const uint64_t (&s)[NB], uint64_t& in) {
+  int v = 0;
+#pragma unroll
+  for (int k = NB - 1; k >= 0; --k) {
+    const uint64_t t = in & s[k];
+    if (__any(t != 0)) {
+      in = t;
+      v |= 1 << k;
+    }
+  }
+  return v;
+}
+
+// Bits of word wd inside [lo, hi).
+__device__ __forceinline__ uint64_t range_bits(int wd, int lo, int hi) {
+  const int b = wd * 64;
+  if (b + 64 <= lo || b >= hi) return 0ull;
+  uint64_t m = ~0ull;
+  if (lo > b) m &= ~0ull << (lo - b);
+  if (hi < b + 64) m &= ~(~0ull << (hi - b));
+  return m;
+}
+
+// The state of one wave in one round.
+struct Wave {
+  const Problem& P;
+  const Work& w;
+  const LazyWork& L;
+  WaveLds s;
+  const uint64_t* T;
+  int lane, nA, w64, h;
+  uint64_t u;                   // lane k < w64: word k of the uncovered mask
+  unsigned long long inc;       // newest incumbent seen
+  int bs, btp, bfp;             // best leaf (tuple in s.tup)
+  // the pair being opened
+  bool own;                     // the wave's best leaf lies below this pair
+  int tie_s;                    // a score this pair has reached: its later tuples lose the tie
+  int a, b, need, sub, lmax;    // best score below it; per lane: largest TP pruned
+};
+
+__device__ __forceinline__ void refresh_need(Wave& v) {
+  if (v.inc == 0) {
+    v.need = 1;
+    return;
+  }
+  const int s = (int)(v.inc >> 32) - 1;
+  const int g1 = 0xffff - (int)((v.inc >> 16) & 0xffff);
+  const int g2 = 0xffff - (int)(v.inc & 0xffff);
+  const bool tie = s != v.tie_s && (v.a < g1 || (v.a == g1 && v.b <= g2));
+  v.need = min_tp_for(v.P, s, tie);
+}
+
+// Both walks below a pair go in tuple order.  Once the prefix s.pre[0, np) has
+// passed the wave's own best leaf, no later leaf of the pair wins its tie.
+__device__ __forceinline__ void pass_own_best(Wave& v, int np) {
+  if (!v.own) return;
+  for (int i = 2; i < np; ++i) {
+    const int x = uniform(v.s.pre[i]), y = uniform(v.s.tup[i]);
+    if (x < y) return;
+    if (x > y) {
+      v.own = false;
+      v.tie_s = v.bs;
+      refresh_need(v);
+      return;
+    }
+  }
+}
+
+__device__ __forceinline__ void publish_key(Wave& v, unsigned long long key) {
+  if (key > v.inc) {
+    unsigned long long best = key;
+    if (v.lane == 0) {
+      unsigned long long old =
+          atomicMax(&v.L.shard[(blockIdx.x % kIncShards) * kCursorStride], key);
+      if (old < key) {
+        old = load_incumbent(v.w.st);
+        if (old < key) old = atomicMax(&v.w.st->incumbent, key);
+      }
+      best = old > key ? old : key;
+    }
+    v.inc = __shfl(best, 0, 64);
+  }
+}
+
+__device__ __forceinline__ void publish(Wave& v, int s, int a, int b) {
+  publish_key(v, leaf_key(s, a, b));
+}
+
+// Takes the leaf (first np genes of s.pre, then d) if it beats the wave's best.
+__device__ __forceinline__ bool take_leaf(Wave& v, int sc, int tp, int fp, int np, int d) {
+  bool better = sc > v.bs;
+  if (sc == v.bs) {
+    wave_lds_sync();
+    bool decided = false;
+    for (int i = 0; i <= np && !decided; ++i) {
+      const int x = i < np ? (int)v.s.pre[i] : d;
+      const int y = (int)v.s.tup[i];
+      if (x != y) {
+        better = x < y;
+        decided = true;
+      }
+    }
+    better = uniform(better ? 1 : 0) != 0;
+  }
+  if (!better) return false;
+  v.bs = sc;
+  v.btp = tp;
+  v.bfp = fp;
+  wave_lds_sync();
+  if (v.lane <= np) v.s.tup[v.lane] = v.lane < np ? v.s.pre[v.lane] : (uint16_t)d;
+  wave_lds_sync();
+  return true;
+}
+
+// Leaves: the prefix s.pre[0, np) with each hit lane's candidate d (TP tp).
+// True when one of them became the wave's best.
+__device__ __forceinline__ bool score_leaves(Wave& v, int np, bool hit, int d, int tp) {
+  if (!__any(hit)) return false;
+  const bool lit = v.P.tn_literal != 0;
+  const uint32_t* NA = v.w.NA;
+  uint32_t z = 0;
+  if (v.lane < kMaxWN32) {
+    z = NA[(size_t)v.s.pre[0] * kMaxWN32 + v.lane];
+    for (int i = 1; i < np; ++i) z = nrm_join(z, NA[(size_t)v.s.pre[i] * kMaxWN32 + v.lane], lit);
+  }
+  // normal words that can hold a false positive
+  unsigned long long zm = __ballot(lit ? v.lane < v.w.wn32 : (v.lane < kMaxWN32 && z != 0));
+  int fp = 0;
+  while (zm) {
+    const int k = __builtin_ctzll(zm);
+    zm &= zm - 1;
+    const uint32_t zk = (uint32_t)__builtin_amdgcn_readlane((int)z, k);
+    if (hit) fp += __popc(nrm_join(zk, NA[(size_t)d * kMaxWN32 + k], lit));
+  }
+  const int sc = hit ? v.P.p * tp + v.P.q * (v.P.n_normal - fp) : -1;
+  const int smax = wave_max(sc);
+  v.sub = max(v.sub, smax);
+  if (smax < v.bs) return false;
+  const int dmin = wave_min(sc == smax ? d : 0x7fffffff);
+  const unsigned long long at = __ballot(sc == smax && d == dmin);
+  const int src = __builtin_ctzll(at);
+  const int btp = __builtin_amdgcn_readlane(tp, src), bfp = __builtin_amdgcn_readlane(fp, src);
+  const bool took = take_leaf(v, smax, btp, bfp, np, dmin);
+  // genes 0 and 1 of the tuple (np >= 1)
+  const int g0 = uniform(v.s.pre[0]);
+  const int g1 = np >= 2 ? uniform(v.s.pre[1]) : dmin;
+  publish(v, smax, g0, g1);
+  return took;
+}
+
+// All candidates in [lo, nA) against the m listed samples, as leaves below the
+// prefix s.pre[0, np); `in` (may be null) limits them to a bitmap.
+template <int NB>
+__device__ __forceinline__ void leaves_by_slices(Wave& v, int m, int np, int lo, const uint64_t* in) {
+  const int w_hi = (v.nA + 63) >> 6;
+  for (int w0 = lo >> 6; w0 < w_hi; w0 += 64) {
+    const int wd = w0 + v.lane;
+    uint64_t s[NB];
+    slice_count<NB>(v.L.B, v.L.gw, v.s.smp, m, wd, wd < w_hi, s);
+    uint64_t r = wd < w_hi ? range_bits(wd, lo, v.nA) : 0ull;
+    if (in && r) r &= in[wd];
+    uint64_t ge = slices_ge<NB>(s, v.need) & r;
+    uint64_t rest = r & ~ge;
+    v.lmax = max(v.lmax, slices_max<NB>(s, rest));
+    while (__any(ge != 0)) {
+      const bool has = ge != 0;
+      const int bit = has ? __builtin_ctzll(ge) : 0;
+      ge &= ge - 1;
+      const int tp = has ? slice_at<NB>(s, bit) : 0;
+      const bool hit = tp >= v.need && has;
+      v.lmax = max(v.lmax, has && !hit ? tp : 0);
+      score_leaves(v, np, hit, wd * 64 + bit, tp);
+      refresh_need(v);
+    }
+  }
+}
+
+// Candidates in [lo, nA) with a count of at least `need` into the level-0
+// list (ascending); false when they do not fit.
+template <int NB>
+__device__ __forceinline__ bool list_by_slices(Wave& v, int m, int lo, int cap, int& n) {
+  const int w_hi = (v.nA + 63) >> 6;
+  n = 0;
+  for (int w0 = lo >> 6; w0 < w_hi; w0 += 64) {
+    const int wd = w0 + v.lane;
+    uint64_t s[NB];
+    slice_count<NB>(v.L.B, v.L.gw, v.s.smp, m, wd, wd < w_hi, s);
+    const uint64_t r = wd < w_hi ? range_bits(wd, lo, v.nA) : 0ull;
+    uint64_t ge = slices_ge<NB>(s, v.need) & r;
+    uint64_t rest = r & ~ge;
+    v.lmax = max(v.lmax, slices_max<NB>(s, rest));
+    const int c = popc64(ge);
+    int pos = wave_before(c, v.lane);
+    const int tot = uniform(__shfl(pos + c, 63, 64));
+    if (n + tot > cap) return false;
+    pos += n;
+    while (ge) {
+      v.s.idx[pos++] = (uint16_t)(wd * 64 + __builtin_ctzll(ge));
+      ge &= ge - 1;
+    }
+    n += tot;
+  }
+  wave_lds_sync();
+  return true;
+}
+
+// Candidate bitmap of one level of the general walk: genes of [lo, nA) (and
+// of `in`) with a count of at least `need`.
+template <int NB>
+__device__ __forceinline__ void bits_by_slices(Wave& v, int m, int lo, const uint64_t* in, uint64_t* out) {
+  const int w_hi = (v.nA + 63) >> 6;
+  for (int w0 = lo >> 6; w0 < w_hi; w0 += 64) {
+    const int wd = w0 + v.lane;
+    uint64_t s[NB];
+    slice_count<NB>(v.L.B, v.L.gw, v.s.smp, m, wd, wd < w_hi, s);
+    uint64_t r = wd < w_hi ? range_bits(wd, lo, v.nA) : 0ull;
+    if (in && r) r &= in[wd];
+    const uint64_t ge = slices_ge<NB>(s, v.need) & r;
+    uint64_t rest = r & ~ge;
+    v.lmax = max(v.lmax, slices_max<NB>(s, rest));
+    if (wd < w_hi) out[wd] = ge;
+  }
+}
+
+// The slice count that holds m.
+#define PDFS_BY_SLICES(m, call)                         \
+  do {                                                  \
+    if ((m) < 4) { constexpr int NB = 2; call; }        \
+    else if ((m) < 16) { constexpr int NB = 4; call; }  \
+    else if ((m) < 128) { constexpr int NB = 7; call; } \
+    else { constexpr int NB = 11; call; }               \
+  } while (0)
+
+// First set bit of bm at or after `from` (below nA), or -1.
+__device__ __forceinline__ int next_bit(const uint64_t* bm, int from, int nA, int lane) {
+  const int w_hi = (nA + 63) >> 6;
+  for (int w0 = from >> 6; w0 < w_hi; w0 += 64) {
+    const int wd = w0 + lane;
+    const uint64_t x = wd < w_hi ? bm[wd] & range_bits(wd, from, nA) : 0ull;
+    const unsigned long long any = __ballot(x != 0);
+    if (any) {
+      const int l = __builtin_ctzll(any);
+      const int c = x ? wd * 64 + __builtin_ctzll(x) : 0;
+      return uniform(__shfl(c, l, 64));
+    }
+  }
+  return -1;
+}
+
+// The general walk below the pair (any number of samples and candidates):
+// depth first, every level's candidates as a bitmap in the wave's scratch.
+__device__ __forceinline__ void open_general(Wave& v, uint64_t y2, uint64_t* bits) {
+  const int h = v.h, lane = v.lane;
+  // level l (0-based) holds the candidates of depth l + 3 below prefix
+  // (s.pre[0, l + 2)), whose intersection is s.y[l]
+  int l = 0;
+  if (lane < v.w64) v.s.y[lane] = y2;
+  wave_lds_sync();
+  int m = list_samples(y2, v.s.smp, lane);
+  PDFS_BY_SLICES(m, (bits_by_slices<NB>(v, m, v.b + 1, nullptr, bits)));
+  __threadfence_block();
+  int at = v.b + 1;
+  for (;;) {
+    const uint64_t* bm = bits + (size_t)l * v.L.gw;
+    const int c = next_bit(bm, at, v.nA, lane);
+    if (c < 0) {
+      if (l == 0) break;
+      --l;
+      at = uniform(v.s.pre[l + 2]) + 1;   // past the gene whose subtree is done
+      continue;
+    }
+    // prefix of l + 3 genes
+    wave_lds_sync();
+    if (lane == 0) v.s.pre[l + 2] = (uint16_t)c;
+    uint64_t y = 0;
+    if (lane < v.w64) y = v.s.y[l * kMaxW64 + lane] & v.T[(size_t)c * v.w64 + lane];
+    const int cnt = wave_sum(popc64(y));
+    v.inc = max(v.inc, load_incumbent(v.w.st));
+    refresh_need(v);
+    wave_lds_sync();
+    pass_own_best(v, l + 3);
+    at = c + 1;
+    if (cnt < v.need) {
+      v.lmax = max(v.lmax, cnt);
+      continue;
+    }
+    m = list_samples(y, v.s.smp, lane);
+    if (l + 4 == h) {
+      PDFS_BY_SLICES(m, (leaves_by_slices<NB>(v, m, h - 1, c + 1, bm)));
+      continue;
+    }
+    if (lane < v.w64) v.s.y[(l + 1) * kMaxW64 + lane] = y;
+    wave_lds_sync();
+    uint64_t* nx = bits + (size_t)(l + 1) * v.L.gw;
+    PDFS_BY_SLICES(m, (bits_by_slices<NB>(v, m, c + 1, bm, nx)));
+    __threadfence_block();
+    ++l;
+  }
+}
+
+// The walk over the level lists (the pair's samples fit one mask word): level
+// l's entries are candidates of depth l + 3 with their samples; entry i's
+// children are the later entries of its list.
+__device__ __forceinline__ void open_lists(Wave& v, int n0) {
+  const int h = v.h, lane = v.lane;
+  const int cap = h <= 5 ? 256 : 128;
+  int l = 0;
+  int n = n0, i = 0;
+  // resume points of the suspended levels, one per lane
+  int keep_n = 0, keep_i = 0;
+  for (;;) {
+    uint64_t* mk = v.s.mask + l * cap;
+    uint16_t* ix = v.s.idx + l * cap;
+    if (i + 1 >= n) {
+      if (l == 0) break;
+      --l;
+      n = __builtin_amdgcn_readlane(keep_n, l);
+      i = __builtin_amdgcn_readlane(keep_i, l) + 1;
+      continue;
+    }
+    if (l == 0 && (i & 15) == 0) {
+      v.inc = max(v.inc, load_incumbent(v.w.st));
+      refresh_need(v);
+    }
+    const uint64_t mi = mk[i];
+    const int ci = uniform(popc64(mi));
+    if (ci < v.need) {
+      v.lmax = max(v.lmax, ci);
+      ++i;
+      continue;
+    }
+    wave_lds_sync();
+    if (lane == 0) v.s.pre[l + 2] = ix[i];
+    wave_lds_sync();
+    if (v.own) {
+      pass_own_best(v, l + 3);
+      if (ci < v.need) {
+        v.lmax = max(v.lmax, ci);
+        ++i;
+        continue;
+      }
+    }
+    if (l + 4 == h) {
+      for (int j0 = i + 1; j0 < n; j0 += kWave) {
+        const int j = j0 + lane;
+        const int tp = j < n ? popc64(mi & mk[j]) : 0;
+        const bool hit = tp >= v.need;
+        v.lmax = max(v.lmax, hit ? 0 : tp);
+        if (__any(hit)) {
+          // the lists are walked in tuple order: a leaf found here precedes
+          // every later one of the pair with its score
+          if (score_leaves(v, h - 1, hit, j < n ? (int)ix[j] : 0, tp)) v.tie_s = v.bs;
+          refresh_need(v);
+        }
+      }
+      ++i;
+      continue;
+    }
+    // the next level's list
+    uint64_t* mo = mk + cap;
+    uint16_t* io = ix + cap;
+    int k = 0;
+    for (int j0 = i + 1; j0 < n; j0 += kWave) {
+      const int j = j0 + lane;
+      const uint64_t mj = j < n ? (mi & mk[j]) : 0ull;
+      const int tp = popc64(mj);
+      const bool hit = tp >= v.need;
+      v.lmax = max(v.lmax, hit ? 0 : tp);
+      const unsigned long long hm = __ballot(hit);
+      if (hit) {
+        const int pos = rank_below(hm, k);
+        mo[pos] = mj;
+        io[pos] = ix[j];
+      }
+      k += __popcll(hm);
+    }
+    wave_lds_sync();
+    keep_n = lane == l ? n : keep_n;
+    keep_i = lane == l ? i : keep_i;
+    ++l;
+    n = k;
+    i = 0;
+  }
+}
+
+// Opens the pair (a, b): every leaf below it that can beat (or tie with a
+// smaller tuple) the incumbent is scored.  Returns an upper bound on the
+// scores below the pair under the current mask (-1: none is non-empty).
+__device__ __forceinline__ int open_pair(Wave& v, int a, int b, uint64_t* bits) {
+  const int lane = v.lane;
+  v.a = a;
+  v.b = b;
+  v.own = v.bs >= 0 && uniform(v.s.tup[0]) == a && uniform(v.s.tup[1]) == b;
+  v.tie_s = -1;
+  v.sub = -1;
+  v.lmax = 0;
+  uint64_t y2 = 0;
+  if (lane < v.w64)
+    y2 = v.T[(size_t)a * v.w64 + lane] & v.T[(size_t)b * v.w64 + lane] & v.u;
+  const int m = wave_sum(popc64(y2));
+  if (m == 0) return -1;
+  v.inc = max(v.inc, load_incumbent(v.w.st));
+  refresh_need(v);
+  const int ub = v.P.p * m + v.P.q * v.P.n_normal;
+  if (m < v.need) return ub;
+  list_samples(y2, v.s.smp, lane);
+  if (lane == 0) {
+    v.s.pre[0] = (uint16_t)a;
+    v.s.pre[1] = (uint16_t)b;
+  }
+  wave_lds_sync();
+  if (v.h == 3) {
+    PDFS_BY_SLICES(m, (leaves_by_slices<NB>(v, m, 2, b + 1, nullptr)));
+  } else {
+    int n = 0;
+    bool listed = false;
+    if (m <= 64) {
+      const int cap = v.h <= 5 ? 256 : 128;
+      if (m < 4) listed = list_by_slices<2>(v, m, b + 1, cap, n);
+      else if (m < 16) listed = list_by_slices<4>(v, m, b + 1, cap, n);
+      else listed = list_by_slices<7>(v, m, b + 1, cap, n);
+    }
+    if (listed) {
+      // the candidates' samples as masks over the pair's
+      for (int i0 = 0; i0 < n; i0 += kWave) {
+        const int i = i0 + lane;
+        if (i < n) {
+          const uint64_t* row = v.T + (size_t)v.s.idx[i] * v.w64;
+          uint64_t mk = 0;
+#pragma unroll 4
+          for (int j = 0; j < m; ++j) {
+            const int sid = v.s.smp[j];
+            mk |= ((row[sid >> 6] >> (sid & 63)) & 1ull) << j;
+          }
+          v.s.mask[i] = mk;
+        }
+      }
+      wave_lds_sync();
+      open_lists(v, n);
+    } else {
+      open_general(v, y2, bits);
+    }
+  }
+  const int lm = wave_max(v.lmax);
+  const int pr = lm > 0 ? v.P.p * lm + v.P.q * v.P.n_normal : -1;
+  return min(ub, max(v.sub, pr));
+}
+
+// A first leaf below the pair (a, b): at every depth the candidate that keeps
+// most samples.
+__device__ __forceinline__ void dive(Wave& v, int a, int b) {
+  const int lane = v.lane, h = v.h;
+  v.a = a;
+  v.b = b;
+  v.own = false;
+  v.tie_s = -1;
+  v.need = 1;
+  uint64_t y = 0;
+  if (lane < v.w64) y = v.T[(size_t)a * v.w64 + lane] & v.T[(size_t)b * v.w64 + lane] & v.u;
+  wave_lds_sync();
+  if (lane == 0) {
+    v.s.pre[0] = (uint16_t)a;
+    v.s.pre[1] = (uint16_t)b;
+  }
+  wave_lds_sync();
+  int last = b;
+  for (int depth = 3; depth <= h; ++depth) {
+    const int m = list_samples(y, v.s.smp, lane);
+    if (m == 0) return;
+    const int hi = v.w.st->amax[depth];
+    int best = 0, gene = -1;
+    const int w_hi = (hi + 63) >> 6;
+    for (int w0 = (last + 1) >> 6; w0 < w_hi; w0 += 64) {
+      const int wd = w0 + lane;
+      uint64_t in = wd < w_hi ? range_bits(wd, last + 1, hi) : 0ull;
+      int c = 0;
+      PDFS_BY_SLICES(m, {
+        uint64_t s[NB];
+        slice_count<NB>(v.L.B, v.L.gw, v.s.smp, m, wd, wd < w_hi, s);
+        c = slices_max<NB>(s, in);
+      });
+      if (c > best) {
+        best = c;
+        gene = wave_min(in ? wd * 64 + __builtin_ctzll(in) : 0x7fffffff);
+      }
+    }
+    if (gene < 0) return;
+    if (depth == h) {
+      score_leaves(v, h - 1, lane == 0, gene, best);
+      return;
+    }
+    wave_lds_sync();
+    if (lane == 0) v.s.pre[depth - 1] = (uint16_t)gene;
+    wave_lds_sync();
+    if (lane < v.w64) y &= v.T[(size_t)gene * v.w64 + lane];
+    last = gene;
+  }
+}
+
+// h = 2: the chunk's pairs are the leaves.  Every lane whose pair can still
+// win takes its exact score, which stays its bound.
+__device__ __forceinline__ void chunk_h2(Wave& v, unsigned long long& e, bool nd, int ct,
+                                         bool& changed) {
+  const int a = (int)(e & 0xffff), b = (int)((e >> 16) & 0xffff);
+  int fp = 0, sc = -1;
+  if (nd && ct > 0) {
+    const uint32_t* NA = v.w.NA;
+    const bool lit = v.P.tn_literal != 0;
+    const uint4* na = reinterpret_cast<const uint4*>(NA + (size_t)a * kMaxWN32);
+    const uint4* nb = reinterpret_cast<const uint4*>(NA + (size_t)b * kMaxWN32);
+#pragma unroll
+    for (int k = 0; k < kMaxWN32 / 4; ++k) {   // rows are zero past the last normal
+      const uint4 x = na[k], y = nb[k];
+      fp += __popc(nrm_join(x.x, y.x, lit)) + __popc(nrm_join(x.y, y.y, lit)) +
+            __popc(nrm_join(x.z, y.z, lit)) + __popc(nrm_join(x.w, y.w, lit));
+    }
+    sc = v.P.p * ct + v.P.q * (v.P.n_normal - fp);
+    e = (e & 0xffffffffull) | ((unsigned long long)(uint32_t)sc << 32);
+    changed = true;
+  }
+  const int smax = wave_max(sc);
+  if (smax < 0 || smax < v.bs) return;
+  // smallest (a, b) of the best score
+  const int key = sc == smax ? (a << 15 | b >> 1) : 0x7fffffff;   // 31 bits of a << 16 | b
+  const int kmin = wave_min(key);
+  const int lowb = wave_min(key == kmin && sc == smax ? (b & 1) : 2);
+  const unsigned long long at = __ballot(sc == smax && key == kmin && (b & 1) == lowb);
+  const int src = __builtin_ctzll(at);
+  const int ba = __builtin_amdgcn_readlane(a, src), bb = __builtin_amdgcn_readlane(b, src);
+  wave_lds_sync();
+  if (v.lane == 0) v.s.pre[0] = (uint16_t)ba;
+  wave_lds_sync();
+  take_leaf(v, smax, __builtin_amdgcn_readlane(ct, src), __builtin_amdgcn_readlane(fp, src), 1, bb);
+  publish(v, smax, ba, bb);
+}
+
+// The round's answer, its record and the cover update, by the last block.
+__device__ __forceinline__ void lazy_finish(const Problem& P, const Work& w, const LazyWork& L,
+                                            int h, int n_win) {
+  __shared__ Slot s_best;
+  __shared__ int s_found;
+  RoundState* st = w.st;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int n_unc = st->n_unc, executed = st->executed, rounds = st->rounds;
+  const int max_rounds = st->max_rounds;
+  if (tid < kWave) {
+    Slot b = empty_slot();
+    for (int i = lane; i < n_win; i += kWave) {
+      const Slot c = L.wins[i];
+      slot_take_if(b, c, slot_better(c, b));
+    }
+    b = wave_best(b);
+    if (lane == 0) {
+      int ok = b.s >= 0;
+      if (ok) {
+        const int nA = st->nA;
+#pragma unroll
+        for (int i = 0; i < kMaxH; ++i)
+          if (i < h && (b.idx[i] < 0 || b.idx[i] >= nA || (i > 0 && b.idx[i] <= b.idx[i - 1])))
+            ok = 0;
+        if (b.tp <= 0) ok = 0;
+        if (!ok) st->overflow |= 2;
+      }
+      s_best = b;
+      s_found = ok;
+    }
+  }
+  __syncthreads();
+  const int found = s_found;
+  const int tp = found ? s_best.tp : 0;
+  const int cov_n = P.n_tumor - n_unc + tp;
+  const bool done = !found || cov_n >= w.target || cov_n >= P.n_tumor ||
+                    (max_rounds > 0 && rounds + found >= max_rounds);
+  for (int i = tid; i < kLazyCtl; i += kBlock) L.ctl[i] = 0u;
+  if (tid < kIncShards) L.shard[tid * kCursorStride] = 0ull;
+  // the run's own columns; a covered sample was uncovered in every round so
+  // far.  The cohort's mask follows when the run stops.
+  const uint64_t* T = reinterpret_cast<const uint64_t*>(w.TA);
+  for (int k = tid >> 6; k < w.w64; k += kBlock / kWave) {
+    const uint64_t u = L.Uc[k];
+    uint64_t cov = found ? u : 0ull;
+    for (int i = 0; i < h && found; ++i) cov &= T[(size_t)s_best.idx[i] * w.w64 + k];
+    if ((cov >> lane) & 1ull) L.tcov[k * 64 + lane] = executed + 1;
+    if (lane == 0) L.Uc[k] = u & ~cov;
+    if (done) {
+      const int smp = k * 64 + lane;
+      const uint64_t left = u & ~cov;
+      if (smp < L.uncs[0] && !((left >> lane) & 1ull)) {
+        const int c = w.cols[smp];
+        atomicAnd(reinterpret_cast<unsigned long long*>(&w.U[c >> 6]), ~(1ull << (c & 63)));
+      }
+    }
+  }
+  // (the genes' caller ids are looked up where the record is read)
+  RoundRecord* rec = found && rounds < w.rec_cap ? w.recs + rounds : nullptr;
+  if (rec && tid >= 64 && tid < 64 + kMaxH) {
+    const int i = tid - 64;
+    rec->sorted_idx[i] = i < h ? w.act[s_best.idx[i]] : -1;
+    rec->genes[i] = -1;
+  }
+  if (tid == 0) {
+    if (rec) {
+      rec->h = h;
+      rec->found = 1;
+      rec->tp = tp;
+      rec->fp = s_best.fp;
+      rec->tn = P.n_normal - s_best.fp;
+      rec->uncovered_before = n_unc;
+      rec->score_num = (int64_t)P.p * tp + (int64_t)P.q * (P.n_normal - s_best.fp);
+      rec->score_den = (int64_t)P.q * (int64_t)(n_unc + P.n_normal);
+    }
+    st->found = found;
+    if (executed + 1 < P.n_tumor + 2) L.uncs[executed + 1] = n_unc - tp;
+    st->covered = cov_n;
+    st->n_unc = n_unc - tp;
+    st->rounds = rounds + (found ? 1 : 0);
+    st->executed = executed + 1;
+    st->incumbent = 0;
+    st->done = done;
+  }
+}
+
+// H: the combination size, or 0 for 5..9 (taken from P).
+template <int H>
+__global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork L) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ Slot wave_slot[kBlock / kWave];
+  __shared__ unsigned long long wave_key[kBlock / kWave];
+  __shared__ int s_last;
+  RoundState* st = w.st;
+  if (st->done) return;
+  const int lane = threadIdx.x & 63;
+  const int wib = uniform(threadIdx.x >> 6);
+  const int wv = blockIdx.x * (kBlock / kWave) + wib;
+  const int h = H > 0 ? H : P.h;
+  Wave v{P, w, L, wave_lds(lds + (size_t)wib * L.wave_bytes, h),
+         reinterpret_cast<const uint64_t*>(w.TA)};
+  v.lane = lane;
+  v.nA = uniform(st->nA);
+  v.w64 = w.w64;
+  v.h = h;
+  v.u = lane < w.w64 ? L.Uc[lane] : 0ull;
+  v.inc = load_incumbent(st);
+  v.bs = -1;
+  v.btp = v.bfp = 0;
+  v.a = v.b = 0;
+  v.own = false;
+  v.tie_s = -1;
+  v.need = 1;
+  v.sub = -1;
+  v.lmax = 0;
+  wave_lds_sync();
+  if (lane < w.w64) v.s.y[(kMaxH - 1) * kMaxW64 + lane] = v.u;   // the mask, for lane-wise counts
+  const uint64_t* um = v.s.y + (kMaxH - 1) * kMaxW64;
+  wave_lds_sync();
+
+  // the best leaf this wave knows from earlier rounds, under the new mask
+  {
+    const Slot q = L.pool[wv];
+    if (uniform(q.s) >= 0) {
+      uint64_t y = v.u;
+#pragma unroll
+      for (int i = 0; i < kMaxH; ++i)
+        if (i < h && lane < w.w64) y &= v.T[(size_t)q.idx[i] * w.w64 + lane];
+      const int tp = wave_sum(popc64(y));
+      if (tp > 0) {
+        v.bfp = uniform(q.fp);
+        v.btp = tp;
+        v.bs = P.p * tp + P.q * (P.n_normal - v.bfp);
+#pragma unroll
+        for (int i = 0; i < kMaxH; ++i)
+          if (i < h && lane == i) v.s.tup[i] = (uint16_t)q.idx[i];
+        wave_lds_sync();
+      }
+    }
+  }
+  // published once per block
+  {
+    const unsigned long long key = v.bs >= 0 ? leaf_key(v.bs, v.s.tup[0], v.s.tup[1]) : 0ull;
+    if (lane == 0) wave_key[wib] = key;
+    __syncthreads();
+    unsigned long long top = wave_key[0];
+    for (int i = 1; i < kBlock / kWave; ++i) top = max(top, wave_key[i]);
+    if (wib == 0 && top > 0) publish_key(v, top);
+    v.inc = max(v.inc, top);
+  }
+
+  const unsigned long long E = st->n_pairs < w.pair_cap ? st->n_pairs : w.pair_cap;
+  const int n_mine = (unsigned long long)wv < E
+                         ? (int)((E - (unsigned long long)wv + (unsigned long long)L.nw - 1ull) /
+                                 (unsigned long long)L.nw)
+                         : 0;
+  const int n_chunk = (n_mine + kWave - 1) / kWave;
+  unsigned long long* list = L.list + (size_t)wv * L.seg;
+  int32_t* cmax = L.cmax + (size_t)wv * (L.seg / kWave);
+  uint64_t* bits = L.bits + (size_t)wv * L.levels * L.gw;
+
+  // No incumbent yet (a run's first round): a greedy leaf below the wave's
+  // best pair first, so that the pairs are opened against something.
+  if (h >= 3 && n_mine > 0 && v.inc == 0) {
+    const unsigned long long e = list[0];
+    dive(v, uniform((int)(e & 0xffff)), uniform((int)((e >> 16) & 0xffff)));
+  }
+
+  for (int k0 = 0; k0 < n_chunk; k0 += kWave) {
+    const int cm = k0 + lane < n_chunk ? cmax[k0 + lane] : -1;
+    v.inc = max(v.inc, load_incumbent(st));
+    unsigned long long todo = __ballot(cm >= 0 && cm >= (int)(v.inc >> 32) - 1);
+    while (todo) {
+      const int kc = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int i = (k0 + kc) * kWave + lane;
+      unsigned long long e = i < n_mine ? list[i] : (0xffffffffull << 32);
+      const int a = (int)(e & 0xffff), b = (int)((e >> 16) & 0xffff);
+      bool changed = false;
+      int sb = (int)(e >> 32);
+      bool nd = sb >= 0 && !dominated(sb, a, b, v.inc);
+      int ct = 0;
+      if (__any(nd)) {
+        // today's count of the pairs in reach, one per lane
+        if (nd) {
+          ct = pair_count(v.T + (size_t)a * w.w64, v.T + (size_t)b * w.w64, um, w.w64);
+          const int ub = ct > 0 ? P.p * ct + P.q * P.n_normal : -1;
+          if (ub < sb) {
+            sb = ub;
+            changed = true;
+          }
+          nd = sb >= 0 && !dominated(sb, a, b, v.inc);
+        }
+        if (h == 2) {
+          e = (e & 0xffffffffull) | ((unsigned long long)(uint32_t)sb << 32);
+          chunk_h2(v, e, nd, ct, changed);
+          sb = (int)(e >> 32);
+        } else {
+          for (;;) {
+            // the largest bound in reach first
+            nd = nd && !dominated(sb, a, b, v.inc);
+            const int top = wave_max(nd ? sb : -1);
+            if (top < 0) break;
+            const int src = __builtin_ctzll(__ballot(nd && sb == top));
+            const int pa = __builtin_amdgcn_readlane(a, src);
+            const int pb = __builtin_amdgcn_readlane(b, src);
+            const int nb = open_pair(v, pa, pb, bits);
+            if (lane == src) {
+              if (nb < sb) {
+                sb = nb;
+                changed = true;
+              }
+              nd = false;
+            }
+          }
+        }
+      }
+      if (__any(changed)) {
+        if (i < n_mine)
+          list[i] = (e & 0xffffffffull) | ((unsigned long long)(uint32_t)sb << 32);
+        const int mx = wave_max(i < n_mine ? sb : -1);
+        if (lane == 0) cmax[k0 + kc] = mx;
+      }
+    }
+  }
+
+  // the wave's best leaf stays its pool leaf
+  Slot sl = empty_slot();
+  wave_lds_sync();
+  if (v.bs >= 0) {
+    sl.s = v.bs;
+    sl.tp = v.btp;
+    sl.fp = v.bfp;
+#pragma unroll
+    for (int i = 0; i < kMaxH; ++i) sl.idx[i] = i < h ? (int)v.s.tup[i] : 0;
+  }
+  if (lane == 0) {
+    L.pool[wv] = sl;
+    wave_slot[wib] = sl;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    Slot r = wave_slot[0];
+    for (int i = 1; i < kBlock / kWave; ++i)
+      slot_take_if(r, wave_slot[i], slot_better(wave_slot[i], r));
+    // only a leaf that the incumbent does not beat can be the answer
+    const unsigned long long inc = load_incumbent(st);
+    if (r.s >= 0 && leaf_key(r.s, r.idx[0], r.idx[1]) >= inc) {
+      const uint32_t pos = atomicAdd(&L.ctl[0], 1u);
+      L.wins[pos] = r;   // one per block at most
+      __threadfence();
+    }
+    // the last block of its group reports the group
+    const uint32_t grp = blockIdx.x % kTicketGroups;
+    const uint32_t members = (gridDim.x + kTicketGroups - 1 - grp) / kTicketGroups;
+    const uint32_t groups = gridDim.x < kTicketGroups ? gridDim.x : kTicketGroups;
+    s_last = 0;
+    if (atomicAdd(&L.ctl[64 * (1 + grp)], 1u) == members - 1) {
+      __threadfence();
+      s_last = atomicAdd(&L.ctl[64 * (1 + kTicketGroups)], 1u) == groups - 1 ? 1 : 0;
+    }
+  }
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  const int n_win = (int)__hip_atomic_load(&L.ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  lazy_finish(P, w, L, h, n_win);
+}
+
+}  // namespace
+
+int lazy_levels(int h) { return kLazyLevels(h); }
+
+hipError_t launch_lazy_begin(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s) {
+  const int tiles = L.gw * w.w64;
+  int blocks = (tiles + 3) / 4;
+  if (blocks > 2048) blocks = 2048;
+  k_lazy_begin<<<blocks, kBlock, 0, s>>>(P, w, L);
+  return hipGetLastError();
+}
+
+hipError_t launch_lazy_deal(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s) {
+  unsigned long long blocks = (w.pair_cap + kDeal - 1) / kDeal;
+  if (blocks > 1024) blocks = 1024;
+  if (blocks < 1) blocks = 1;
+  k_lazy_deal<<<(int)blocks, kBlock, 0, s>>>(P, w, L);
+  return hipGetLastError();
+}
+
+hipError_t launch_lazy_round(const Problem& P, const Work& w, const LazyWork& L0, hipStream_t s) {
+  LazyWork L = L0;
+  L.wave_bytes = (int)lazy_wave_bytes(P.h);
+  const size_t lds = (size_t)L.wave_bytes * (kBlock / kWave);
+  const int blocks = L.nw / (kBlock / kWave);
+  switch (P.h) {
+    case 2: k_lazy_round<2><<<blocks, kBlock, lds, s>>>(P, w, L); break;
+    case 3: k_lazy_round<3><<<blocks, kBlock, lds, s>>>(P, w, L); break;
+    case 4: k_lazy_round<4><<<blocks, kBlock, lds, s>>>(P, w, L); break;
+    default: k_lazy_round<0><<<blocks, kBlock, lds, s>>>(P, w, L); break;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace pdfs

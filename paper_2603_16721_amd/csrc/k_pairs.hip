@@ -260,6 +260,11 @@ hipError_t launch_pairs_m(const BatchDesc* bd, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_pair_list(const Problem& P, const Work& w, hipStream_t s) {
+  k_pairs<false><<<kPersistBlocks, kBlock, 0, s>>>(P, w);
+  return hipGetLastError();
+}
+
 hipError_t launch_pairs(const Problem& P, const Work& w, hipStream_t s) {
   if (P.h == 2)
     k_pairs<true><<<kPersistBlocks, kBlock, 0, s>>>(P, w);  // h = 2 writes one slot per block

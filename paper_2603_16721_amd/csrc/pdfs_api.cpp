@@ -57,7 +57,9 @@ void release(pdfs_ctx* c) {
   void* ptrs[] = {c->Ts, c->Ns, c->perm, c->ncount, c->U, c->cols, c->act, c->flags, c->TA, c->NA,
                   c->A8, c->N8, c->pairs, c->work_pairs, c->seed_pairs, c->hist, c->cursors,
                   c->items, c->slots, c->tallies, c->st, c->recs, c->tri, c->tri_s,
-                  c->tri_rank, c->c_hist, c->deepq};
+                  c->tri_rank, c->c_hist, c->deepq, c->lz.B, c->lz.Uc, c->lz.list, c->lz.cmax,
+                  c->lz.cursor, c->lz.pool, c->lz.wins, c->lz.tcov, c->lz.uncs, c->lz.bits,
+                  c->lz.ctl, c->lz.shard};
   for (void* p : ptrs) dfree(c, p);
   if (c->h_slots && c->own_h_st) (void)hipHostFree(c->h_slots);
   for (auto& set : c->ev)
@@ -83,12 +85,13 @@ static int32_t grow_for_all_genes(pdfs_ctx* c) {
   void** bufs[] = {(void**)&c->TA, (void**)&c->NA, (void**)&c->A8, (void**)&c->N8,
                    (void**)&c->pairs, (void**)&c->work_pairs, (void**)&c->seed_pairs,
                    (void**)&c->items, (void**)&c->tri, (void**)&c->tri_s, (void**)&c->tri_rank,
-                   (void**)&c->c_hist};
+                   (void**)&c->c_hist, (void**)&c->lz.list, (void**)&c->lz.cmax};
   for (void** b : bufs) {
     dfree(c, *b);
     *b = nullptr;
   }
   c->pair_cap = c->item_cap = c->tri_cap = 0;
+  c->lz_list_n = 0;
   c->two_phase = false;
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
   c->graphs.clear();
@@ -118,24 +121,91 @@ static unsigned long long item_cap_for(unsigned long long n) {
   return ic < (1ull << 20) ? 1ull << 20 : ic;
 }
 
-// (Re)allocates the pair list (and its bound-mode work copy) and the item list
-// for n pairs; the captured rounds holding the old addresses are dropped.
+// (Re)allocates the pair list for n pairs, and the work copy and item list
+// where they were in use; the lazy rounds' shares and the captured rounds
+// holding the old addresses are dropped and re-made on demand.
 static int32_t alloc_pair_lists(pdfs_ctx* c, unsigned long long n) {
-  void** bufs[] = {(void**)&c->pairs, (void**)&c->work_pairs, (void**)&c->items};
+  const bool work = c->work_pairs != nullptr, items = c->items != nullptr;
+  void** bufs[] = {(void**)&c->pairs, (void**)&c->work_pairs, (void**)&c->items,
+                   (void**)&c->lz.list, (void**)&c->lz.cmax};
   for (void** b : bufs) {
     dfree(c, *b);
     *b = nullptr;
   }
+  c->lz_list_n = 0;
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
   c->graphs.clear();
   c->pair_cap = c->item_cap = 0;
   CK(c, dalloc(c, &c->pairs, (size_t)n));
-  if (c->prune_mode == PDFS_PRUNE_BOUND) CK(c, dalloc(c, &c->work_pairs, (size_t)n));
-  const unsigned long long ic = item_cap_for(n);
-  CK(c, dalloc(c, &c->items, (size_t)ic));
+  if (work) CK(c, dalloc(c, &c->work_pairs, (size_t)n));
+  if (items) {
+    const unsigned long long ic = item_cap_for(n);
+    CK(c, dalloc(c, &c->items, (size_t)ic));
+    c->item_cap = ic;
+  }
   c->pair_cap = n;
-  c->item_cap = ic;
   return PDFS_OK;
+}
+
+// Waves of a lazy round for a pair list of n pairs: a share of 128 pairs at
+// least, at most one block per compute unit.
+static int lazy_waves(unsigned long long n) {
+  unsigned long long nw = (n + 127) / 128;
+  nw = (nw + 3) / 4 * 4;
+  return (int)(nw > (unsigned long long)kLazyWaves ? (unsigned long long)kLazyWaves : nw);
+}
+
+static int lazy_seg(unsigned long long n, int nw) {
+  return (int)((n + nw - 1) / nw + kWave - 1) / kWave * kWave;
+}
+
+// The lazy rounds' buffers for a run of depth h at row width w64.
+static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
+  LazyWork& L = c->lz;
+  L.nw = lazy_waves(c->pair_cap);
+  L.seg = lazy_seg(c->pair_cap, L.nw);
+  L.gw = (c->nA_max + 63) / 64 > 0 ? (c->nA_max + 63) / 64 : 1;
+  L.levels = lazy_levels(h);
+  auto grow = [&](auto** p, size_t& have, size_t n) -> int32_t {
+    if (*p && have >= n) return PDFS_OK;
+    dfree(c, *p);
+    *p = nullptr;
+    have = 0;
+    CK(c, dalloc(c, p, n));
+    have = n;
+    return PDFS_OK;
+  };
+  if (!L.Uc) {
+    CK(c, dalloc(c, &L.Uc, (size_t)kMaxW64));
+    CK(c, dalloc(c, &L.cursor, (size_t)kMaxCount + 1));
+    CK(c, dalloc(c, &L.pool, (size_t)kLazyWaves));
+    CK(c, dalloc(c, &L.wins, (size_t)kLazyWaves));
+    CK(c, dalloc(c, &L.tcov, (size_t)64 * kMaxW64));
+    CK(c, dalloc(c, &L.uncs, (size_t)c->n_tumor + 2));
+    CK(c, dalloc(c, &L.ctl, (size_t)kLazyCtl));
+    CK(c, dalloc(c, &L.shard, (size_t)kIncShards * kCursorStride));
+  }
+  const size_t ln = (size_t)L.nw * L.seg;
+  if (!L.list || c->lz_list_n < ln) {
+    dfree(c, L.cmax);
+    L.cmax = nullptr;
+    int32_t rc = grow(&L.list, c->lz_list_n, ln);
+    if (rc != PDFS_OK) return rc;
+    CK(c, dalloc(c, &L.cmax, ln / kWave));
+  }
+  int32_t rc = grow(&L.B, c->lz_b_n, (size_t)64 * w64 * L.gw);
+  if (rc != PDFS_OK) return rc;
+  if (h >= 4) rc = grow(&L.bits, c->lz_bits_n, (size_t)L.nw * L.levels * L.gw);
+  return rc;
+}
+
+// Score-bound pruning runs as lazy rounds, whose bounds carry over from one
+// round to the next.  A single round of h = 2 is left to the pair table, which
+// scores every pair in its own epilogue: 115 us against 134 us with the lists
+// (G = 500); a cover of 82 rounds at G = 5000 takes 1.9 ms on the lists, 5.4 ms
+// with a table per round.
+static bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds) {
+  return c->prune_mode == PDFS_PRUNE_BOUND && (h >= 3 || (h == 2 && max_rounds != 1));
 }
 
 // A round emitted `emitted` pairs into a shorter list: grows the list to that
@@ -155,15 +225,21 @@ static int32_t regrow_pairs(pdfs_ctx* c, unsigned long long emitted) {
 }
 
 // Allocates the pair list, item list and normal bytes when a call first needs
-// them.
-int32_t ensure_workspace(pdfs_ctx* c, int h) {
+// them (lazy: the lazy rounds' pair list only).
+int32_t ensure_workspace(pdfs_ctx* c, int h, bool lazy) {
   if (c->prune_mode == PDFS_PRUNE_NONE) {
     const int32_t rc = grow_for_all_genes(c);
     if (rc != PDFS_OK) return rc;
   }
-  if (h >= 3 && !c->pairs) {
+  if (h >= (lazy ? 2 : 3) && !c->pairs) {
     const int32_t rc = alloc_pair_lists(c, pair_cap_for(c->nA_max, c->pair_cap_hint));
     if (rc != PDFS_OK) return rc;
+  }
+  if (lazy) return PDFS_OK;
+  if (h >= 3 && !c->items) {
+    const unsigned long long ic = item_cap_for(c->pair_cap);
+    CK(c, dalloc(c, &c->items, (size_t)ic));
+    c->item_cap = ic;
   }
   if (h >= 3 && !c->seed_pairs) CK(c, dalloc(c, &c->seed_pairs, (size_t)kSeedCap));
   if (h >= 3 && c->prune_mode == PDFS_PRUNE_BOUND && !c->work_pairs)
@@ -308,6 +384,15 @@ int32_t ctx_fail(pdfs_ctx* c, int32_t code, const std::string& msg) { return fai
 // chunk's event set when timing.
 static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int chunk, int slot) {
   const Run& r = c->run;
+  if (r.lazy) {
+    // one launch per round
+    for (int k = 0; k < chunk; ++k) {
+      if (c->time_kernels) CK(c, hipEventRecord(c->ev[slot][k][2], c->stream));
+      CK(c, launch_lazy_round(P, w, c->lz, c->stream));
+      if (c->time_kernels) CK(c, hipEventRecord(c->ev[slot][k][3], c->stream));
+    }
+    return PDFS_OK;
+  }
   if (c->use_graphs && !c->time_kernels) {
     const auto key = std::make_tuple(P.h, w.w64, r.p, r.q, r.target, c->prune_mode,
                                      c->chunk_items, c->seed_pairs_n, c->two_phase,
@@ -337,6 +422,23 @@ static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int 
     const int32_t rc = enqueue_round(c, P, w, c->ev[slot][k], c->two_phase);
     if (rc != PDFS_OK) return rc;
   }
+  return PDFS_OK;
+}
+
+// Start of a lazy run: the run's rows and pair table, made once, and the pairs
+// dealt to the round kernel's waves.
+static int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, int slot) {
+  hipStream_t s = c->stream;
+  const bool tk = c->time_kernels;
+  CK(c, launch_round_begin(P, w, s));
+  CK(c, launch_active(P, w, s));
+  CK(c, launch_gather_active(P, w, true, false, s));
+  if (tk) CK(c, hipEventRecord(c->ev[slot][0][0], s));
+  CK(c, launch_pair_list(P, w, s));
+  if (tk) CK(c, hipEventRecord(c->ev[slot][0][1], s));
+  CK(c, launch_lazy_begin(P, w, c->lz, s));
+  CK(c, launch_pair_hist(w, s));
+  CK(c, launch_lazy_deal(P, w, c->lz, s));
   return PDFS_OK;
 }
 
@@ -423,20 +525,27 @@ int32_t grow_row_width(pdfs_ctx* c, int w64) {
 }
 
 int32_t prepare_run(pdfs_ctx* c, int h, int n_unc) {
-  const int32_t rc = ensure_workspace(c, h);
+  const int32_t rc = ensure_workspace(c, h, false);
   if (rc != PDFS_OK) return rc;
   return size_triples(c, h, n_unc);
 }
 
 int32_t run_start(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int max_rounds,
                   int n_unc) {
-  int32_t rc = prepare_run(c, h, n_unc);
+  const bool lazy = runs_lazy(c, h, max_rounds);
+  const int w64 = dfs_row_words(words(n_unc > 0 ? n_unc : 1));
+  int32_t rc = lazy ? ensure_workspace(c, h, true) : prepare_run(c, h, n_unc);
+  if (rc == PDFS_OK && lazy) {
+    if (w64 < 0 || w64 > c->w64_max) return fail(c, PDFS_ERR_UNSUPPORTED, "row too wide");
+    rc = ensure_lazy(c, h, w64);
+  }
   if (rc != PDFS_OK) return rc;
   Run& r = c->run;
   // chunks of an earlier run still in flight are no-ops queued before
   // this run's work; their slots are simply reused in stream order
   r = Run();
   r.h = h; r.p = p; r.q = q; r.target = target; r.max_rounds = max_rounds; r.n_unc = n_unc;
+  r.lazy = lazy; r.w64 = w64;
   const Problem P = make_problem(c, h, p, q);
   Work w0 = make_work(c, 1, target);
   CK(c, launch_run_begin(P, w0, max_rounds, c->stream));
@@ -453,13 +562,20 @@ int32_t run_enqueue(pdfs_ctx* c) {
   Run& r = c->run;
   while (r.active && r.inflight < kDepth) {
     if (r.max_rounds > 0 && r.enqueued >= r.max_rounds) break;
-    const int w64 = dfs_row_words(words(r.n_unc > 0 ? r.n_unc : 1));
+    // (a lazy run keeps its first round's rows)
+    const int w64 = r.lazy ? r.w64 : dfs_row_words(words(r.n_unc > 0 ? r.n_unc : 1));
     if (w64 < 0 || w64 > c->w64_max) return fail(c, PDFS_ERR_UNSUPPORTED, "row too wide");
     int n = r.chunk;
     if (r.max_rounds > 0 && n > r.max_rounds - r.enqueued) n = r.max_rounds - r.enqueued;
     const int slot = c->next_slot;
     const Problem P = make_problem(c, r.h, r.p, r.q);
     const Work w = make_work(c, w64, r.target);
+    if (r.lazy && !r.listed) {
+      const int32_t rc = enqueue_lists(c, P, w, slot);
+      if (rc != PDFS_OK) return rc;
+      r.listed = true;
+      r.time_pairs = c->time_kernels;
+    }
     const int32_t rc = enqueue_rounds(c, P, w, n, slot);
     if (rc != PDFS_OK) return rc;
     CK(c, hipMemcpyAsync(&c->h_slots[slot], c->st, sizeof(RoundState), hipMemcpyDeviceToHost,
@@ -497,7 +613,8 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
     for (int k = 0; k < ran && k < chunk; ++k) {
       hipEvent_t* ev = c->ev[slot][k];
       float ms = 0.f;
-      if (r.h >= 2) {
+      if (r.h >= 2 && (!r.lazy || r.time_pairs)) {
+        r.time_pairs = false;
         CK(c, hipEventElapsedTime(&ms, ev[0], ev[1]));
         c->kernel_ns[0] += (int64_t)(ms * 1e6);
         c->kernel_launches[0] += 1;
@@ -507,7 +624,7 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
         c->kernel_ns[1] += (int64_t)(ms * 1e6);
         c->kernel_launches[1] += 1;
       }
-      if (r.h >= 3 && c->two_phase) {
+      if (r.h >= 3 && !r.lazy && c->two_phase) {
         CK(c, hipEventElapsedTime(&ms, ev[4], ev[3]));
         c->kernel_ns[2] += (int64_t)(ms * 1e6);
         c->kernel_launches[2] += 1;
@@ -530,6 +647,8 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
     const unsigned long long emitted = st.n_pairs;
     const int executed = st.executed;
     int32_t rc = regrow_pairs(c, emitted);   // waits for the chunks in flight
+    if (rc == PDFS_OK && r.lazy) rc = ensure_lazy(c, r.h, r.w64);
+    r.listed = false;
     if (rc != PDFS_OK) {
       r.active = false;
       return rc;
@@ -692,7 +811,11 @@ int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds) 
     CK(c, hipMemcpyAsync(recs.data(), c->recs, sizeof(RoundRecord) * recs.size(),
                          hipMemcpyDeviceToHost, c->stream));
     CK(c, hipStreamSynchronize(c->stream));
-    for (int i = 0; i < n; ++i) fill_combo(&out[i], recs[i], c->run.h);
+    for (int i = 0; i < n; ++i) {
+      if (c->run.lazy)   // recorded by sorted index only
+        for (int k = 0; k < c->run.h; ++k) recs[i].genes[k] = c->h_perm[recs[i].sorted_idx[k]];
+      fill_combo(&out[i], recs[i], c->run.h);
+    }
   }
   return PDFS_OK;
 }
@@ -708,12 +831,20 @@ size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int 
   b += (size_t)kSlotPhases * kPersistBlocks * kTallyN * 8;
   if (h >= 3) {
     const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
-    const size_t items = (size_t)item_cap_for(pairs);
-    b += pairs * 8 * (prune_mode == PDFS_PRUNE_BOUND ? 2 : 1) + items * sizeof(Item) +
-         (size_t)kSeedCap * 8;
+    b += pairs * 8;
+    if (prune_mode != PDFS_PRUNE_BOUND)
+      b += (size_t)item_cap_for(pairs) * sizeof(Item) + (size_t)kSeedCap * 8;
+  }
+  if (h >= 2 && prune_mode == PDFS_PRUNE_BOUND) {   // lazy rounds
+    const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
+    const size_t nw = (size_t)lazy_waves(pairs), gw = (size_t)(nA_max + 63) / 64;
+    if (h == 2) b += pairs * 8;
+    b += nw * (size_t)lazy_seg(pairs, (int)nw) * 9 + (size_t)w64max * 64 * gw * 8;
+    if (h >= 4) b += nw * (size_t)lazy_levels(h) * gw * 8;
+    b += (size_t)kLazyWaves * sizeof(Slot) * 2;
   }
   if (h == 2) b += rows * (size_t)unpacked_row_bytes((int)wn);
-  if (h >= 5) {
+  if (h >= 5 && prune_mode != PDFS_PRUNE_BOUND) {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)

@@ -204,6 +204,39 @@ struct Work {
   Slot* slot_log;
 };
 
+// ---------------------------------------------------------------- lazy rounds
+// One address serves its atomics one at a time (about 60 ns each), so what
+// every block of a round updates is spread: the incumbent goes through shards
+// (a wave goes on to the round's own only if it raised its shard), the count
+// of finished blocks through groups.
+constexpr int kLazyWaves = 1024;   // waves of a lazy round at most
+constexpr int kIncShards = 32;
+constexpr int kTicketGroups = 32;
+constexpr int kLazyCtl = 64 * (2 + kTicketGroups);
+
+// Run-long workspace of the lazy rounds (k_lazy.hip), in the index space of
+// the run's first round (its active genes, its uncovered samples).
+struct LazyWork {
+  uint64_t* B;                // [64 * w64][gw] a sample's genes, one bit each
+  uint64_t* Uc;               // [kMaxW64] uncovered mask
+  unsigned long long* list;   // [nw][seg] pairs a | b << 16 | bound << 32
+  int32_t* cmax;              // [nw][seg / 64] a chunk's largest bound
+  uint32_t* cursor;           // [kMaxCount + 1] pairs of a count dealt so far
+  Slot* pool;                 // [nw] a wave's best known leaf
+  Slot* wins;                 // [nw / 4] leaves that may be the round's answer
+  int32_t* tcov;              // [64 * kMaxW64] the round that covered a sample
+  int32_t* uncs;              // [n_tumor + 2] uncovered samples at a round's start
+  uint64_t* bits;             // [nw][levels][gw] candidate bitmaps of the general walk
+  unsigned long long* shard;  // [kIncShards * kCursorStride] incumbents of a part of the blocks
+  uint32_t* ctl;              // [0] entries of wins; [64 * (1 + i)] blocks of group i done;
+                              // [64 * (1 + kTicketGroups)] groups done
+  int32_t gw;                 // words of a row of B
+  int32_t nw;                 // waves of the round kernel (a multiple of 4)
+  int32_t seg;                // entries of a wave's share (a multiple of 64)
+  int32_t levels;             // bitmaps per wave
+  int32_t wave_bytes;         // LDS per wave (set by the launcher)
+};
+
 // ---------------------------------------------------------------- batched
 // Many cohorts' rounds in one launch per round step.  Light steps run one
 // block row per instance (blockIdx.y); the depth-first steps drain one shared
@@ -250,6 +283,9 @@ hipError_t launch_gather_active(const Problem& P, const Work& w, bool unpack_tum
                                 bool unpack_normal, hipStream_t s);
 hipError_t launch_h1(const Problem& P, const Work& w, hipStream_t s);
 hipError_t launch_pairs(const Problem& P, const Work& w, hipStream_t s);
+// the pair list at any h >= 2 (launch_pairs scores the pairs at h = 2)
+hipError_t launch_pair_list(const Problem& P, const Work& w, hipStream_t s);
+hipError_t launch_pair_hist(const Work& w, hipStream_t s);
 hipError_t launch_seed_select(const Problem& P, const Work& w, hipStream_t s);
 hipError_t launch_make_items(const Problem& P, const Work& w, bool seed, hipStream_t s);
 hipError_t launch_filter_pairs(const Problem& P, const Work& w, hipStream_t s);
@@ -266,6 +302,11 @@ hipError_t launch_sort_triples(const Work& w, hipStream_t s);
 hipError_t launch_dfs4_tiles(const Problem& P, const Work& w, hipStream_t s);
 hipError_t launch_finish_round(const Problem& P, const Work& w, int phase_mask, int tally_mask,
                                hipStream_t s);
+// Lazy rounds: the run's lists from the pair list, then one launch per round.
+int lazy_levels(int h);
+hipError_t launch_lazy_begin(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
+hipError_t launch_lazy_deal(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
+hipError_t launch_lazy_round(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
 hipError_t launch_clear_slots(Slot* slots, int n, hipStream_t s);
 // n32 32-bit words at p set to zero by a fill kernel (no memset node)
 hipError_t launch_zero_u32(void* p, size_t n32, hipStream_t s);

@@ -43,6 +43,10 @@ struct Run {
   int enqueued = 0;         // rounds enqueued by this run
   int inflight = 0;         // chunks queued and not yet read
   int executed_before = 0;
+  bool lazy = false;        // lazy rounds (k_lazy.hip)
+  bool listed = false;      // lazy rounds: the run's pair lists are queued
+  int w64 = 1;              // lazy rounds: row width of the run
+  bool time_pairs = false;  // lazy rounds: the next chunk read holds the pair table's events
   int32_t status = PDFS_OK;
   std::chrono::steady_clock::time_point t_prev;   // when the host last saw a chunk end
 };
@@ -86,6 +90,9 @@ struct pdfs_ctx {
   uint32_t* c_hist = nullptr;
   uint32_t* deepq = nullptr;   // h >= 5 leaf-prefix rings
   unsigned long long tri_cap = 0;
+  // lazy rounds: buffers sized by the pair list, the row width and h
+  pdfs::LazyWork lz = {};
+  size_t lz_list_n = 0, lz_b_n = 0, lz_bits_n = 0;   // entries held by list, B and bits
   bool two_phase = false;              // this run uses the two-phase path
   pdfs::Slot* slots = nullptr;
   unsigned long long* tallies = nullptr;

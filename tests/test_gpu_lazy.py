@@ -1,0 +1,44 @@
+"""Lazy rounds (k_lazy.hip) at the edges of their paths, against the oracle:
+pairs with more samples than one mask word (the general walk), more candidates
+than a level list holds, every list depth, candidate words past one wave, and
+runs resumed from a mask on the same context.  Results are whole numbers, so
+the comparison is equality."""
+import numpy as np
+import pytest
+
+from oracle import cpu
+from paper_2603_16721_amd import synth
+from tests.helpers import mask_of_bits
+from tests.test_gpu_parity import _same_rounds, pdfs  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [
+    # G, n_tumor, n_normal, density, h, alpha, max_rounds
+    (50, 30, 10, 0.3, 2, (1, 10), 0),
+    (300, 70, 33, 0.5, 3, (1, 10), 0),       # leaves straight from the slices
+    (300, 1280, 20, 0.3, 3, (2, 3), 3),      # 11 bit slices
+    (70, 200, 60, 0.5, 4, (1, 10), 0),       # more than 64 samples below a pair
+    (330, 12, 40, 0.6, 4, (1, 10), 2),       # more than 256 candidates, few samples
+    (64, 64, 5, 1.0, 4, (1, 10), 0),         # every row full: exactly 64 samples
+    (65, 65, 5, 1.0, 5, (1, 10), 0),         # every row full: 65
+    (130, 400, 20, 0.4, 5, (1, 10), 2),
+    (40, 150, 64, 0.55, 6, (1, 10), 0),
+    (34, 200, 40, 0.6, 9, (1, 10), 2),
+    (9, 40, 512, 0.7, 9, (3, 1), 0),         # one combination
+    (4200, 30, 40, 0.02, 4, (1, 10), 0),     # more than 64 candidate words
+]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=[f"G{c[0]}_nt{c[1]}_h{c[4]}" for c in EDGES])
+def test_lazy_edges(pdfs, case):  # noqa: F811
+    G, nt, nn, d, h, (p, q), mr = case
+    I = synth.random_tiny(31, G, nt, nn, d, h, alpha=(p, q))
+    T, N = I.packed()
+    mask = mask_of_bits(np.arange(nt) % 3 != 0)
+    with pdfs.Solver(T, N, nt, nn, "bound") as s:
+        for u in (None, mask):
+            exp = cpu.wsc(T, N, nt, nn, h, p, q, mode="bound", max_rounds=mr, U0=u)
+            got, _, final = s.wsc(h, p, q, 0, mr, u)
+            _same_rounds(got, exp.rounds)
+            assert np.array_equal(final, exp.final_uncovered)
