@@ -6,11 +6,15 @@ Alg. 1, each round's argmax done by the depth-first search of Alg. 2) of the
 h=4, G=20,000 workload (1,000 tumour / 500 normal samples, log-normal gene
 rates, 10 planted quadruples, alpha = 1/10), inputs already resident in HBM.
 
-value = h-subsets scored per second: the leaves the search scores (h-subsets
+value = h-subsets scored per second: the leaves Alg. 2 scores (h-subsets
 whose cover meets the uncovered tumour samples), summed over all rounds, per
 second of solve time, with the paper's empty-intersection pruning (the mode
-whose scored set is canonical).  The exact bound-pruned solve of the same
-workload (the library default) is timed beside it.
+whose scored set is canonical).  The library settles these leaves exactly
+without forming each of them in every round: the argmax opens the pairs whose
+score bound reaches the best leaf, and the count of the leaves is one weighted
+enumeration per solve (checked here against the oracle's stored count).  The
+exact bound-pruned solve of the same workload (the library default, without
+the counts) is timed beside it.
 
 Beside the step: the bound-pruned solve, whole solves of the two smaller
 workloads, the pruned-vs-exhaustive first rounds, deeper combinations, the
@@ -36,32 +40,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = ("h-hit subsets scored/s + WSC solve time, batched/served vs plain; "
           "p50/p99 latency")
-VALU_PEAK = 256 * 4 * 16 * 2.4e9          # lane-instructions/s (CUs x SIMDs x lanes x clock)
 MFMA_I8_PEAK_OPS = 5.0e15                 # dense int8 MFMA, ops/s (2 per multiply-add)
-
-# HBM traffic of the depth-first stage, per launch (one round), from two
-# rocprofv3 --pmc runs of two h4_G20000 solves (FETCH_SIZE, WRITE_SIZE; KiB
-# summed over both solves' stage kernels), each scaled by what the counter
-# reads for a 1 GiB device copy (FETCH_SIZE reads half the bytes, WRITE_SIZE
-# all of them); profiles/dfs_stage_h4_G20000_traffic.md.
-# Valid for the stage kernels' sources it was taken on (hash below); reported
-# as null once they change.
-STAGE_SOURCES = ("k_dfs.hip", "k_tri.hip", "dfs_core.h", "slot_reduce.h", "pdfs_dev.h")
-STAGE_TRAFFIC = {"sources_sha256_16": "3ce6828f2e443e7f", "workload": "h4_G20000",
-                 "bytes_per_launch": (2.0 * 8726112 + 1.0 * 24320177) / 2 * 1024 / 133}
-
-
-def stage_traffic(workload):
-    import hashlib
-    h = hashlib.sha256()
-    here = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2603_16721_amd", "csrc")
-    for f in STAGE_SOURCES:
-        with open(os.path.join(here, f), "rb") as fh:
-            h.update(fh.read())
-    if h.hexdigest()[:16] != STAGE_TRAFFIC["sources_sha256_16"] or \
-            workload != STAGE_TRAFFIC["workload"]:
-        return None
-    return STAGE_TRAFFIC["bytes_per_launch"]
+HBM_PEAK = 8.0e12                         # bytes/s
 
 
 def words(n):
@@ -80,21 +60,6 @@ def oracle_subsets_scored(workload):
         return None
     c = cases.get(f"{workload}_empty_all_rounds")
     return None if c is None else int(c["nonempty"][c["h"]])
-
-
-def dfs_alg_ops(st, h, n_normal, depth3_ops_per_word=4):
-    """Algorithmic integer lane-ops of the depth-first kernels for the work they
-    were given.  A visited node of depth 3 or 4 costs one W-word AND plus a
-    popcount-accumulate, 4 lane-ops per 64-bit word of its round's compacted
-    row (W = ceil(|U|/64)); a scored leaf adds its score and comparison (4)
-    and, when its normal prefix is non-empty, an AND plus popcount per normal
-    word.  depth3_ops_per_word=2 gives the smaller count the h = 4 kernels
-    execute for a depth-3 node (a fused and-or emptiness test, no popcount)."""
-    w3 = st["dfs_visit_words3"]     # sum of visits x ceil(|U|/64)
-    w4 = st["dfs_visit_words4"]
-    ops = (depth3_ops_per_word if h == 4 else 4) * w3 + 4 * w4
-    ops += 4 * st["dfs_leaves"] + 4 * words(n_normal) * st["dfs_fp_leaves"]
-    return ops
 
 
 # ---- CPU baseline: the oracle (unmodified, pinned) on every host core.  The
@@ -429,7 +394,7 @@ def main():
         rounds, st, _ = sv.wsc(h, p, q, target=inst.target_covered)
         return rounds, st
 
-    # ---- paper's walk (empty-intersection pruning): the timed steps
+    # ---- empty-intersection pruning with its counters: the timed steps
     sv = pdfs.Solver(Td, Nd, inst.n_tumor, inst.n_normal, "empty", 0, stream.cuda_stream,
                      time_kernels=True)
     for i in range(args.warmup):
@@ -459,25 +424,20 @@ def main():
     ms_per_step = 1e3 * elapsed / args.steps
     value = scored * args.steps / elapsed
 
-    # dominant stage: the depth-first kernels of each round (HIP events on the
-    # library's stream around the main DFS kernel, the bucketing kernels and
-    # the depth-4 tile kernel); index 2 = the tile kernel alone
-    dfs_ns = sum(s["kernel_ns"][1] for s in stats)
-    dfs_launches = sum(s["kernel_launches"][1] for s in stats)
-    tile_ns = sum(s["kernel_ns"][2] for s in stats)
-    tile_launches = sum(s["kernel_launches"][2] for s in stats)
-    ops = sum(dfs_alg_ops(s, h, inst.n_normal) for s in stats)
-    ops_exec = sum(dfs_alg_ops(s, h, inst.n_normal, depth3_ops_per_word=2) for s in stats)
-    achieved = ops / (dfs_ns * 1e-9) if dfs_ns else 0.0
-    achieved_exec = ops_exec / (dfs_ns * 1e-9) if dfs_ns else 0.0
+    # the rounds: one launch each (HIP events on the library's stream), and
+    # the pair table made once per solve
+    round_ns = sum(s["kernel_ns"][1] for s in stats)
+    round_launches = max(1, sum(s["kernel_launches"][1] for s in stats))
     pair_ns = sum(s["kernel_ns"][0] for s in stats)
-    pair_ops = 2 * sum(s["pair_macs"] for s in stats)
-
-    measured_peak = pdfs.pdfs_measure_int_peak(0)
-    # the roof is the higher of the datasheet figure and the rate a probe of
-    # the kernels' own and + popcount pair reaches on this device
-    roof = max(VALU_PEAK, measured_peak)
-    traffic = stage_traffic(inst.name)
+    pair_launches = max(1, sum(s["kernel_launches"][0] for s in stats))
+    # the table's own work: every pair of the first round's active genes times
+    # the first round's uncovered samples (the sum over rounds, pair_macs, is
+    # what Alg. 2 would redo every round)
+    n_active = int((T != 0).any(axis=1).sum())
+    pair_ops = 2 * (n_active * (n_active - 1) // 2) * inst.n_tumor * pair_launches
+    # what a solve cannot do without: the cohort's rows, read once
+    cohort_bytes = 8 * inst.G * (words(inst.n_tumor) + words(inst.n_normal))
+    achieved = cohort_bytes * args.steps / elapsed
 
     # ---- pruned vs exhaustive walk, first greedy round of the two smaller
     # workloads (the exhaustive walk of h4_G20000 visits ~6.7e15 leaves a round)
@@ -604,29 +564,19 @@ def main():
         "bound_effective_subsets_per_s": (scored / (bound_ms * 1e-3)) if bound_ms else None,
         # Alg. 2's visited depth-h nodes against the C(G,h) subsets of every round
         "visited_fraction": stats[0]["visited"][h] / (len(rounds) * math.comb(inst.G, h)),
-        "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": roof / 1e12,
-                     "unit": "Tlane-op/s", "frac": achieved / roof,
-                     "traffic": traffic,
-                     "traffic_unit": "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-scaled)",
-                     "traffic_GBps": (traffic / (dfs_ns / max(1, dfs_launches) * 1e-9) / 1e9
-                                      if traffic and dfs_ns else None),
-                     "kernel": "depth-first stage per round: k_tri_begin, k_dfs<4,W>, "
-                               "k_scan_c, k_scatter_c, k_dfs4_tiles<W>",
-                     "launches": dfs_launches,
-                     "avg_launch_ms": (dfs_ns / max(1, dfs_launches)) * 1e-6,
-                     "tile_kernel_avg_ms": (tile_ns / max(1, tile_launches)) * 1e-6,
-                     "ops_per_solve": ops // args.steps,
-                     "peak_datasheet": VALU_PEAK / 1e12,
-                     # the and + popcount pair measured by a probe kernel on this device
-                     "peak_measured": measured_peak / 1e12,
-                     "frac_of_datasheet": achieved / VALU_PEAK,
-                     # depth-3 nodes of h = 4 charged at the and-or test the kernel runs
-                     "frac_depth3_executed": achieved_exec / roof},
+        # A solve is a chain of dependent rounds of one launch each; its
+        # compulsory traffic is a few MB, so neither a bandwidth nor an
+        # arithmetic rate bounds it but the rounds' latency (avg_launch_ms).
+        "roofline": {"bound": "hbm", "achieved": achieved / 1e12, "peak": HBM_PEAK / 1e12,
+                     "unit": "TB/s", "frac": achieved / HBM_PEAK, "traffic": None,
+                     "compulsory_bytes_per_solve": cohort_bytes,
+                     "kernel": "k_lazy_round, one launch per greedy round",
+                     "launches": round_launches,
+                     "avg_launch_ms": round_ns / round_launches * 1e-6},
         "pair_table": {"bound": "mfma", "achieved": pair_ops / max(1e-12, pair_ns * 1e-9) / 1e12,
                        "peak": MFMA_I8_PEAK_OPS / 1e12, "unit": "TOP/s (int8)",
                        "frac": pair_ops / max(1e-12, pair_ns * 1e-9) / MFMA_I8_PEAK_OPS,
-                       "avg_launch_ms": pair_ns / max(1, sum(s["kernel_launches"][0]
-                                                             for s in stats)) * 1e-6},
+                       "avg_launch_ms": pair_ns / pair_launches * 1e-6},
     }
     if exhaustive is not None:
         out["exhaustive_vs_pruned_round1"] = exhaustive

@@ -19,7 +19,7 @@ BUILD = os.path.join(ROOT, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["k_round.hip", "k_pairs.hip", "k_dfs.hip", "k_tri.hip", "k_deep.hip", "k_lazy.hip",
+SOURCES = ["k_round.hip", "k_pairs.hip", "k_dfs.hip", "k_tri.hip", "k_deep.hip", "k_lazy.hip", "k_count.hip",
            "k_probe.hip",
            "pdfs_api.cpp", "pdfs_batch.cpp", "pdfs_noalloc.hip"]
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-result", f"--offload-arch={ARCH}",

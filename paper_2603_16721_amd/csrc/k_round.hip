@@ -154,6 +154,16 @@ __global__ void k_normal_counts(const uint64_t* __restrict__ Ns, int G, int wn, 
   ncount[g] = c;
 }
 
+__global__ __launch_bounds__(256) void k_total_bits(const uint64_t* __restrict__ Ts, size_t words,
+                                                    RoundState* st) {
+  unsigned long long c = 0;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < words;
+       i += (size_t)gridDim.x * blockDim.x)
+    c += __popcll(Ts[i]);
+  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+  if ((threadIdx.x & 63) == 0 && c) atomicAdd(&st->tumor_bits, c);
+}
+
 __global__ void k_check_pad(const uint64_t* __restrict__ T, int64_t ts, int G, int n,
                             int* __restrict__ bad) {
   int g = blockIdx.x * blockDim.x + threadIdx.x;
@@ -682,6 +692,11 @@ hipError_t launch_gather_sorted(const uint64_t* T, int64_t ts, const uint64_t* N
 hipError_t launch_normal_counts(const uint64_t* Ns, int G, int wn, int32_t* ncount,
                                 hipStream_t s) {
   k_normal_counts<<<(G + 255) / 256, 256, 0, s>>>(Ns, G, wn, ncount);
+  return hipGetLastError();
+}
+
+hipError_t launch_total_bits(const uint64_t* Ts, size_t words, RoundState* st, hipStream_t s) {
+  k_total_bits<<<32, 256, 0, s>>>(Ts, words, st);
   return hipGetLastError();
 }
 

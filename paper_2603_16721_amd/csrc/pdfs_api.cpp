@@ -59,7 +59,9 @@ void release(pdfs_ctx* c) {
                   c->items, c->slots, c->tallies, c->st, c->recs, c->tri, c->tri_s,
                   c->tri_rank, c->c_hist, c->deepq, c->lz.B, c->lz.Uc, c->lz.list, c->lz.cmax,
                   c->lz.cursor, c->lz.pool, c->lz.wins, c->lz.tcov, c->lz.uncs, c->lz.bits,
-                  c->lz.ctl, c->lz.shard};
+                  c->lz.ctl, c->lz.shard, c->cw.order, c->cw.tt, c->cw.wc, c->cw.pref, c->cw.kc,
+                  c->cw.off, c->cw.ecnt, c->cw.genes, c->cw.q, c->cw.tg, c->cw.seg_v,
+                  c->cw.seg_w, c->cw.tab_v, c->cw.tab_w, c->cw.bits};
   for (void* p : ptrs) dfree(c, p);
   if (c->h_slots && c->own_h_st) (void)hipHostFree(c->h_slots);
   for (auto& set : c->ev)
@@ -199,13 +201,68 @@ static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
   return rc;
 }
 
-// Score-bound pruning runs as lazy rounds, whose bounds carry over from one
-// round to the next.  A single round of h = 2 is left to the pair table, which
-// scores every pair in its own epilogue: 115 us against 134 us with the lists
-// (G = 500); a cover of 82 rounds at G = 5000 takes 1.9 ms on the lists, 5.4 ms
-// with a table per round.
+// Sums along the samples' gene lists that the counters keep (k_count.hip).
+static size_t count_sums(int h) { return h >= 4 ? (size_t)(h - 3) + (h == 4 ? 2 : 0) : 0; }
+
+// Runs under score-bound and empty-intersection pruning go out as lazy rounds,
+// whose bounds carry over from one round to the next; an empty-intersection
+// run takes its counters from one enumeration after the rounds (its lists must
+// stay under kMaxCountBytes; G = 20000 at 66 mutations a sample needs 2 MB).
+// A single round of h = 2 is left to the pair table, which scores every pair
+// in its own epilogue: 115 us against 134 us with the lists (G = 500); a cover
+// of 82 rounds at G = 5000 takes 1.9 ms on the lists, 5.4 ms with a table per
+// round.
+constexpr size_t kMaxCountBytes = (size_t)1 << 30;
+
 static bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds) {
-  return c->prune_mode == PDFS_PRUNE_BOUND && (h >= 3 || (h == 2 && max_rounds != 1));
+  if (h < 2 || (h == 2 && max_rounds == 1)) return false;
+  if (c->prune_mode == PDFS_PRUNE_BOUND) return true;
+  return c->prune_mode == PDFS_PRUNE_EMPTY &&
+         c->tumor_bits * (8 * count_sums(h) + 2) <= kMaxCountBytes;
+}
+
+// The counters' buffers for a run of `rounds` rounds of depth h.
+static int32_t ensure_count(pdfs_ctx* c, int h, int w64, int rounds) {
+  CountWork& C = c->cw;
+  auto grow = [&](auto** p, size_t& have, size_t n) -> int32_t {
+    if (*p && have >= n) return PDFS_OK;
+    dfree(c, *p);
+    *p = nullptr;
+    have = 0;
+    CK(c, dalloc(c, p, n));
+    have = n;
+    return PDFS_OK;
+  };
+  if (!C.order) {
+    CK(c, dalloc(c, &C.order, (size_t)64 * kMaxW64));
+    CK(c, dalloc(c, &C.tt, (size_t)64 * kMaxW64));
+    CK(c, dalloc(c, &C.wc, (size_t)kCountMaxT + 1));
+    CK(c, dalloc(c, &C.kc, (size_t)64 * kMaxW64));
+    CK(c, dalloc(c, &C.off, (size_t)64 * kMaxW64));
+    CK(c, dalloc(c, &C.ecnt, (size_t)64 * kMaxW64 * 16));
+    CK(c, dalloc(c, &C.genes, (size_t)c->tumor_bits));
+    CK(c, dalloc(c, &C.tg, (size_t)count_segments(c->G) * 512));
+  }
+  C.q_n = (size_t)c->tumor_bits;
+  int32_t rc = grow(&C.pref, c->cw_pref_n, (size_t)64 * w64 * c->lz.gw);
+  const size_t sums = count_sums(h);
+  if (rc == PDFS_OK && sums > 0) rc = grow(&C.q, c->cw_q_n, sums * C.q_n);
+  C.sv = C.q ? C.q + C.q_n : nullptr;
+  C.sw = C.q ? C.q + 2 * C.q_n : nullptr;
+  if (rc == PDFS_OK && (h == 3 || h == 4)) {
+    const size_t seg = (size_t)count_segments(c->nA_max) * (rounds + 1);
+    const size_t tab = count_table_rows(c->nA_max) * (size_t)(rounds + 1);
+    size_t n = c->cw_seg_n;
+    rc = grow(&C.seg_v, n, seg);
+    if (rc == PDFS_OK) rc = grow(&C.seg_w, c->cw_seg_n, seg);
+    n = c->cw_tab_n;
+    if (rc == PDFS_OK) rc = grow(&C.tab_v, n, tab);
+    if (rc == PDFS_OK) rc = grow(&C.tab_w, c->cw_tab_n, tab);
+  }
+  C.waves = kCountWaves / c->lz.nw * c->lz.nw;
+  if (rc == PDFS_OK && h >= 4)
+    rc = grow(&C.bits, c->cw_bits_n, (size_t)C.waves * c->lz.levels * c->lz.gw);
+  return rc;
 }
 
 // A round emitted `emitted` pairs into a shorter list: grows the list to that
@@ -560,7 +617,7 @@ int32_t run_start(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int ma
 // shrinks).  Rounds past a round cap are not queued at all.
 int32_t run_enqueue(pdfs_ctx* c) {
   Run& r = c->run;
-  while (r.active && r.inflight < kDepth) {
+  while (r.active && r.count_slot < 0 && r.inflight < kDepth) {
     if (r.max_rounds > 0 && r.enqueued >= r.max_rounds) break;
     // (a lazy run keeps its first round's rows)
     const int w64 = r.lazy ? r.w64 : dfs_row_words(words(r.n_unc > 0 ? r.n_unc : 1));
@@ -632,6 +689,12 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
     }
   }
   r.executed_before = st.executed;
+  if (r.count_slot >= 0) {   // rounds are over: the counters end the run
+    if (slot != r.count_slot) return PDFS_OK;
+    r.active = false;
+    *done = true;
+    return PDFS_OK;
+  }
   if (st.overflow & 2) {
     r.active = false;
     return fail(c, PDFS_ERR_DEVICE, "corrupt per-wave result slot or listed prefix");
@@ -675,6 +738,25 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
     return fail(c, PDFS_ERR_DEVICE, "greedy loop did not stop");
   }
   if (st.done || (r.max_rounds > 0 && r.enqueued >= r.max_rounds && r.inflight == 0)) {
+    if (r.lazy && c->prune_mode == PDFS_PRUNE_EMPTY && c->want_counters && st.executed > 0) {
+      const int32_t rc = ensure_count(c, r.h, r.w64, st.executed);
+      if (rc != PDFS_OK) {
+        r.active = false;
+        return rc;
+      }
+      const Problem P = make_problem(c, r.h, r.p, r.q);
+      const Work w = make_work(c, r.w64, r.target);
+      CK(c, launch_count(P, w, c->lz, c->cw, c->nA_max, c->stream));
+      const int cs = c->next_slot;
+      CK(c, hipMemcpyAsync(&c->h_slots[cs], c->st, sizeof(RoundState), hipMemcpyDeviceToHost,
+                           c->stream));
+      CK(c, hipEventRecord(c->chunk_done[cs], c->stream));
+      c->chunk_rounds[cs] = 0;
+      c->next_slot = (cs + 1) % kDepth;
+      r.inflight += 1;
+      r.count_slot = cs;
+      return PDFS_OK;
+    }
     r.active = false;
     *done = true;
     return PDFS_OK;
@@ -832,10 +914,10 @@ size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int 
   if (h >= 3) {
     const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
     b += pairs * 8;
-    if (prune_mode != PDFS_PRUNE_BOUND)
+    if (prune_mode == PDFS_PRUNE_NONE)
       b += (size_t)item_cap_for(pairs) * sizeof(Item) + (size_t)kSeedCap * 8;
   }
-  if (h >= 2 && prune_mode == PDFS_PRUNE_BOUND) {   // lazy rounds
+  if (h >= 2 && prune_mode != PDFS_PRUNE_NONE) {   // lazy rounds
     const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
     const size_t nw = (size_t)lazy_waves(pairs), gw = (size_t)(nA_max + 63) / 64;
     if (h == 2) b += pairs * 8;
@@ -844,7 +926,7 @@ size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int 
     b += (size_t)kLazyWaves * sizeof(Slot) * 2;
   }
   if (h == 2) b += rows * (size_t)unpacked_row_bytes((int)wn);
-  if (h >= 5 && prune_mode != PDFS_PRUNE_BOUND) {
+  if (h >= 5 && prune_mode == PDFS_PRUNE_NONE) {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -1061,12 +1143,14 @@ int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out
     P.G = G; P.n_tumor = m->n_tumor; P.n_normal = m->n_normal; P.wt = wt; P.wn = c->wn;
     P.h = 1; P.p = 1; P.q = 1; P.mode = mode; P.n_cu = c->n_cu; P.tn_literal = 0;
     Work w = make_work(c, 1, 0);
+    CKC(launch_total_bits(c->Ts, (size_t)G * wt, c->st, s));
     CKC(launch_fill_u(c->U, wt, m->n_tumor, s));
     CKC(launch_round_begin(P, w, s));
     CKC(launch_active(P, w, s));
     CKC(hipMemcpyAsync(c->h_st, c->st, sizeof(RoundState), hipMemcpyDeviceToHost, s));
     CKC(hipStreamSynchronize(s));
     c->nA_max = c->h_st->nA;
+    c->tumor_bits = c->h_st->tumor_bits > 0 ? c->h_st->tumor_bits : 1;
   }
   // row padding: whole 128-row MFMA block tiles
   const size_t rows = (size_t)((c->nA_max + 127) / 128 * 128 + 128);

@@ -965,6 +965,7 @@ bool admit_one(pdfs_server* s) {
   o.stream = s->admit_stream;
   o.flags = PDFS_OPT_GRAPHS;
   int32_t rc = create_ctx(&r->m, &o, &r->ctx, r->pinned, true);
+  if (rc == PDFS_OK) r->ctx->want_counters = false;   // answers carry no statistics
   if (rc == PDFS_OK) {
     r->ctx->stream = s->streams[s->next_stream++ % (int)s->streams.size()];
     rc = check_call(r->ctx, r->h, r->p, r->q);

@@ -98,6 +98,7 @@ struct RoundState {
   unsigned long long tx_vis_words3, tx_vis_words4;   // visits x ceil(|U|/64)
   // ---- two-phase depth-4 (h = 4, empty-prefix pruning)
   unsigned long long n_tri;        // non-empty depth-3 prefixes listed this round
+  unsigned long long tumor_bits;   // create: tumour mutations of the cohort
   // ---- batched launches: best-leaf log entries per slot phase this round
   uint32_t nlog[4];
 };
@@ -237,6 +238,33 @@ struct LazyWork {
   int32_t wave_bytes;         // LDS per wave (set by the launcher)
 };
 
+// Counters of an empty-intersection run (k_count.hip), made after its rounds.
+constexpr int kCountMaxT = 1281;    // rounds a run can take (each covers a sample, or is the last)
+constexpr int kCountWaves = 4096;   // waves of the enumeration at most
+
+struct CountWork {
+  int32_t* order;     // [64 * kMaxW64] samples by falling rounds
+  int32_t* tt;        // [64 * kMaxW64] their rounds
+  uint32_t* wc;       // [kCountMaxT + 1] row words of the first k rounds
+  uint16_t* pref;     // [64 * w64][gw] a sample's genes before each word
+  int32_t* kc;        // [64 * kMaxW64] a sample's genes
+  uint32_t* off;      // [64 * kMaxW64] where its list starts
+  uint8_t* ecnt;      // [64 * kMaxW64][16] its genes above the loop bound of depth h - i
+  uint16_t* genes;    // [q_n] the samples' genes, list after list
+  unsigned long long* q;    // [h - 3][q_n] sums along the lists
+  unsigned long long* sv;   // [q_n] h = 4
+  unsigned long long* sw;   // [q_n]
+  uint16_t* tg;       // [whole segments of genes] a gene's rounds
+  uint32_t* seg_v;    // [segments][rounds + 1]
+  uint32_t* seg_w;
+  uint32_t* tab_v;    // [table rows][rounds + 1]
+  uint32_t* tab_w;
+  uint64_t* bits;     // [waves][levels][gw]
+  size_t q_n;         // tumour bits of the cohort (an upper bound of the lists' length)
+  int32_t waves;      // a multiple of LazyWork::nw
+  int32_t wave_bytes;
+};
+
 // ---------------------------------------------------------------- batched
 // Many cohorts' rounds in one launch per round step.  Light steps run one
 // block row per instance (blockIdx.y); the depth-first steps drain one shared
@@ -274,6 +302,7 @@ hipError_t launch_gather_sorted(const uint64_t* T, int64_t ts, const uint64_t* N
                                 uint64_t* Ns, hipStream_t s);
 hipError_t launch_normal_counts(const uint64_t* Ns, int G, int wn, int32_t* ncount,
                                 hipStream_t s);
+hipError_t launch_total_bits(const uint64_t* Ts, size_t words, RoundState* st, hipStream_t s);
 hipError_t launch_check_pad(const uint64_t* T, int64_t ts, int G, int n, int* bad, hipStream_t s);
 
 // per round
@@ -307,6 +336,11 @@ int lazy_levels(int h);
 hipError_t launch_lazy_begin(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
 hipError_t launch_lazy_deal(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
 hipError_t launch_lazy_round(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
+// The counters of a finished run into its state's totals.
+int count_segments(int nA);
+size_t count_table_rows(int nA);
+hipError_t launch_count(const Problem& P, const Work& w, const LazyWork& L, const CountWork& C,
+                        int nA_max, hipStream_t s);
 hipError_t launch_clear_slots(Slot* slots, int n, hipStream_t s);
 // n32 32-bit words at p set to zero by a fill kernel (no memset node)
 hipError_t launch_zero_u32(void* p, size_t n32, hipStream_t s);

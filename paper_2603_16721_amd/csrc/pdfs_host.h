@@ -46,6 +46,7 @@ struct Run {
   bool lazy = false;        // lazy rounds (k_lazy.hip)
   bool listed = false;      // lazy rounds: the run's pair lists are queued
   int w64 = 1;              // lazy rounds: row width of the run
+  int count_slot = -1;      // lazy rounds: the counters are queued, read with this slot
   bool time_pairs = false;  // lazy rounds: the next chunk read holds the pair table's events
   int32_t status = PDFS_OK;
   std::chrono::steady_clock::time_point t_prev;   // when the host last saw a chunk end
@@ -93,6 +94,11 @@ struct pdfs_ctx {
   // lazy rounds: buffers sized by the pair list, the row width and h
   pdfs::LazyWork lz = {};
   size_t lz_list_n = 0, lz_b_n = 0, lz_bits_n = 0;   // entries held by list, B and bits
+  // counters of an empty-intersection run, made after its rounds
+  pdfs::CountWork cw = {};
+  size_t cw_tab_n = 0, cw_seg_n = 0, cw_bits_n = 0, cw_q_n = 0, cw_pref_n = 0;
+  unsigned long long tumor_bits = 0;   // tumour mutations of the cohort
+  bool want_counters = true;           // callers that report no counters skip them
   bool two_phase = false;              // this run uses the two-phase path
   pdfs::Slot* slots = nullptr;
   unsigned long long* tallies = nullptr;

@@ -1,4 +1,5 @@
-"""Lazy rounds (k_lazy.hip) at the edges of their paths, against the oracle:
+"""Lazy rounds (k_lazy.hip) and the counters made after them (k_count.hip) at
+the edges of their paths, against the oracle:
 pairs with more samples than one mask word (the general walk), more candidates
 than a level list holds, every list depth, candidate words past one wave, and
 runs resumed from a mask on the same context.  Results are whole numbers, so
@@ -9,7 +10,7 @@ import pytest
 from oracle import cpu
 from paper_2603_16721_amd import synth
 from tests.helpers import mask_of_bits
-from tests.test_gpu_parity import _same_rounds, pdfs  # noqa: F401
+from tests.test_gpu_parity import _counters_equal, _same_rounds, pdfs  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -26,19 +27,22 @@ EDGES = [
     (40, 150, 64, 0.55, 6, (1, 10), 0),
     (34, 200, 40, 0.6, 9, (1, 10), 2),
     (9, 40, 512, 0.7, 9, (3, 1), 0),         # one combination
-    (4200, 30, 40, 0.02, 4, (1, 10), 0),     # more than 64 candidate words
+    (4200, 30, 40, 0.02, 4, (1, 10), 2),     # more than 64 candidate words
 ]
 
 
 @pytest.mark.parametrize("case", EDGES, ids=[f"G{c[0]}_nt{c[1]}_h{c[4]}" for c in EDGES])
-def test_lazy_edges(pdfs, case):  # noqa: F811
+@pytest.mark.parametrize("mode", ["bound", "empty"])
+def test_lazy_edges(pdfs, case, mode):  # noqa: F811
     G, nt, nn, d, h, (p, q), mr = case
     I = synth.random_tiny(31, G, nt, nn, d, h, alpha=(p, q))
     T, N = I.packed()
     mask = mask_of_bits(np.arange(nt) % 3 != 0)
-    with pdfs.Solver(T, N, nt, nn, "bound") as s:
+    with pdfs.Solver(T, N, nt, nn, mode) as s:
         for u in (None, mask):
-            exp = cpu.wsc(T, N, nt, nn, h, p, q, mode="bound", max_rounds=mr, U0=u)
-            got, _, final = s.wsc(h, p, q, 0, mr, u)
+            exp = cpu.wsc(T, N, nt, nn, h, p, q, mode=mode, max_rounds=mr, U0=u)
+            got, st, final = s.wsc(h, p, q, 0, mr, u)
             _same_rounds(got, exp.rounds)
             assert np.array_equal(final, exp.final_uncovered)
+            if mode == "empty":
+                _counters_equal(st, exp.counters, h)
