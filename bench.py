@@ -224,7 +224,7 @@ def bench_batched(pdfs, data, modes=("bound", "empty")):
             print(f"[bench] batched {mode} {name}: {min(times):.1f} ms vs plain serial "
                   f"{plain_ms:.1f} ms", file=sys.stderr, flush=True)
         # the path a batch takes by default for this mode (path="auto")
-        row["default_path"] = "one_launch_per_step" if mode == "bound" else "streams"
+        row["default_path"] = "streams"
         row["default_speedup_vs_plain_serial"] = row[row["default_path"]]["speedup_vs_plain_serial"]
         out[mode] = row
     return out

@@ -58,7 +58,9 @@ extern "C" {
 
 /* ------------------------------------------------------------ pruning modes */
 /* PDFS_PRUNE_EMPTY: the paper's rule (Alg. 2) -- a prefix whose running tumour
- *   intersection is empty is not extended.
+ *   intersection is empty is not extended.  The combinations and the counters
+ *   of that walk; the counters are made in one enumeration after the last
+ *   round, not by walking every round.
  * PDFS_PRUNE_BOUND: EMPTY plus the score bound of Sec. III-E -- a prefix
  *   covering c uncovered tumour samples can reach at most p*c + q*N_n, so it
  *   is not extended when that cannot beat the best combination found so far.
@@ -149,11 +151,10 @@ typedef struct {
     int32_t reserved;
     int64_t ns_total;   /* host wall time of the call, nanoseconds */
     /* Filled when the context was created with PDFS_OPT_TIME_KERNELS:
-     * index 0 = int8-MFMA pair-table kernel, 1 = depth-first stage (depths
-     * 3..h), 2 = the part of index 1 spent in the depth-4 tile kernel (h = 4
-     * under PDFS_PRUNE_EMPTY: depth-3 prefixes with long depth-4 candidate
-     * streams are listed, bucketed by their third gene and expanded in
-     * tiles; 0 otherwise). */
+     * index 0 = int8-MFMA pair-table kernel (once per run, or once per round
+     * under PDFS_PRUNE_NONE), 1 = the rounds' search launches (depths 3..h),
+     * 2 = the part of index 1 spent in the depth-4 tile kernel, where a run
+     * uses it (0 otherwise). */
     int64_t kernel_ns[3];        /* summed HIP-event durations            */
     int32_t kernel_launches[3];  /* launches timed                        */
     /* Work the kernels had to do, counted inside them (always filled):
@@ -202,9 +203,9 @@ int32_t pdfs_best_combo(pdfs_ctx *ctx, int32_t h, uint32_t alpha_p, uint32_t alp
  * the number of rounds.  If more than cap rounds were needed the call returns
  * PDFS_ERR_TRUNCATED with *n_out = rounds needed (the first cap are written).
  * final_uncovered (host, may be NULL) receives the mask after the last round.
- * stats may be NULL.  The first call with h >= 5 on a context allocates the
- * deep walk's prefix rings (about 0.8 GB at 1000 tumour samples), kept until
- * pdfs_destroy; PDFS_ERR_OUT_OF_MEMORY if that fails.  PDFS_ERR_DEVICE also
+ * stats may be NULL.  The first call with h >= 5 under PDFS_PRUNE_NONE on a
+ * context allocates the deep walk's prefix rings (about 0.8 GB at 1000 tumour
+ * samples), kept until pdfs_destroy; PDFS_ERR_OUT_OF_MEMORY if that fails.  PDFS_ERR_DEVICE also
  * reports a device-side consistency failure (a corrupt result slot, or the
  * deep walk's scheduler making no progress), with the run stopped. */
 int32_t pdfs_wsc_run(pdfs_ctx *ctx, int32_t h, uint32_t alpha_p, uint32_t alpha_q,
@@ -251,32 +252,26 @@ int32_t pdfs_measure_int_peak(int32_t device, double *lane_ops_per_s);
 
 /* ------------------------------------------------------------- batched
  * Many independent cohorts (instances) solved together: each instance keeps
- * its own context, rounds stay device-resident, one round per row width is
- * captured as a HIP graph and replayed, and the instances' rounds run
- * concurrently on a small set of streams (one per hardware queue) while a
+ * its own context, its rounds stay device-resident, and the instances' rounds
+ * run concurrently on a small set of streams (one per hardware queue) while a
  * single host thread feeds them.  Results are those of pdfs_wsc_run on each
- * instance alone.  The split granularity (depth-3 candidates per work item,
- * seed pairs in bound mode) is chosen per instance class by the tuner below
- * when the batch is created with PDFS_OPT_AUTOTUNE. */
+ * instance alone. */
+/* Tunes the split granularity of the launches of PDFS_OPT_BATCH_ONE_LAUNCH
+ * (depth-3 candidates per work item, seed pairs in bound mode) per instance
+ * class; without effect where the rounds have nothing to tune. */
 #define PDFS_OPT_AUTOTUNE 4
-/* Two ways to run a batch; by default each run takes the one that measures
- * faster for its pruning mode.
- * One launch per round step over all instances (default under
- * PDFS_PRUNE_BOUND; only for batches of up to 64 instances, all with h in
- * {3, 4}, under PDFS_PRUNE_EMPTY or PDFS_PRUNE_BOUND): every light step
- * covers every instance with a block row each, each depth-first step drains
- * one shared work queue of all live instances' work items (the ordering of
- * Sec. III-D's request-driven chunks), and the round's launches are one
- * captured HIP graph replayed until every instance's stop flag is set; the
- * row width of a chunk of rounds is the largest any live instance needs.
- * Each instance's own launches concurrently on the batch's streams (default
- * otherwise): under PDFS_PRUNE_EMPTY a round of a large instance fills the
- * device by itself, and instances that run independently overlap one
- * instance's narrow tail rounds with another's wide ones, where one launch
- * per step makes every instance wait for the slowest at each step.
- * PDFS_OPT_BATCH_STREAMS asks for the streams, PDFS_OPT_BATCH_ONE_LAUNCH for
- * one launch per step where the batch allows it (streams otherwise); both
- * together are PDFS_ERR_INVALID_ARG. */
+/* Two ways to run a batch.  Each instance's own launches concurrently on the
+ * batch's streams is the default and the faster one (8 cohorts under
+ * PDFS_PRUNE_BOUND: 25 ms against 109 ms); PDFS_OPT_BATCH_STREAMS asks for it.
+ * PDFS_OPT_BATCH_ONE_LAUNCH asks for one launch per round step over all
+ * instances where the batch allows it (up to 64 instances, all with h in
+ * {3, 4}, under PDFS_PRUNE_EMPTY or PDFS_PRUNE_BOUND; streams otherwise):
+ * every light step covers every instance with a block row each, each
+ * depth-first step drains one shared work queue of all live instances' work
+ * items (the ordering of Sec. III-D's request-driven chunks), and the round's
+ * launches are one captured HIP graph replayed until every instance's stop
+ * flag is set; the row width of a chunk of rounds is the largest any live
+ * instance needs.  Both flags together are PDFS_ERR_INVALID_ARG. */
 #define PDFS_OPT_BATCH_STREAMS 16
 #define PDFS_OPT_BATCH_ONE_LAUNCH 32
 

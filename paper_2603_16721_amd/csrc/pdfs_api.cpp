@@ -215,7 +215,7 @@ static size_t count_sums(int h) { return h >= 4 ? (size_t)(h - 3) + (h == 4 ? 2 
 constexpr size_t kMaxCountBytes = (size_t)1 << 30;
 
 static bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds) {
-  if (h < 2 || (h == 2 && max_rounds == 1)) return false;
+  if (c->lazy_off || h < 2 || (h == 2 && max_rounds == 1)) return false;
   if (c->prune_mode == PDFS_PRUNE_BOUND) return true;
   return c->prune_mode == PDFS_PRUNE_EMPTY &&
          c->tumor_bits * (8 * count_sums(h) + 2) <= kMaxCountBytes;

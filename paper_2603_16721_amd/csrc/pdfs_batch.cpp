@@ -156,7 +156,11 @@ double time_first_round(pdfs_ctx* c, int h, uint32_t p, uint32_t q) {
   if (set_uncovered(c, nullptr) <= 0) return 1e30;
   (void)hipStreamSynchronize(c->stream);
   const auto t0 = Clock::now();
-  if (run_blocking(c, h, p, q, c->n_tumor + 1, 1, c->n_tumor) != PDFS_OK) return 1e30;
+  // the launches that the choices are for, not the lazy rounds
+  c->lazy_off = true;
+  const int32_t rc = run_blocking(c, h, p, q, c->n_tumor + 1, 1, c->n_tumor);
+  c->lazy_off = false;
+  if (rc != PDFS_OK) return 1e30;
   return std::chrono::duration<double>(Clock::now() - t0).count();
 }
 
@@ -250,7 +254,6 @@ struct pdfs_batch {
   hipEvent_t fork_ev = nullptr;              // ranges' depth-first launches run side by side
   std::vector<hipEvent_t> join_ev;
   int n_alloc = 0;                           // instances the batched buffers hold
-  bool streams_only = false;                 // PDFS_OPT_BATCH_STREAMS: no batched launches
   bool one_launch = false;                   // PDFS_OPT_BATCH_ONE_LAUNCH: batched launches in every mode
 };
 
@@ -714,9 +717,8 @@ int32_t pdfs_batch_create(const pdfs_matrix* inst, int32_t n, const pdfs_options
   pdfs_batch* b = new pdfs_batch();
   b->device = opt ? opt->device : 0;
   b->autotune = opt && (opt->flags & PDFS_OPT_AUTOTUNE);
-  b->streams_only = opt && (opt->flags & PDFS_OPT_BATCH_STREAMS);
   b->one_launch = opt && (opt->flags & PDFS_OPT_BATCH_ONE_LAUNCH);
-  if (b->streams_only && b->one_launch) {
+  if (b->one_launch && (opt->flags & PDFS_OPT_BATCH_STREAMS)) {
     delete b;
     return ctx_fail(nullptr, PDFS_ERR_INVALID_ARG,
                     "PDFS_OPT_BATCH_STREAMS and PDFS_OPT_BATCH_ONE_LAUNCH exclude each other");
@@ -765,16 +767,16 @@ int32_t pdfs_batch_run(pdfs_batch* b, const int32_t* h, uint32_t p, uint32_t q,
     if (rc != PDFS_OK) return batch_fail(b, rc, i);
     n_outs[i] = 0;
   }
-  if (b->autotune)
-    for (int i = 0; i < n; ++i) autotune(b->ctx[i], h[i], p, q);
-  // one launch per round step over every instance when all take it (h = 3, 4
-  // with empty or bound pruning) and it is the faster way for the mode (bound
-  // pruning) or asked for; the stream-parallel runs below otherwise
+  // one launch per round step over every instance where it is asked for and
+  // all take it (h = 3, 4 with empty or bound pruning); otherwise the
+  // stream-parallel runs below, whose rounds are lazy ones (8 cohorts under
+  // bound pruning: 109 ms in one launch per step, 25 ms on the streams)
   const int pm = b->ctx[0]->prune_mode;
-  bool multi = n <= kMaxBatch && pm != PDFS_PRUNE_NONE && !b->streams_only &&
-               (b->one_launch || pm == PDFS_PRUNE_BOUND);
+  bool multi = n <= kMaxBatch && pm != PDFS_PRUNE_NONE && b->one_launch;
   for (int i = 0; i < n; ++i)
     multi = multi && (h[i] == 3 || h[i] == 4) && b->ctx[i]->tn_literal == b->ctx[0]->tn_literal;
+  if (b->autotune && (multi || pm == PDFS_PRUNE_NONE))   // lazy rounds have nothing to tune
+    for (int i = 0; i < n; ++i) autotune(b->ctx[i], h[i], p, q);
   if (multi) return run_multi(b, h, p, q, target, outs, caps, n_outs, stats, t0);
   for (int i = 0; i < n; ++i) {
     pdfs_ctx* c = b->ctx[i];

@@ -98,6 +98,7 @@ struct pdfs_ctx {
   pdfs::CountWork cw = {};
   size_t cw_tab_n = 0, cw_seg_n = 0, cw_bits_n = 0, cw_q_n = 0, cw_pref_n = 0;
   unsigned long long tumor_bits = 0;   // tumour mutations of the cohort
+  bool lazy_off = false;               // the tuner times the other rounds
   bool want_counters = true;           // callers that report no counters skip them
   bool two_phase = false;              // this run uses the two-phase path
   pdfs::Slot* slots = nullptr;
