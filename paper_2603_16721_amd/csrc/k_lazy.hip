@@ -24,8 +24,12 @@
 // turn; a wave owns its share for the whole run (no queue, no atomics), 64
 // pairs to a chunk with the chunk's largest bound beside it.  Each round a
 // wave re-evaluates the best leaf it knows, publishes it, and then opens its
-// pairs from the largest bounds down.  The last block to finish takes the
-// argmax, writes the round's record and updates the cover.
+// pairs from the largest bounds down.  The leaves that no incumbent beat are
+// left in a short list, and the next launch begins by taking their argmax and
+// updating the cover (every block for itself, the first one for the record):
+// no block waits for another.  Taking it in the last block to finish instead
+// costs its chain of loads (7 us) and the count of finished blocks (3 us) at
+// the end of every round.
 #include <type_traits>
 
 #include "dfs_core.h"
@@ -61,23 +65,31 @@ __device__ __forceinline__ int pair_count(const uint64_t* __restrict__ ra,
 // The first block also starts the run's control words.
 __global__ __launch_bounds__(256) void k_lazy_begin(Problem P, Work w, LazyWork L) {
   RoundState* st = w.st;
-  if (st->done) return;
+  if (st->done) {   // nothing to cover: the round launches do nothing either
+    if (blockIdx.x == 0 && threadIdx.x == 0) L.S[1].done = 1;
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int nA = st->nA;
   if (blockIdx.x == 0) {
     const int n_unc = st->n_unc;
     for (int k = threadIdx.x; k < kMaxW64; k += 256) {
       const int lo = 64 * k;
-      L.Uc[k] = n_unc - lo >= 64 ? ~0ull : (n_unc > lo ? (1ull << (n_unc - lo)) - 1ull : 0ull);
+      L.U2[kMaxW64 + k] = n_unc - lo >= 64 ? ~0ull : (n_unc > lo ? (1ull << (n_unc - lo)) - 1ull : 0ull);
     }
     if (threadIdx.x == 0) L.uncs[0] = n_unc;
     for (int v = threadIdx.x; v <= kMaxCount; v += 256) L.cursor[v] = 0u;
-    for (int i = threadIdx.x; i < kLazyCtl; i += 256) L.ctl[i] = 0u;
-    if (threadIdx.x < kIncShards) L.shard[threadIdx.x * kCursorStride] = 0ull;
-    if (threadIdx.x == 0 && st->n_pairs > w.pair_cap) {
-      // n_pairs keeps the count emitted; the run stops before its first round
-      st->overflow |= kOverflowPairs;
-      st->done = 1;
+    if (threadIdx.x < 3) L.n_win[64 * threadIdx.x] = 0u;
+    if (threadIdx.x < 2) L.inc[threadIdx.x * kCursorStride] = 0ull;
+    if (threadIdx.x < 2 * kIncShards) L.shard[threadIdx.x * kCursorStride] = 0ull;
+    if (threadIdx.x == 0) {
+      LazyState z = {n_unc, 0, 0, 0, 0};
+      if (st->n_pairs > w.pair_cap) {
+        // n_pairs keeps the count emitted; the run stops before its first round
+        st->overflow |= kOverflowPairs;
+        z.done = 1;
+      }
+      L.S[1] = z;
     }
   }
   const uint64_t* T = reinterpret_cast<const uint64_t*>(w.TA);
@@ -110,7 +122,7 @@ __global__ __launch_bounds__(256) void k_lazy_deal(Problem P, Work w, LazyWork L
   __shared__ uint32_t base[kMaxCount + 1];
   __shared__ uint32_t part[kBlock];
   RoundState* st = w.st;
-  if (st->done) return;
+  if (L.S[1].done) return;
   const unsigned long long np = st->n_pairs < w.pair_cap ? st->n_pairs : w.pair_cap;
   const int tid = threadIdx.x;
   constexpr int kPer = (kMaxCount + kBlock) / kBlock;   // bins per thread, from the top
@@ -283,6 +295,8 @@ struct Wave {
   const uint64_t* T;
   int lane, nA, w64, h;
   uint64_t u;                   // lane k < w64: word k of the uncovered mask
+  unsigned long long* incp;     // the launch's incumbent and its shards
+  unsigned long long* shard;
   unsigned long long inc;       // newest incumbent seen
   int bs, btp, bfp;             // best leaf (tuple in s.tup)
   // the pair being opened
@@ -290,6 +304,10 @@ struct Wave {
   int tie_s;                    // a score this pair has reached: its later tuples lose the tie
   int a, b, need, sub, lmax;    // best score below it; per lane: largest TP pruned
 };
+
+__device__ __forceinline__ unsigned long long load_inc(const Wave& v) {
+  return __hip_atomic_load(v.incp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 __device__ __forceinline__ void refresh_need(Wave& v) {
   if (v.inc == 0) {
@@ -324,10 +342,10 @@ __device__ __forceinline__ void publish_key(Wave& v, unsigned long long key) {
     unsigned long long best = key;
     if (v.lane == 0) {
       unsigned long long old =
-          atomicMax(&v.L.shard[(blockIdx.x % kIncShards) * kCursorStride], key);
+          atomicMax(&v.shard[(blockIdx.x % kIncShards) * kCursorStride], key);
       if (old < key) {
-        old = load_incumbent(v.w.st);
-        if (old < key) old = atomicMax(&v.w.st->incumbent, key);
+        old = load_inc(v);
+        if (old < key) old = atomicMax(v.incp, key);
       }
       best = old > key ? old : key;
     }
@@ -581,7 +599,7 @@ __device__ __forceinline__ void open_general(Wave& v, uint64_t y2, uint64_t* bit
     uint64_t y = 0;
     if (lane < v.w64) y = v.s.y[l * kMaxW64 + lane] & v.T[(size_t)c * v.w64 + lane];
     const int cnt = wave_sum(popc64(y));
-    v.inc = max(v.inc, load_incumbent(v.w.st));
+    v.inc = max(v.inc, load_inc(v));
     refresh_need(v);
     wave_lds_sync();
     pass_own_best(v, l + 3);
@@ -629,7 +647,7 @@ __device__ __forceinline__ void open_lists(Wave& v, int n0) {
       continue;
     }
     if (l == 0 && (i & 15) == 0) {
-      v.inc = max(v.inc, load_incumbent(v.w.st));
+      v.inc = max(v.inc, load_inc(v));
       refresh_need(v);
     }
     const uint64_t mi = mk[i];
@@ -711,7 +729,7 @@ __device__ __forceinline__ void open_lanes(Wave& v, uint64_t mk, int ix, unsigne
     const int i = __builtin_ctzll(set);
     set &= set - 1;
     if (LV == 0 && (++n & 15) == 0) {
-      v.inc = max(v.inc, load_incumbent(v.w.st));
+      v.inc = max(v.inc, load_inc(v));
       refresh_need(v);
     }
     const uint64_t mi = readlane64(mk, i);
@@ -754,7 +772,7 @@ __device__ __forceinline__ int open_pair(Wave& v, int a, int b, uint64_t* bits) 
   v.tie_s = -1;
   v.sub = -1;
   v.lmax = 0;
-  const unsigned long long newest = load_incumbent(v.w.st);   // in flight with the rows
+  const unsigned long long newest = load_inc(v);   // in flight with the rows
   uint64_t y2 = 0;
   if (lane < v.w64)
     y2 = v.T[(size_t)a * v.w64 + lane] & v.T[(size_t)b * v.w64 + lane] & v.u;
@@ -929,57 +947,43 @@ __device__ __forceinline__ void chunk_h2(Wave& v, unsigned long long& e, bool nd
   publish(v, smax, ba, bb);
 }
 
-// The round's answer, its record and the cover update, by the last block.
-__device__ __forceinline__ void lazy_finish(const Problem& P, const Work& w, const LazyWork& L,
-                                            int h, int n_win) {
-  __shared__ Slot s_best;
-  __shared__ int s_found;
-  RoundState* st = w.st;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int n_unc = st->n_unc, executed = st->executed, rounds = st->rounds;
-  const int max_rounds = st->max_rounds;
-  if (tid < kWave) {
+// The answer of the launch before this one, for every wave of the block: the
+// argmax of the leaves it left, in best (s = -1: none).
+__device__ __forceinline__ void last_answer(const LazyWork& L, int n, int nA, int h, Slot* best) {
+  if (threadIdx.x < kWave) {
+    const int lane = threadIdx.x, ring = (n + 2) % 3;
+    const Slot* wins = L.wins + (size_t)ring * (kLazyWaves / 4);
+    const int n_win = (int)L.n_win[64 * ring];
     Slot b = empty_slot();
     for (int i = lane; i < n_win; i += kWave) {
-      const Slot c = L.wins[i];
+      const Slot c = wins[i];
       slot_take_if(b, c, slot_better(c, b));
     }
-    b = wave_best(b);
-    if (lane == 0) {
-      int ok = b.s >= 0;
-      if (ok) {
-        const int nA = st->nA;
-#pragma unroll
-        for (int i = 0; i < kMaxH; ++i)
-          if (i < h && (b.idx[i] < 0 || b.idx[i] >= nA || (i > 0 && b.idx[i] <= b.idx[i - 1])))
-            ok = 0;
-        if (b.tp <= 0) ok = 0;
-        if (!ok) st->overflow |= 2;
-      }
-      s_best = b;
-      s_found = ok;
-    }
+    if (n_win > 1) b = wave_best(b);
+    if (lane == 0) *best = b;
   }
   __syncthreads();
-  const int found = s_found;
-  const int tp = found ? s_best.tp : 0;
-  const int cov_n = P.n_tumor - n_unc + tp;
-  const bool done = !found || cov_n >= w.target || cov_n >= P.n_tumor ||
-                    (max_rounds > 0 && rounds + found >= max_rounds);
-  for (int i = tid; i < kLazyCtl; i += kBlock) L.ctl[i] = 0u;
-  if (tid < kIncShards) L.shard[tid * kCursorStride] = 0ull;
-  // the run's own columns; a covered sample was uncovered in every round so
-  // far.  The cohort's mask follows when the run stops.
+}
+
+// Commits it (the first block): the round's record, the state and the masks.
+__device__ __forceinline__ void commit_answer(const Problem& P, const Work& w, const LazyWork& L,
+                                              int h, const LazyState& z, const LazyState& nz,
+                                              const Slot& best, bool found, uint64_t* un) {
+  RoundState* st = w.st;
+  const int tid = threadIdx.x, lane = tid & 63;
   const uint64_t* T = reinterpret_cast<const uint64_t*>(w.TA);
+  const uint64_t* uo = un == L.U2 ? L.U2 + kMaxW64 : L.U2;
   for (int k = tid >> 6; k < w.w64; k += kBlock / kWave) {
-    const uint64_t u = L.Uc[k];
+    const uint64_t u = uo[k];
     uint64_t cov = found ? u : 0ull;
-    for (int i = 0; i < h && found; ++i) cov &= T[(size_t)s_best.idx[i] * w.w64 + k];
-    if ((cov >> lane) & 1ull) L.tcov[k * 64 + lane] = executed + 1;
-    if (lane == 0) L.Uc[k] = u & ~cov;
-    if (done) {
+    for (int i = 0; i < h && found; ++i) cov &= T[(size_t)best.idx[i] * w.w64 + k];
+    const uint64_t left = u & ~cov;
+    // a covered sample was uncovered in every round so far
+    if ((cov >> lane) & 1ull) L.tcov[k * 64 + lane] = nz.executed;
+    if (lane == 0) un[k] = left;
+    if (nz.done) {   // the cohort's own mask follows when the run stops
       const int smp = k * 64 + lane;
-      const uint64_t left = u & ~cov;
+      if (lane == 0) L.Uc[k] = left;
       if (smp < L.uncs[0] && !((left >> lane) & 1ull)) {
         const int c = w.cols[smp];
         atomicAnd(reinterpret_cast<unsigned long long*>(&w.U[c >> 6]), ~(1ull << (c & 63)));
@@ -987,55 +991,118 @@ __device__ __forceinline__ void lazy_finish(const Problem& P, const Work& w, con
     }
   }
   // (the genes' caller ids are looked up where the record is read)
-  RoundRecord* rec = found && rounds < w.rec_cap ? w.recs + rounds : nullptr;
+  RoundRecord* rec = found && z.rounds < w.rec_cap ? w.recs + z.rounds : nullptr;
   if (rec && tid >= 64 && tid < 64 + kMaxH) {
     const int i = tid - 64;
-    rec->sorted_idx[i] = i < h ? w.act[s_best.idx[i]] : -1;
+    rec->sorted_idx[i] = i < h ? w.act[best.idx[i]] : -1;
     rec->genes[i] = -1;
   }
   if (tid == 0) {
     if (rec) {
       rec->h = h;
       rec->found = 1;
-      rec->tp = tp;
-      rec->fp = s_best.fp;
-      rec->tn = P.n_normal - s_best.fp;
-      rec->uncovered_before = n_unc;
-      rec->score_num = (int64_t)P.p * tp + (int64_t)P.q * (P.n_normal - s_best.fp);
-      rec->score_den = (int64_t)P.q * (int64_t)(n_unc + P.n_normal);
+      rec->tp = best.tp;
+      rec->fp = best.fp;
+      rec->tn = P.n_normal - best.fp;
+      rec->uncovered_before = z.n_unc;
+      rec->score_num = (int64_t)P.p * best.tp + (int64_t)P.q * (P.n_normal - best.fp);
+      rec->score_den = (int64_t)P.q * (int64_t)(z.n_unc + P.n_normal);
     }
     st->found = found;
-    if (executed + 1 < P.n_tumor + 2) L.uncs[executed + 1] = n_unc - tp;
-    st->covered = cov_n;
-    st->n_unc = n_unc - tp;
-    st->rounds = rounds + (found ? 1 : 0);
-    st->executed = executed + 1;
-    st->incumbent = 0;
-    st->done = done;
+    if (nz.executed < P.n_tumor + 2) L.uncs[nz.executed] = nz.n_unc;
+    st->covered = P.n_tumor - nz.n_unc;
+    st->n_unc = nz.n_unc;
+    st->rounds = nz.rounds;
+    st->executed = nz.executed;
+    st->done = nz.done;
   }
 }
 
 // H: the combination size, or 0 for 5..9 (taken from P).
 template <int H>
-__global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork L) {
+__global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork L, int n,
+                                                    int search) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ Slot wave_slot[kBlock / kWave];
   __shared__ unsigned long long wave_key[kBlock / kWave];
-  __shared__ int s_last;
+  __shared__ Slot s_best;
   RoundState* st = w.st;
-  if (st->done) return;
   const int lane = threadIdx.x & 63;
   const int wib = uniform(threadIdx.x >> 6);
   const int wv = blockIdx.x * (kBlock / kWave) + wib;
   const int h = H > 0 ? H : P.h;
-  Wave v{P, w, L, wave_lds(lds + (size_t)wib * L.wave_bytes, h),
-         reinterpret_cast<const uint64_t*>(w.TA)};
+  const uint64_t* T = reinterpret_cast<const uint64_t*>(w.TA);
+  const int cur = n & 1;
+  const LazyState z = L.S[cur ^ 1];
+  if (z.done) {   // launches queued past the stop hand the state on
+    if (blockIdx.x == 0 && threadIdx.x == 0) L.S[cur] = z;
+    return;
+  }
+  const int nA = uniform(st->nA);
+  uint64_t u = lane < w.w64 ? L.U2[(cur ^ 1) * kMaxW64 + lane] : 0ull;
+  // the best leaf this wave knows from earlier rounds: its rows are on their
+  // way while the last round's answer is taken
+  const Slot pool = L.pool[wv];
+  uint64_t py = ~0ull;
+  if (uniform(pool.s) >= 0) {
+#pragma unroll
+    for (int i = 0; i < kMaxH; ++i)
+      if (i < h && lane < w.w64) py &= T[(size_t)pool.idx[i] * w.w64 + lane];
+  }
+  LazyState nz = z;
+  if (z.searched) {
+    last_answer(L, n, nA, h, &s_best);
+    const Slot& best = s_best;
+    bool found = best.s >= 0;
+    if (found) {
+      bool ok = best.tp > 0;
+      for (int i = 0; i < h; ++i)
+        ok = ok && best.idx[i] >= 0 && best.idx[i] < nA && (i == 0 || best.idx[i] > best.idx[i - 1]);
+      if (!ok) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->overflow |= 2;
+        found = false;
+      }
+    }
+    const int tp = found ? best.tp : 0;
+    const int max_rounds = st->max_rounds;
+    nz.n_unc = z.n_unc - tp;
+    nz.executed = z.executed + 1;
+    nz.rounds = z.rounds + (found ? 1 : 0);
+    const int cov = P.n_tumor - nz.n_unc;
+    nz.done = !found || cov >= w.target || cov >= P.n_tumor ||
+              (max_rounds > 0 && nz.rounds >= max_rounds);
+    if (found && lane < w.w64) {
+      uint64_t c = u;
+      for (int i = 0; i < h; ++i) c &= T[(size_t)best.idx[i] * w.w64 + lane];
+      u &= ~c;
+    }
+    if (blockIdx.x == 0)
+      commit_answer(P, w, L, h, z, nz, best, found, L.U2 + cur * kMaxW64);
+  } else if (blockIdx.x == 0 && threadIdx.x < w.w64) {
+    L.U2[cur * kMaxW64 + lane] = u;
+  }
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      nz.searched = search;
+      L.S[cur] = nz;
+      // cleared for the next launch; last used by the one before this
+      L.n_win[64 * ((n + 1) % 3)] = 0u;
+      L.inc[(cur ^ 1) * kCursorStride] = 0ull;
+    }
+    if (threadIdx.x < kIncShards)
+      L.shard[((cur ^ 1) * kIncShards + threadIdx.x) * kCursorStride] = 0ull;
+  }
+  if (nz.done || !search) return;
+
+  Wave v{P, w, L, wave_lds(lds + (size_t)wib * L.wave_bytes, h), T};
   v.lane = lane;
-  v.nA = uniform(st->nA);
+  v.nA = nA;
   v.w64 = w.w64;
   v.h = h;
-  v.u = lane < w.w64 ? L.Uc[lane] : 0ull;
-  v.inc = load_incumbent(st);
+  v.u = u;
+  v.incp = L.inc + cur * kCursorStride;
+  v.shard = L.shard + cur * kIncShards * kCursorStride;
+  v.inc = 0;
   v.bs = -1;
   v.btp = v.bfp = 0;
   v.a = v.b = 0;
@@ -1049,24 +1116,17 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
   const uint64_t* um = v.s.y + (kMaxH - 1) * kMaxW64;
   wave_lds_sync();
 
-  // the best leaf this wave knows from earlier rounds, under the new mask
-  {
-    const Slot q = L.pool[wv];
-    if (uniform(q.s) >= 0) {
-      uint64_t y = v.u;
+  // the wave's known leaf under the new mask
+  if (uniform(pool.s) >= 0) {
+    const int tp = wave_sum(popc64(py & v.u));
+    if (tp > 0) {
+      v.bfp = uniform(pool.fp);
+      v.btp = tp;
+      v.bs = P.p * tp + P.q * (P.n_normal - v.bfp);
 #pragma unroll
       for (int i = 0; i < kMaxH; ++i)
-        if (i < h && lane < w.w64) y &= v.T[(size_t)q.idx[i] * w.w64 + lane];
-      const int tp = wave_sum(popc64(y));
-      if (tp > 0) {
-        v.bfp = uniform(q.fp);
-        v.btp = tp;
-        v.bs = P.p * tp + P.q * (P.n_normal - v.bfp);
-#pragma unroll
-        for (int i = 0; i < kMaxH; ++i)
-          if (i < h && lane == i) v.s.tup[i] = (uint16_t)q.idx[i];
-        wave_lds_sync();
-      }
+        if (i < h && lane == i) v.s.tup[i] = (uint16_t)pool.idx[i];
+      wave_lds_sync();
     }
   }
   // published once per block
@@ -1099,7 +1159,7 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
 
   for (int k0 = 0; k0 < n_chunk; k0 += kWave) {
     const int cm = k0 + lane < n_chunk ? cmax[k0 + lane] : -1;
-    v.inc = max(v.inc, load_incumbent(st));
+    v.inc = max(v.inc, load_inc(v));
     unsigned long long todo = __ballot(cm >= 0 && cm >= (int)(v.inc >> 32) - 1);
     while (todo) {
       const int kc = __builtin_ctzll(todo);
@@ -1175,27 +1235,12 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
     for (int i = 1; i < kBlock / kWave; ++i)
       slot_take_if(r, wave_slot[i], slot_better(wave_slot[i], r));
     // only a leaf that the incumbent does not beat can be the answer
-    const unsigned long long inc = load_incumbent(st);
+    const unsigned long long inc = load_inc(v);
     if (r.s >= 0 && leaf_key(r.s, r.idx[0], r.idx[1]) >= inc) {
-      const uint32_t pos = atomicAdd(&L.ctl[0], 1u);
-      L.wins[pos] = r;   // one per block at most
-      __threadfence();
-    }
-    // the last block of its group reports the group
-    const uint32_t grp = blockIdx.x % kTicketGroups;
-    const uint32_t members = (gridDim.x + kTicketGroups - 1 - grp) / kTicketGroups;
-    const uint32_t groups = gridDim.x < kTicketGroups ? gridDim.x : kTicketGroups;
-    s_last = 0;
-    if (atomicAdd(&L.ctl[64 * (1 + grp)], 1u) == members - 1) {
-      __threadfence();
-      s_last = atomicAdd(&L.ctl[64 * (1 + kTicketGroups)], 1u) == groups - 1 ? 1 : 0;
+      const uint32_t pos = atomicAdd(&L.n_win[64 * (n % 3)], 1u);
+      L.wins[(size_t)(n % 3) * (kLazyWaves / 4) + pos] = r;   // one per block at most
     }
   }
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  const int n_win = (int)__hip_atomic_load(&L.ctl[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  lazy_finish(P, w, L, h, n_win);
 }
 
 }  // namespace
@@ -1218,16 +1263,18 @@ hipError_t launch_lazy_deal(const Problem& P, const Work& w, const LazyWork& L, 
   return hipGetLastError();
 }
 
-hipError_t launch_lazy_round(const Problem& P, const Work& w, const LazyWork& L0, hipStream_t s) {
+hipError_t launch_lazy_round(const Problem& P, const Work& w, const LazyWork& L0, int n,
+                             bool search, hipStream_t s) {
   LazyWork L = L0;
   L.wave_bytes = (int)lazy_wave_bytes(P.h);
   const size_t lds = (size_t)L.wave_bytes * (kBlock / kWave);
-  const int blocks = L.nw / (kBlock / kWave);
+  const int blocks = search ? L.nw / (kBlock / kWave) : 1;
+  const int sr = search ? 1 : 0;
   switch (P.h) {
-    case 2: k_lazy_round<2><<<blocks, kBlock, lds, s>>>(P, w, L); break;
-    case 3: k_lazy_round<3><<<blocks, kBlock, lds, s>>>(P, w, L); break;
-    case 4: k_lazy_round<4><<<blocks, kBlock, lds, s>>>(P, w, L); break;
-    default: k_lazy_round<0><<<blocks, kBlock, lds, s>>>(P, w, L); break;
+    case 2: k_lazy_round<2><<<blocks, kBlock, lds, s>>>(P, w, L, n, sr); break;
+    case 3: k_lazy_round<3><<<blocks, kBlock, lds, s>>>(P, w, L, n, sr); break;
+    case 4: k_lazy_round<4><<<blocks, kBlock, lds, s>>>(P, w, L, n, sr); break;
+    default: k_lazy_round<0><<<blocks, kBlock, lds, s>>>(P, w, L, n, sr); break;
   }
   return hipGetLastError();
 }

@@ -59,7 +59,7 @@ void release(pdfs_ctx* c) {
                   c->items, c->slots, c->tallies, c->st, c->recs, c->tri, c->tri_s,
                   c->tri_rank, c->c_hist, c->deepq, c->lz.B, c->lz.Uc, c->lz.list, c->lz.cmax,
                   c->lz.cursor, c->lz.pool, c->lz.wins, c->lz.tcov, c->lz.uncs, c->lz.bits,
-                  c->lz.ctl, c->lz.shard, c->cw.order, c->cw.tt, c->cw.wc, c->cw.pref, c->cw.kc,
+                  c->lz.S, c->lz.U2, c->lz.n_win, c->lz.inc, c->lz.shard, c->cw.order, c->cw.tt, c->cw.wc, c->cw.pref, c->cw.kc,
                   c->cw.off, c->cw.ecnt, c->cw.genes, c->cw.q, c->cw.tg, c->cw.seg_v,
                   c->cw.seg_w, c->cw.tab_v, c->cw.tab_w, c->cw.bits};
   for (void* p : ptrs) dfree(c, p);
@@ -181,11 +181,14 @@ static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
     CK(c, dalloc(c, &L.Uc, (size_t)kMaxW64));
     CK(c, dalloc(c, &L.cursor, (size_t)kMaxCount + 1));
     CK(c, dalloc(c, &L.pool, (size_t)kLazyWaves));
-    CK(c, dalloc(c, &L.wins, (size_t)kLazyWaves));
+    CK(c, dalloc(c, &L.wins, (size_t)3 * (kLazyWaves / 4)));
+    CK(c, dalloc(c, &L.n_win, 3 * 64));
+    CK(c, dalloc(c, &L.inc, (size_t)2 * kCursorStride));
+    CK(c, dalloc(c, &L.S, 2));
+    CK(c, dalloc(c, &L.U2, (size_t)2 * kMaxW64));
     CK(c, dalloc(c, &L.tcov, (size_t)64 * kMaxW64));
     CK(c, dalloc(c, &L.uncs, (size_t)c->n_tumor + 2));
-    CK(c, dalloc(c, &L.ctl, (size_t)kLazyCtl));
-    CK(c, dalloc(c, &L.shard, (size_t)kIncShards * kCursorStride));
+    CK(c, dalloc(c, &L.shard, (size_t)2 * kIncShards * kCursorStride));
   }
   const size_t ln = (size_t)L.nw * L.seg;
   if (!L.list || c->lz_list_n < ln) {
@@ -440,14 +443,16 @@ int32_t ctx_fail(pdfs_ctx* c, int32_t code, const std::string& msg) { return fai
 // captured round when graphs are on, direct launches otherwise.  slot = the
 // chunk's event set when timing.
 static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int chunk, int slot) {
-  const Run& r = c->run;
+  Run& r = c->run;
   if (r.lazy) {
-    // one launch per round
+    // one launch per round, each committing the round before it; a last one
+    // commits the chunk's last round
     for (int k = 0; k < chunk; ++k) {
       if (c->time_kernels) CK(c, hipEventRecord(c->ev[slot][k][2], c->stream));
-      CK(c, launch_lazy_round(P, w, c->lz, c->stream));
+      CK(c, launch_lazy_round(P, w, c->lz, r.launches++, true, c->stream));
       if (c->time_kernels) CK(c, hipEventRecord(c->ev[slot][k][3], c->stream));
     }
+    CK(c, launch_lazy_round(P, w, c->lz, r.launches++, false, c->stream));
     return PDFS_OK;
   }
   if (c->use_graphs && !c->time_kernels) {
@@ -631,6 +636,7 @@ int32_t run_enqueue(pdfs_ctx* c) {
       const int32_t rc = enqueue_lists(c, P, w, slot);
       if (rc != PDFS_OK) return rc;
       r.listed = true;
+      r.launches = 0;
       r.time_pairs = c->time_kernels;
     }
     const int32_t rc = enqueue_rounds(c, P, w, n, slot);

@@ -206,31 +206,37 @@ struct Work {
 };
 
 // ---------------------------------------------------------------- lazy rounds
-// One address serves its atomics one at a time (about 60 ns each), so what
-// every block of a round updates is spread: the incumbent goes through shards
-// (a wave goes on to the round's own only if it raised its shard), the count
-// of finished blocks through groups.
 constexpr int kLazyWaves = 1024;   // waves of a lazy round at most
+// One address serves its atomics one at a time (about 60 ns each), so the
+// incumbent goes through shards: a wave goes on to the round's own only if it
+// raised its shard.
 constexpr int kIncShards = 32;
-constexpr int kTicketGroups = 32;
-constexpr int kLazyCtl = 64 * (2 + kTicketGroups);
+
+// Where a lazy run stands.  Launch n leaves the state of its round's start
+// (the last round committed) in entry n & 1 and reads entry (n - 1) & 1.
+struct LazyState {
+  int32_t n_unc, executed, rounds, done;
+  int32_t searched;   // the launch searched a round: its answer is to be committed
+};
 
 // Run-long workspace of the lazy rounds (k_lazy.hip), in the index space of
 // the run's first round (its active genes, its uncovered samples).
 struct LazyWork {
   uint64_t* B;                // [64 * w64][gw] a sample's genes, one bit each
-  uint64_t* Uc;               // [kMaxW64] uncovered mask
+  LazyState* S;               // [2]
+  uint64_t* U2;               // [2][kMaxW64] uncovered masks, by launch as S
+  uint64_t* Uc;               // [kMaxW64] the mask at the run's end
   unsigned long long* list;   // [nw][seg] pairs a | b << 16 | bound << 32
   int32_t* cmax;              // [nw][seg / 64] a chunk's largest bound
   uint32_t* cursor;           // [kMaxCount + 1] pairs of a count dealt so far
   Slot* pool;                 // [nw] a wave's best known leaf
-  Slot* wins;                 // [nw / 4] leaves that may be the round's answer
+  Slot* wins;                 // [3][kLazyWaves / 4] leaves that may be a launch's answer
+  uint32_t* n_win;            // [3 * 64] how many
+  unsigned long long* inc;    // [2 * kCursorStride] a launch's incumbent
   int32_t* tcov;              // [64 * kMaxW64] the round that covered a sample
   int32_t* uncs;              // [n_tumor + 2] uncovered samples at a round's start
   uint64_t* bits;             // [nw][levels][gw] candidate bitmaps of the general walk
-  unsigned long long* shard;  // [kIncShards * kCursorStride] incumbents of a part of the blocks
-  uint32_t* ctl;              // [0] entries of wins; [64 * (1 + i)] blocks of group i done;
-                              // [64 * (1 + kTicketGroups)] groups done
+  unsigned long long* shard;  // [2][kIncShards * kCursorStride] incumbents of a part of the blocks
   int32_t gw;                 // words of a row of B
   int32_t nw;                 // waves of the round kernel (a multiple of 4)
   int32_t seg;                // entries of a wave's share (a multiple of 64)
@@ -331,11 +337,14 @@ hipError_t launch_sort_triples(const Work& w, hipStream_t s);
 hipError_t launch_dfs4_tiles(const Problem& P, const Work& w, hipStream_t s);
 hipError_t launch_finish_round(const Problem& P, const Work& w, int phase_mask, int tally_mask,
                                hipStream_t s);
-// Lazy rounds: the run's lists from the pair list, then one launch per round.
+// Lazy rounds: the run's lists from the pair list, then a launch per round.
 int lazy_levels(int h);
 hipError_t launch_lazy_begin(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
 hipError_t launch_lazy_deal(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
-hipError_t launch_lazy_round(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
+// Launch n of the run: commits the answer of launch n - 1, then searches the
+// next round (search = false: commits only).
+hipError_t launch_lazy_round(const Problem& P, const Work& w, const LazyWork& L, int n,
+                             bool search, hipStream_t s);
 // The counters of a finished run into its state's totals.
 int count_segments(int nA);
 size_t count_table_rows(int nA);

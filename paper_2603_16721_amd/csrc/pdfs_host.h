@@ -46,6 +46,7 @@ struct Run {
   bool lazy = false;        // lazy rounds (k_lazy.hip)
   bool listed = false;      // lazy rounds: the run's pair lists are queued
   int w64 = 1;              // lazy rounds: row width of the run
+  int launches = 0;         // lazy rounds: launches queued since the lists
   int count_slot = -1;      // lazy rounds: the counters are queued, read with this slot
   bool time_pairs = false;  // lazy rounds: the next chunk read holds the pair table's events
   int32_t status = PDFS_OK;
