@@ -70,9 +70,9 @@ __global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
     p[i] = v;
 }
 
-// One block per tile.  tile_hist [ntiles][nkeys] must be zero.
+// One block per tile.  tile_hist [nkeys][ntiles] must be zero.
 __global__ __launch_bounds__(kSortTile) void k_sort_tile_ranks(const uint32_t* __restrict__ counts,
-                                                               int G, int nkeys,
+                                                               int G,
                                                                uint32_t* __restrict__ tile_hist,
                                                                uint32_t* __restrict__ rank) {
   __shared__ uint32_t key[kSortTile];
@@ -90,24 +90,21 @@ __global__ __launch_bounds__(kSortTile) void k_sort_tile_ranks(const uint32_t* _
     last = last && !(same && j > i);
   }
   rank[g] = r;
-  if (last) tile_hist[(size_t)blockIdx.x * nkeys + k] = r + 1;
+  if (last) tile_hist[(size_t)k * gridDim.x + blockIdx.x] = r + 1;
 }
 
-// One block: tile_hist[t][k] <- first position of the genes of tile t with
-// key k (exclusive scan in the order k major, t minor).
-__global__ __launch_bounds__(1024) void k_sort_scan(uint32_t* __restrict__ tile_hist, int nkeys,
-                                                    int ntiles) {
+// One block: tile_hist[k][t] <- first position of the genes of tile t with
+// key k (exclusive scan; the table is laid out in that order, so a thread's
+// stretch is contiguous: 31 us against 200 us across it at G = 20000).
+__global__ __launch_bounds__(1024) void k_sort_scan(uint32_t* __restrict__ tile_hist, size_t n) {
   __shared__ uint32_t part[1024];
   const int tid = threadIdx.x;
-  const size_t n = (size_t)nkeys * ntiles;
   const size_t per = (n + 1023) / 1024;
   const size_t lo = (size_t)tid * per < n ? (size_t)tid * per : n;
   const size_t hi = lo + per < n ? lo + per : n;
-  auto at = [&](size_t e) -> uint32_t& {
-    return tile_hist[(e % (size_t)ntiles) * nkeys + e / (size_t)ntiles];
-  };
   uint32_t sum = 0;
-  for (size_t e = lo; e < hi; ++e) sum += at(e);
+#pragma unroll 8
+  for (size_t e = lo; e < hi; ++e) sum += tile_hist[e];
   part[tid] = sum;
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {
@@ -117,20 +114,21 @@ __global__ __launch_bounds__(1024) void k_sort_scan(uint32_t* __restrict__ tile_
     __syncthreads();
   }
   uint32_t run = part[tid] - sum;
+#pragma unroll 8
   for (size_t e = lo; e < hi; ++e) {
-    const uint32_t x = at(e);
-    at(e) = run;
+    const uint32_t x = tile_hist[e];
+    tile_hist[e] = run;
     run += x;
   }
 }
 
 __global__ void k_sort_scatter(const uint32_t* __restrict__ counts,
                                const uint32_t* __restrict__ rank,
-                               const uint32_t* __restrict__ tile_first, int G, int nkeys,
+                               const uint32_t* __restrict__ tile_first, int G, int ntiles,
                                int32_t* __restrict__ perm) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= G) return;
-  const uint32_t pos = tile_first[(size_t)(g / kSortTile) * nkeys + counts[g]] + rank[g];
+  const uint32_t pos = tile_first[(size_t)counts[g] * ntiles + g / kSortTile] + rank[g];
   perm[pos] = g;
 }
 
@@ -676,9 +674,9 @@ hipError_t sort_genes(const uint32_t* counts, int G, int max_key, uint32_t* tmp,
   const size_t nh = (size_t)ntiles * nkeys;
   k_fill_u32<<<(int)((nh + 255) / 256 < 1024 ? (nh + 255) / 256 : 1024), 256, 0, s>>>(tile_hist,
                                                                                      nh, 0u);
-  k_sort_tile_ranks<<<ntiles, kSortTile, 0, s>>>(counts, G, nkeys, tile_hist, rank);
-  k_sort_scan<<<1, 1024, 0, s>>>(tile_hist, nkeys, ntiles);
-  k_sort_scatter<<<(G + 255) / 256, 256, 0, s>>>(counts, rank, tile_hist, G, nkeys, perm);
+  k_sort_tile_ranks<<<ntiles, kSortTile, 0, s>>>(counts, G, tile_hist, rank);
+  k_sort_scan<<<1, 1024, 0, s>>>(tile_hist, nh);
+  k_sort_scatter<<<(G + 255) / 256, 256, 0, s>>>(counts, rank, tile_hist, G, ntiles, perm);
   return hipGetLastError();
 }
 

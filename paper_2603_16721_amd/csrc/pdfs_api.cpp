@@ -38,6 +38,7 @@ int32_t fail(pdfs_ctx* c, int32_t code, const std::string& msg) {
 hipError_t dmalloc(pdfs_ctx* c, void** p, size_t bytes) {
   bytes += 256;
   c->bytes += bytes;
+  if (c->async_alloc && c->pool) return hipMallocFromPoolAsync(p, bytes, c->pool, c->stream);
   if (c->async_alloc) return hipMallocAsync(p, bytes, c->stream);
   return hipMalloc(p, bytes);
 }
@@ -53,16 +54,41 @@ hipError_t dalloc(pdfs_ctx* c, T** p, size_t n) {
   return dmalloc(c, reinterpret_cast<void**>(p), n * sizeof(T));
 }
 
+// Several buffers in one allocation, kept until the context goes (a request's
+// 35 allocations took the server's worker 0.2 ms, their frees 0.3 ms).
+struct Part {
+  void** p;
+  size_t bytes;
+};
+
+template <typename T>
+Part part(T** p, size_t n) {
+  return {reinterpret_cast<void**>(p), n * sizeof(T)};
+}
+
+hipError_t dalloc_kept(pdfs_ctx* c, std::initializer_list<Part> parts) {
+  size_t total = 0;
+  for (const Part& q : parts) total += (q.bytes + 511) / 256 * 256;   // as dmalloc: some slack each
+  void* block = nullptr;
+  const hipError_t e = dmalloc(c, &block, total);
+  if (e != hipSuccess) return e;
+  c->blocks.push_back(block);
+  char* at = static_cast<char*>(block);
+  for (const Part& q : parts) {
+    *q.p = at;
+    at += (q.bytes + 511) / 256 * 256;
+  }
+  return hipSuccess;
+}
+
 void release(pdfs_ctx* c) {
-  void* ptrs[] = {c->Ts, c->Ns, c->perm, c->ncount, c->U, c->cols, c->act, c->flags, c->TA, c->NA,
-                  c->A8, c->N8, c->pairs, c->work_pairs, c->seed_pairs, c->hist, c->cursors,
-                  c->items, c->slots, c->tallies, c->st, c->recs, c->tri, c->tri_s,
-                  c->tri_rank, c->c_hist, c->deepq, c->lz.B, c->lz.Uc, c->lz.list, c->lz.cmax,
-                  c->lz.cursor, c->lz.pool, c->lz.wins, c->lz.tcov, c->lz.uncs, c->lz.bits,
-                  c->lz.S, c->lz.U2, c->lz.n_win, c->lz.inc, c->lz.shard, c->cw.order, c->cw.tt, c->cw.wc, c->cw.pref, c->cw.kc,
-                  c->cw.off, c->cw.ecnt, c->cw.genes, c->cw.q, c->cw.tg, c->cw.seg_v,
-                  c->cw.seg_w, c->cw.tab_v, c->cw.tab_w, c->cw.bits};
+  void* ptrs[] = {c->TA, c->NA, c->A8, c->N8, c->pairs, c->work_pairs, c->seed_pairs, c->items,
+                  c->tri, c->tri_s, c->tri_rank, c->c_hist, c->deepq, c->lz.B, c->lz.list,
+                  c->lz.cmax, c->lz.bits, c->cw.pref, c->cw.q, c->cw.seg_v, c->cw.seg_w,
+                  c->cw.tab_v, c->cw.tab_w, c->cw.bits};
   for (void* p : ptrs) dfree(c, p);
+  for (void* p : c->blocks) dfree(c, p);
+  c->blocks.clear();
   if (c->h_slots && c->own_h_st) (void)hipHostFree(c->h_slots);
   for (auto& set : c->ev)
     for (auto& row : set)
@@ -178,17 +204,12 @@ static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
     return PDFS_OK;
   };
   if (!L.Uc) {
-    CK(c, dalloc(c, &L.Uc, (size_t)kMaxW64));
-    CK(c, dalloc(c, &L.cursor, (size_t)kMaxCount + 1));
-    CK(c, dalloc(c, &L.pool, (size_t)kLazyWaves));
-    CK(c, dalloc(c, &L.wins, (size_t)3 * (kLazyWaves / 4)));
-    CK(c, dalloc(c, &L.n_win, 3 * 64));
-    CK(c, dalloc(c, &L.inc, (size_t)2 * kCursorStride));
-    CK(c, dalloc(c, &L.S, 2));
-    CK(c, dalloc(c, &L.U2, (size_t)2 * kMaxW64));
-    CK(c, dalloc(c, &L.tcov, (size_t)64 * kMaxW64));
-    CK(c, dalloc(c, &L.uncs, (size_t)c->n_tumor + 2));
-    CK(c, dalloc(c, &L.shard, (size_t)2 * kIncShards * kCursorStride));
+    CK(c, dalloc_kept(c, {part(&L.Uc, kMaxW64), part(&L.cursor, kMaxCount + 1),
+                          part(&L.pool, kLazyWaves), part(&L.wins, 3 * (kLazyWaves / 4)),
+                          part(&L.n_win, 3 * 64), part(&L.inc, 2 * kCursorStride),
+                          part(&L.S, 2), part(&L.U2, 2 * kMaxW64), part(&L.tcov, 64 * kMaxW64),
+                          part(&L.uncs, (size_t)c->n_tumor + 2),
+                          part(&L.shard, 2 * kIncShards * kCursorStride)}));
   }
   const size_t ln = (size_t)L.nw * L.seg;
   if (!L.list || c->lz_list_n < ln) {
@@ -237,14 +258,11 @@ static int32_t ensure_count(pdfs_ctx* c, int h, int w64, int rounds) {
     return PDFS_OK;
   };
   if (!C.order) {
-    CK(c, dalloc(c, &C.order, (size_t)64 * kMaxW64));
-    CK(c, dalloc(c, &C.tt, (size_t)64 * kMaxW64));
-    CK(c, dalloc(c, &C.wc, (size_t)kCountMaxT + 1));
-    CK(c, dalloc(c, &C.kc, (size_t)64 * kMaxW64));
-    CK(c, dalloc(c, &C.off, (size_t)64 * kMaxW64));
-    CK(c, dalloc(c, &C.ecnt, (size_t)64 * kMaxW64 * 16));
-    CK(c, dalloc(c, &C.genes, (size_t)c->tumor_bits));
-    CK(c, dalloc(c, &C.tg, (size_t)count_segments(c->G) * 512));
+    CK(c, dalloc_kept(c, {part(&C.order, 64 * kMaxW64), part(&C.tt, 64 * kMaxW64),
+                          part(&C.wc, kCountMaxT + 1), part(&C.kc, 64 * kMaxW64),
+                          part(&C.off, 64 * kMaxW64), part(&C.ecnt, 64 * kMaxW64 * 16),
+                          part(&C.genes, (size_t)c->tumor_bits),
+                          part(&C.tg, (size_t)count_segments(c->G) * 512)}));
   }
   C.q_n = (size_t)c->tumor_bits;
   int32_t rc = grow(&C.pref, c->cw_pref_n, (size_t)64 * w64 * c->lz.gw);
@@ -445,14 +463,15 @@ int32_t ctx_fail(pdfs_ctx* c, int32_t code, const std::string& msg) { return fai
 static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int chunk, int slot) {
   Run& r = c->run;
   if (r.lazy) {
-    // one launch per round, each committing the round before it; a last one
-    // commits the chunk's last round
+    // one launch per round, each committing the round before it
     for (int k = 0; k < chunk; ++k) {
       if (c->time_kernels) CK(c, hipEventRecord(c->ev[slot][k][2], c->stream));
       CK(c, launch_lazy_round(P, w, c->lz, r.launches++, true, c->stream));
       if (c->time_kernels) CK(c, hipEventRecord(c->ev[slot][k][3], c->stream));
     }
-    CK(c, launch_lazy_round(P, w, c->lz, r.launches++, false, c->stream));
+    // (needed where no further launch follows, or each chunk's times are read)
+    if (c->time_kernels || (r.max_rounds > 0 && r.enqueued + chunk >= r.max_rounds))
+      CK(c, launch_lazy_round(P, w, c->lz, r.launches++, false, c->stream));
     return PDFS_OK;
   }
   if (c->use_graphs && !c->time_kernels) {
@@ -608,6 +627,7 @@ int32_t run_start(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int ma
   r = Run();
   r.h = h; r.p = p; r.q = q; r.target = target; r.max_rounds = max_rounds; r.n_unc = n_unc;
   r.lazy = lazy; r.w64 = w64;
+  if (lazy) r.chunk = 8;   // rounds of 10-30 us, no-ops past the end of 2 us
   const Problem P = make_problem(c, h, p, q);
   Work w0 = make_work(c, 1, target);
   CK(c, launch_run_begin(P, w0, max_rounds, c->stream));
@@ -731,7 +751,7 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
     r.inflight = 0;
     r.enqueued = executed;
     r.executed_before = executed;
-    r.chunk = 1;
+    r.chunk = r.lazy ? 8 : 1;
     r.t_prev = std::chrono::steady_clock::now();
     return PDFS_OK;
   }
@@ -891,14 +911,24 @@ int32_t set_uncovered(pdfs_ctx* c, const uint64_t* mask) {
   return c->n_tumor;
 }
 
-int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds) {
+bool run_drained(pdfs_ctx* c) {
+  if (c->run.inflight > 0) {
+    const int newest = (c->next_slot - 1 + kDepth) % kDepth;
+    if (hipEventQuery(c->chunk_done[newest]) == hipErrorNotReady) return false;
+    c->run.inflight = 0;
+  }
+  return true;
+}
+
+int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds,
+                    hipStream_t over) {
   *rounds = c->h_st->rounds;
   const int n = *rounds < cap ? *rounds : cap;
   if (n > 0 && out) {
     std::vector<RoundRecord> recs((size_t)n);
     CK(c, hipMemcpyAsync(recs.data(), c->recs, sizeof(RoundRecord) * recs.size(),
-                         hipMemcpyDeviceToHost, c->stream));
-    CK(c, hipStreamSynchronize(c->stream));
+                         hipMemcpyDeviceToHost, over));
+    CK(c, hipStreamSynchronize(over));
     for (int i = 0; i < n; ++i) {
       if (c->run.lazy)   // recorded by sorted index only
         for (int k = 0; k < c->run.h; ++k) recs[i].genes[k] = c->h_perm[recs[i].sorted_idx[k]];
@@ -1000,7 +1030,7 @@ namespace pdfs {
 const std::string& create_error() { return g_create_error; }
 
 int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out,
-                   RoundState* pinned_state, bool async_alloc) {
+                   RoundState* pinned_state, bool async_alloc, hipMemPool_t pool) {
   if (!out) return fail(nullptr, PDFS_ERR_INVALID_ARG, "out is NULL");
   *out = nullptr;
   if (!m) return fail(nullptr, PDFS_ERR_INVALID_ARG, "matrix is NULL");
@@ -1025,6 +1055,7 @@ int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out
   c->device = opt ? opt->device : 0;
   c->stream = opt ? static_cast<hipStream_t>(opt->stream) : nullptr;
   c->async_alloc = async_alloc && c->stream != nullptr;
+  c->pool = pool;
   c->prune_mode = mode;
   c->time_kernels = opt && (opt->flags & PDFS_OPT_TIME_KERNELS);
   c->pair_cap_hint = opt && opt->pair_cap > 0 ? (unsigned long long)opt->pair_cap : 0ull;
@@ -1063,13 +1094,30 @@ int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out
   const uint64_t* dN = m->normal;
   uint64_t* stageT = nullptr;
   uint64_t* stageN = nullptr;
+  int* d_bad = nullptr;
+  uint32_t* counts = nullptr;
+  uint32_t* sort_tmp = nullptr;
+  const int max_key = m->n_tumor + m->n_normal;
+  const size_t host_rows = m->on_device ? 0 : (size_t)G;
+  // (first of the kept blocks until free_stage)
+  CKC(dalloc_kept(c, {part(&stageT, host_rows * (size_t)m->tumor_stride_words),
+                      part(&stageN, m->n_normal > 0 ? host_rows * (size_t)m->normal_stride_words : 0),
+                      part(&d_bad, 1), part(&counts, (size_t)G),
+                      part(&sort_tmp, sort_tmp_words(G, max_key))}));
+  c->rec_cap = m->n_tumor + 1;   // every found round covers at least one sample
+  CKC(dalloc_kept(c, {part(&c->perm, (size_t)G), part(&c->Ts, (size_t)G * wt),
+                      part(&c->Ns, (size_t)G * c->wn), part(&c->ncount, (size_t)G),
+                      part(&c->U, (size_t)wt), part(&c->cols, (size_t)m->n_tumor),
+                      part(&c->act, (size_t)G), part(&c->flags, (size_t)G), part(&c->st, 1),
+                      part(&c->recs, (size_t)c->rec_cap),
+                      part(&c->slots, (size_t)kSlotPhases * kSlotsPerPhase),
+                      part(&c->hist, kMaxCount + 1), part(&c->cursors, kSubQueues * kCursorStride),
+                      part(&c->tallies, (size_t)kSlotPhases * kPersistBlocks * kTallyN)}));
   if (!m->on_device) {
-    CKC(dalloc(c, &stageT, (size_t)G * m->tumor_stride_words));
     CKC(hipMemcpyAsync(stageT, m->tumor, (size_t)G * m->tumor_stride_words * 8,
                        hipMemcpyHostToDevice, s));
     dT = stageT;
     if (m->n_normal > 0) {
-      CKC(dalloc(c, &stageN, (size_t)G * m->normal_stride_words));
       CKC(hipMemcpyAsync(stageN, m->normal, (size_t)G * m->normal_stride_words * 8,
                          hipMemcpyHostToDevice, s));
       dN = stageN;
@@ -1077,21 +1125,17 @@ int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out
   }
   if (m->n_normal == 0) dN = nullptr;
   auto free_stage = [&]() {
-    dfree(c, stageT);
-    dfree(c, stageN);
-    stageT = stageN = nullptr;
+    dfree(c, c->blocks.front());
+    c->blocks.erase(c->blocks.begin());
   };
 
   // Pad bits must be zero.
-  int* d_bad = nullptr;
-  CKC(dalloc(c, &d_bad, 1));
   CKC(hipMemsetAsync(d_bad, 0, sizeof(int), s));
   CKC(launch_check_pad(dT, m->tumor_stride_words, G, m->n_tumor, d_bad, s));
   if (dN) CKC(launch_check_pad(dN, m->normal_stride_words, G, m->n_normal, d_bad, s));
   int bad = 0;
   CKC(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, s));
   CKC(hipStreamSynchronize(s));
-  dfree(c, d_bad);
   if (bad) {
     free_stage();
     c->err = "nonzero bits past the sample count";
@@ -1099,40 +1143,18 @@ int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out
   }
 
   // Sparsest-first order: stable counting sort of the combined counts.
-  uint32_t* counts = nullptr;
-  uint32_t* sort_tmp = nullptr;
-  const int max_key = m->n_tumor + m->n_normal;
-  CKC(dalloc(c, &counts, (size_t)G));
-  CKC(dalloc(c, &sort_tmp, sort_tmp_words(G, max_key)));
-  CKC(dalloc(c, &c->perm, (size_t)G));
   CKC(launch_gene_counts(dT, m->tumor_stride_words, dN, m->normal_stride_words, G, wt, wn_in,
                          counts, s));
   CKC(sort_genes(counts, G, max_key, sort_tmp, c->perm, s));
-  CKC(dalloc(c, &c->Ts, (size_t)G * wt));
-  CKC(dalloc(c, &c->Ns, (size_t)G * c->wn));
   CKC(launch_gather_sorted(dT, m->tumor_stride_words, dN, m->normal_stride_words, c->perm, G, wt,
                            c->wn, c->Ts, c->Ns, s));
-  CKC(dalloc(c, &c->ncount, (size_t)G));
   CKC(launch_normal_counts(c->Ns, G, c->wn, c->ncount, s));
   c->h_perm.resize(G);
   CKC(hipMemcpyAsync(c->h_perm.data(), c->perm, sizeof(int32_t) * G, hipMemcpyDeviceToHost, s));
   CKC(hipStreamSynchronize(s));
-  dfree(c, sort_tmp);
-  dfree(c, counts);
   free_stage();
 
   // Upper bound of the active list: genes with any tumour mutation.
-  CKC(dalloc(c, &c->U, (size_t)wt));
-  CKC(dalloc(c, &c->cols, (size_t)m->n_tumor));
-  CKC(dalloc(c, &c->act, (size_t)G));
-  CKC(dalloc(c, &c->flags, (size_t)G));
-  CKC(dalloc(c, &c->st, 1));
-  c->rec_cap = m->n_tumor + 1;   // every found round covers at least one sample
-  CKC(dalloc(c, &c->recs, (size_t)c->rec_cap));
-  CKC(dalloc(c, &c->slots, (size_t)kSlotPhases * kSlotsPerPhase));
-  CKC(dalloc(c, &c->hist, (size_t)kMaxCount + 1));
-  CKC(dalloc(c, &c->cursors, (size_t)kSubQueues * kCursorStride));
-  CKC(dalloc(c, &c->tallies, (size_t)kSlotPhases * kPersistBlocks * kTallyN));
   if (pinned_state) {
     c->h_slots = pinned_state;
     c->own_h_st = false;
@@ -1188,7 +1210,7 @@ int32_t pdfs_best_combo(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q, const ui
   if (rc != PDFS_OK) return rc;
   end_stats(c, stats, t0);
   int32_t rounds = 0;
-  rc = run_records(c, out, 1, &rounds);
+  rc = run_records(c, out, 1, &rounds, c->stream);
   if (rc != PDFS_OK) return rc;
   return rounds < 1 ? PDFS_NO_COMBO : PDFS_OK;
 }
@@ -1209,7 +1231,7 @@ int32_t pdfs_wsc_run(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q, int32_t tar
   rc = run_blocking(c, h, p, q, K, max_rounds > 0 ? max_rounds : 0, n_unc);
   if (rc != PDFS_OK) return rc;
   int32_t rounds = 0;
-  rc = run_records(c, out, cap, &rounds);
+  rc = run_records(c, out, cap, &rounds, c->stream);
   if (rc != PDFS_OK) return rc;
   *n_out = rounds;
   if (final_uncovered) {

@@ -822,7 +822,7 @@ int32_t pdfs_batch_run(pdfs_batch* b, const int32_t* h, uint32_t p, uint32_t q,
     pdfs_ctx* c = b->ctx[i];
     int32_t rounds = 0;
     const int cap = caps ? caps[i] : 0;
-    const int32_t rc = run_records(c, outs ? outs[i] : nullptr, cap, &rounds);
+    const int32_t rc = run_records(c, outs ? outs[i] : nullptr, cap, &rounds, c->stream);
     if (rc != PDFS_OK) return batch_fail(b, rc, i);
     n_outs[i] = rounds;
     if (rounds > cap) {
@@ -884,6 +884,9 @@ struct Request {
 
 }  // namespace
 
+// Freed device memory a server's pool may hold back (it also fits the budget).
+constexpr uint64_t kPoolBytes = 2ull << 30;
+
 struct pdfs_server {
   int device = 0;
   int prune_mode = PDFS_PRUNE_BOUND;
@@ -895,12 +898,18 @@ struct pdfs_server {
   std::condition_variable cv;
   std::deque<std::shared_ptr<Request>> queue;
   std::vector<std::shared_ptr<Request>> active;
+  std::vector<std::shared_ptr<Request>> draining;   // answered, queued no-ops left (worker only)
   std::map<uint64_t, std::shared_ptr<Request>> tickets;
   std::thread worker;
   bool stop = false;
   uint64_t next_ticket = 1;
   int next_stream = 0;
   hipStream_t admit_stream = nullptr;   // ingest of admitted requests
+  // Requests' device memory comes from a pool of the server's own, which keeps
+  // up to kPoolBytes of freed memory for the next requests: from the device's
+  // default pool a request's buffers cost the worker 0.4-1.4 ms to get and
+  // 1-2.4 ms to give back, nearly all of a burst's time (12 requests: 31 ms).
+  hipMemPool_t pool = nullptr;
   std::string err;   // detail of the last failing call (guarded by mu)
 };
 
@@ -912,17 +921,9 @@ int32_t server_fail(pdfs_server* s, int32_t code, const std::string& msg) {
   return code;
 }
 
-// Finishes a run: records copied to the request, device memory released.
-void complete(pdfs_server* s, const std::shared_ptr<Request>& r, int32_t status) {
-  if (status == PDFS_OK && r->ctx) {
-    r->result.resize((size_t)r->ctx->n_tumor + 1);
-    int32_t rounds = 0;
-    status = run_records(r->ctx, r->result.data(), (int32_t)r->result.size(), &rounds);
-    r->rounds = rounds;
-    r->result.resize((size_t)std::min<int32_t>(rounds, (int32_t)r->result.size()));
-  }
-  if (status != PDFS_OK && status != PDFS_ERR_TRUNCATED)
-    r->err = r->ctx ? r->ctx->err : create_error();
+// Gives back what a finished request held: its device memory (in stream
+// order) and its pinned state slots.
+void release_request(pdfs_server* s, const std::shared_ptr<Request>& r) {
   if (r->ctx) {
     pdfs_destroy(r->ctx);
     r->ctx = nullptr;
@@ -931,13 +932,35 @@ void complete(pdfs_server* s, const std::shared_ptr<Request>& r, int32_t status)
   if (r->pinned) s->pinned_pool.push_back(r->pinned);
   r->pinned = nullptr;
   s->used -= r->bytes;
-  r->t_done = Clock::now();
-  r->status = status;
-  r->T.clear();
-  r->T.shrink_to_fit();
-  r->N.clear();
-  r->N.shrink_to_fit();
-  s->cv.notify_all();
+}
+
+// Finishes a run: records copied to the request, the answer handed out.  The
+// run's chunks still queued behind others' on the shared stream are not waited
+// for (that held the worker up to 5 ms): what it held is released once they
+// are through.
+void complete(pdfs_server* s, const std::shared_ptr<Request>& r, int32_t status) {
+  if (status == PDFS_OK && r->ctx) {
+    r->result.resize((size_t)r->ctx->n_tumor + 1);
+    int32_t rounds = 0;
+    status = run_records(r->ctx, r->result.data(), (int32_t)r->result.size(), &rounds,
+                         s->admit_stream);
+    r->rounds = rounds;
+    r->result.resize((size_t)std::min<int32_t>(rounds, (int32_t)r->result.size()));
+  }
+  if (status != PDFS_OK && status != PDFS_ERR_TRUNCATED)
+    r->err = r->ctx ? r->ctx->err : create_error();
+  {
+    std::lock_guard<std::mutex> g(s->mu);
+    r->t_done = Clock::now();
+    r->status = status;
+    r->T.clear();
+    r->T.shrink_to_fit();
+    r->N.clear();
+    r->N.shrink_to_fit();
+    s->cv.notify_all();
+  }
+  if (r->ctx && !run_drained(r->ctx)) s->draining.push_back(r);
+  else release_request(s, r);
 }
 
 // Admission: FIFO; the head request waits until a slot is free and its
@@ -951,8 +974,12 @@ bool admit_one(pdfs_server* s) {
     r = s->queue.front();
     if (s->used + r->bytes > s->budget) return false;
     size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && r->bytes + (64ull << 20) > free_b)
-      return false;
+    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && r->bytes + (64ull << 20) > free_b) {
+      // what the pool holds back counts as used: give it up before waiting
+      if (s->pool) (void)hipMemPoolTrimTo(s->pool, 0);
+      if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && r->bytes + (64ull << 20) > free_b)
+        return false;
+    }
     s->queue.pop_front();
     s->used += r->bytes;
     r->pinned = s->pinned_pool.back();
@@ -966,7 +993,7 @@ bool admit_one(pdfs_server* s) {
   o.device = s->device;
   o.stream = s->admit_stream;
   o.flags = PDFS_OPT_GRAPHS;
-  int32_t rc = create_ctx(&r->m, &o, &r->ctx, r->pinned, true);
+  int32_t rc = create_ctx(&r->m, &o, &r->ctx, r->pinned, true, s->pool);
   if (rc == PDFS_OK) r->ctx->want_counters = false;   // answers carry no statistics
   if (rc == PDFS_OK) {
     r->ctx->stream = s->streams[s->next_stream++ % (int)s->streams.size()];
@@ -995,18 +1022,26 @@ void worker_loop(pdfs_server* s) {
   for (;;) {
     {
       std::unique_lock<std::mutex> g(s->mu);
-      if (s->stop && s->queue.empty() && s->active.empty()) return;
-      if (s->queue.empty() && s->active.empty())
+      if (s->stop && s->queue.empty() && s->active.empty() && s->draining.empty()) return;
+      if (s->queue.empty() && s->active.empty() && s->draining.empty())
         s->cv.wait_for(g, std::chrono::milliseconds(5));
     }
-    while (admit_one(s)) {
+    for (size_t i = 0; i < s->draining.size();) {
+      if (!run_drained(s->draining[i]->ctx)) {
+        ++i;
+        continue;
+      }
+      const std::shared_ptr<Request> r = s->draining[i];
+      s->draining.erase(s->draining.begin() + (long)i);
+      release_request(s, r);
     }
+    // one ingest at a time (about 0.4 ms), the running requests fed in between
+    bool progressed = admit_one(s);
     std::vector<std::shared_ptr<Request>> act;
     {
       std::lock_guard<std::mutex> g(s->mu);
       act = s->active;
     }
-    bool progressed = false;
     for (auto& r : act) {
       int32_t rc = run_enqueue(r->ctx);
       bool ready = false, done = false;
@@ -1021,7 +1056,8 @@ void worker_loop(pdfs_server* s) {
         progressed = true;
       }
     }
-    if (!progressed && !act.empty()) std::this_thread::sleep_for(std::chrono::microseconds(20));
+    if (!progressed && (!act.empty() || !s->draining.empty()))
+      std::this_thread::sleep_for(std::chrono::microseconds(20));
   }
 }
 
@@ -1059,6 +1095,20 @@ int32_t pdfs_server_create(const pdfs_options* opt, uint64_t hbm_budget_bytes, i
     return ctx_fail(nullptr, PDFS_ERR_DEVICE, "hipMemGetInfo failed");
   }
   s->budget = hbm_budget_bytes ? (size_t)hbm_budget_bytes : free_b / 10 * 9;
+  hipMemPoolProps props = {};
+  props.allocType = hipMemAllocationTypePinned;
+  props.location.type = hipMemLocationTypeDevice;
+  props.location.id = s->device;
+  if (hipMemPoolCreate(&s->pool, &props) != hipSuccess) {
+    (void)hipGetLastError();
+    s->pool = nullptr;   // the device's default pool serves as well
+  } else {
+    uint64_t keep = std::min<uint64_t>(kPoolBytes, s->budget);
+    (void)hipMemPoolSetAttribute(s->pool, hipMemPoolAttrReleaseThreshold, &keep);
+    // an ingest never waits for the rounds queued before a free
+    int no = 0;
+    (void)hipMemPoolSetAttribute(s->pool, hipMemPoolReuseAllowInternalDependencies, &no);
+  }
   for (int k = 0; k < kStreams; ++k) {
     hipStream_t st = nullptr;
     if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
@@ -1183,6 +1233,9 @@ void pdfs_server_destroy(pdfs_server* s) {
   }
   if (s->worker.joinable()) s->worker.join();
   (void)hipSetDevice(s->device);
+  for (hipStream_t st : s->streams) (void)hipStreamSynchronize(st);   // the frees queued there
+  if (s->admit_stream) (void)hipStreamSynchronize(s->admit_stream);
+  if (s->pool) (void)hipMemPoolDestroy(s->pool);
   for (hipStream_t st : s->streams) (void)hipStreamDestroy(st);
   if (s->admit_stream) (void)hipStreamDestroy(s->admit_stream);
   for (RoundState* p : s->pinned_pool) (void)hipHostFree(p);

@@ -133,18 +133,20 @@ struct pdfs_ctx {
   std::map<std::tuple<int, int, uint32_t, uint32_t, int, int, int, int, bool, int>, hipGraphExec_t>
       graphs;
   size_t bytes = 0;                    // device bytes held (admission accounting)
+  std::vector<void*> blocks;           // allocations that hold several of the buffers above
   bool async_alloc = false;            // stream-ordered allocation (batched / served)
+  hipMemPool_t pool = nullptr;         // from this pool (the server's), or the device's
   bool own_h_st = true;                // h_slots allocated by the context
 };
 
 namespace pdfs {
 
 int32_t ctx_fail(pdfs_ctx* c, int32_t code, const std::string& msg);
-// pdfs_create with two internal options: pinned_state (caller-owned pinned
-// memory of kPinnedBytes, or NULL) and stream-ordered allocation on
-// opt->stream.
+// pdfs_create with three internal options: pinned_state (caller-owned pinned
+// memory of kPinnedBytes, or NULL), stream-ordered allocation on opt->stream,
+// and the memory pool it takes from.
 int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out,
-                   RoundState* pinned_state, bool async_alloc);
+                   RoundState* pinned_state, bool async_alloc, hipMemPool_t pool = nullptr);
 void begin_stats(pdfs_ctx* c, pdfs_stats* st);
 void end_stats(pdfs_ctx* c, pdfs_stats* st, std::chrono::steady_clock::time_point t0);
 const std::string& create_error();
@@ -171,7 +173,13 @@ int32_t run_blocking(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int
 // One round record as the ABI's pdfs_combo.
 void fill_combo(pdfs_combo* o, const RoundRecord& r, int h);
 // Copies up to cap round records of the finished run into out; returns rounds.
-int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds);
+// The run's end has been read, so the copy may go over any stream: one whose
+// other work need not be waited for.
+int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds,
+                    hipStream_t over);
+// True once the chunks a stopped run still had queued (no-ops past its end,
+// whose state copies write the pinned slots) are through; does not wait.
+bool run_drained(pdfs_ctx* c);
 int32_t check_call(pdfs_ctx* c, int h, uint32_t p, uint32_t q);
 // Sets U from a host mask (NULL = all samples); returns |U| or -1.
 int32_t set_uncovered(pdfs_ctx* c, const uint64_t* mask);
