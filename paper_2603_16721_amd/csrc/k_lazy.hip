@@ -198,6 +198,7 @@ struct WaveLds {
 };
 
 constexpr int kLazyCap(int h) { return h <= 5 ? 256 : 128; }
+constexpr int kListSamples = 256;   // samples of a pair whose candidates are listed, at most
 constexpr int kLazyLevels(int h) { return h <= 4 ? 1 : h - 3; }
 
 size_t lazy_wave_bytes(int h) {
@@ -717,12 +718,52 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
   return (uint64_t)hi << 32 | lo;
 }
 
+// A candidate's samples as a mask over the pair's m <= 64 * MW.
+template <int MW>
+struct Mask {
+  uint64_t w[MW];
+};
+
+template <int MW>
+__device__ __forceinline__ int mask_count(const Mask<MW>& m) {
+  int c = 0;
+#pragma unroll
+  for (int k = 0; k < MW; ++k) c += popc64(m.w[k]);
+  return c;
+}
+
+// Every lane's candidate row cut to the samples of y2 (lane k: word k).
+template <int MW>
+__device__ __forceinline__ Mask<MW> sample_mask(const Wave& v, uint64_t y2, int ix, bool on) {
+  Mask<MW> m;
+#pragma unroll
+  for (int k = 0; k < MW; ++k) m.w[k] = 0;
+  const uint64_t* row = v.T + (size_t)(on ? ix : 0) * v.w64;
+  int pos = 0;
+  for (int k = 0; k < v.w64; ++k) {
+    uint64_t yk = readlane64(y2, k);
+    if (!yk) continue;
+    const uint64_t r = on ? row[k] : 0ull;
+    while (yk) {
+      const uint64_t bit = ((r >> __builtin_ctzll(yk)) & 1ull) << (pos & 63);
+      yk &= yk - 1;
+#pragma unroll
+      for (int i = 0; i < MW; ++i) m.w[i] |= i == (pos >> 6) ? bit : 0ull;
+      ++pos;
+    }
+  }
+  return m;
+}
+
 // The same walk over a list of at most 64 candidates held one per lane (gene
 // ix, samples mk; `set`: the lanes of this level): an entry's children are the
 // later lanes that share enough of its samples.  No LDS round trip per entry:
-// 20 candidates at h = 5 take 13 us from the LDS lists, 7 us here.
-template <int LV>
-__device__ __forceinline__ void open_lanes(Wave& v, uint64_t mk, int ix, unsigned long long set) {
+// 20 candidates at h = 5 take 13 us from the LDS lists, 7 us here; and masks
+// of several words cost little more, where the general walk takes about 6 us a
+// candidate (a pair with 100 samples and 49 candidates: 300 us).
+template <int LV, int MW>
+__device__ __forceinline__ void open_lanes(Wave& v, const Mask<MW>& mk, int ix,
+                                           unsigned long long set) {
   const int lane = v.lane, h = v.h;
   int n = 0;
   while (set & (set - 1)) {   // the last entry has no later one
@@ -732,8 +773,14 @@ __device__ __forceinline__ void open_lanes(Wave& v, uint64_t mk, int ix, unsigne
       v.inc = max(v.inc, load_inc(v));
       refresh_need(v);
     }
-    const uint64_t mi = readlane64(mk, i);
-    const int ci = __popcll(mi);
+    Mask<MW> mj;
+    int ci = 0;
+#pragma unroll
+    for (int k = 0; k < MW; ++k) {
+      const uint64_t mi = readlane64(mk.w[k], i);
+      ci += __popcll(mi);
+      mj.w[k] = mi & mk.w[k];
+    }
     if (lane == 0) v.s.pre[LV + 2] = (uint16_t)__builtin_amdgcn_readlane(ix, i);
     if (v.own) {
       wave_lds_sync();
@@ -744,8 +791,7 @@ __device__ __forceinline__ void open_lanes(Wave& v, uint64_t mk, int ix, unsigne
       continue;
     }
     const bool in = __builtin_amdgcn_inverse_ballot_w64(set);
-    const uint64_t mj = mi & mk;
-    const int tp = in ? popc64(mj) : 0;
+    const int tp = in ? mask_count(mj) : 0;
     const bool hit = in && tp >= v.need;
     v.lmax = max(v.lmax, hit ? 0 : tp);
     const unsigned long long hm = __ballot(hit);
@@ -756,9 +802,16 @@ __device__ __forceinline__ void open_lanes(Wave& v, uint64_t mk, int ix, unsigne
       if (score_leaves(v, h - 1, hit, ix, tp)) v.tie_s = v.bs;
       refresh_need(v);
     } else {
-      if constexpr (LV + 4 < kMaxH) open_lanes<LV + 1>(v, mj, ix, hm);
+      if constexpr (LV + 4 < kMaxH) open_lanes<LV + 1, MW>(v, mj, ix, hm);
     }
   }
+}
+
+template <int MW>
+__device__ __forceinline__ void open_few(Wave& v, uint64_t y2, int n) {
+  const int ix = v.lane < n ? (int)v.s.idx[v.lane] : 0;
+  const Mask<MW> mk = sample_mask<MW>(v, y2, ix, v.lane < n);
+  open_lanes<0, MW>(v, mk, ix, n < 64 ? (1ull << n) - 1ull : ~0ull);
 }
 
 // Opens the pair (a, b): every leaf below it that can beat (or tie with a
@@ -790,32 +843,23 @@ __device__ __forceinline__ int open_pair(Wave& v, int a, int b, uint64_t* bits) 
   }
   if (lane < v.w64) v.s.y[lane] = y2;
   wave_lds_sync();
-  if (m <= 64 || (v.h == 3 && !by_rows)) list_samples(y2, v.s.smp, lane);
+  if (m <= 64 || !by_rows) list_samples(y2, v.s.smp, lane);
   if (v.h == 3) {
     if (by_rows) leaves_by_rows(v, v.s.y, 2, b + 1, nullptr);
     else PDFS_BY_SLICES(m, (leaves_by_slices<NB>(v, m, 2, b + 1, nullptr)));
   } else {
+    // more than 64 samples: a list only where one candidate per lane holds it
     int n = 0;
     bool listed = false;
-    if (m <= 64) {
-      const int cap = v.h <= 5 ? 256 : 128;
+    if (m <= kListSamples) {
+      const int cap = m > 64 ? kWave : (v.h <= 5 ? 256 : 128);
       if (by_rows) listed = list_by_rows(v, v.s.y, b + 1, cap, n);
-      else if (m < 4) listed = list_by_slices<2>(v, m, b + 1, cap, n);
-      else if (m < 16) listed = list_by_slices<4>(v, m, b + 1, cap, n);
-      else listed = list_by_slices<7>(v, m, b + 1, cap, n);
+      else PDFS_BY_SLICES(m, listed = list_by_slices<NB>(v, m, b + 1, cap, n));
     }
     if (listed && n <= kWave) {
-      const int ix = lane < n ? (int)v.s.idx[lane] : 0;
-      uint64_t mk = 0;
-      if (lane < n) {
-        const uint64_t* row = v.T + (size_t)ix * v.w64;
-#pragma unroll 4
-        for (int j = 0; j < m; ++j) {
-          const int sid = v.s.smp[j];
-          mk |= ((row[sid >> 6] >> (sid & 63)) & 1ull) << j;
-        }
-      }
-      open_lanes<0>(v, mk, ix, n < 64 ? (1ull << n) - 1ull : ~0ull);
+      if (m <= 64) open_few<1>(v, y2, n);
+      else if (m <= 128) open_few<2>(v, y2, n);
+      else open_few<4>(v, y2, n);
     } else if (listed) {
       // the candidates' samples as masks over the pair's
       for (int i0 = 0; i0 < n; i0 += kWave) {
