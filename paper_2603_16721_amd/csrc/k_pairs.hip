@@ -120,6 +120,7 @@ __device__ __forceinline__ void pairs_body(const Problem& P, const Work& w) {
   const int wr = wave >> 1, wc = wave & 1;
   const int T = (nA + kBT - 1) / kBT;
   const long long ntiles = (long long)T * (T + 1) / 2;
+  if ((long long)blockIdx.x >= ntiles) return;   // the finish reads pair_blocks() rows
   const int kpad = unpacked_row_bytes(w.w64);
   const int knpad = unpacked_row_bytes(P.wn);
   const int amax1 = st->amax[1], amax2 = st->amax[2];

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kSortTile) void k_sort_tile_ranks(const uint32_t* _
 
 // One block: tile_hist[k][t] <- first position of the genes of tile t with
 // key k (exclusive scan; the table is laid out in that order, so a thread's
-// stretch is contiguous: 31 us against 200 us across it at G = 20000).
+// stretch is contiguous: 59 us against 200 us across it at G = 20000).
 __global__ __launch_bounds__(1024) void k_sort_scan(uint32_t* __restrict__ tile_hist, size_t n) {
   __shared__ uint32_t part[1024];
   const int tid = threadIdx.x;
@@ -228,10 +228,6 @@ __device__ __forceinline__ void round_begin_body(const Problem& P, const Work& w
   }
 }
 
-__global__ void k_round_begin(Problem P, Work w) {
-  round_begin_body(P, w);
-}
-
 __global__ void k_round_begin_m(const BatchDesc* __restrict__ bd) {
   round_begin_body(bd[blockIdx.y].P, bd[blockIdx.y].w);
 }
@@ -246,10 +242,6 @@ __device__ __forceinline__ void active_flags_body(const Problem& P, const Work& 
   for (int k = 0; k < P.wt; ++k) acc |= row[k] & w.U[k];
   // 1: the gene meets U; 2: it does not, but exhaustive mode walks it anyway
   w.flags[g] = acc != 0 ? 1 : (P.mode == kPruneNone ? 2 : 0);
-}
-
-__global__ void k_active_flags(Problem P, Work w) {
-  active_flags_body(P, w);
 }
 
 __global__ void k_active_flags_m(const BatchDesc* __restrict__ bd) {
@@ -328,10 +320,6 @@ __device__ __forceinline__ void active_scan_body(const Problem& P, const Work& w
   }
 }
 
-__global__ __launch_bounds__(1024) void k_active_scan(Problem P, Work w) {
-  active_scan_body(P, w);
-}
-
 __global__ __launch_bounds__(1024) void k_active_scan_m(const BatchDesc* __restrict__ bd) {
   active_scan_body(bd[blockIdx.y].P, bd[blockIdx.y].w);
 }
@@ -376,13 +364,201 @@ __device__ __forceinline__ void gather_active_body(const Problem& P, const Work&
   }
 }
 
-__global__ __launch_bounds__(256) void k_gather_active(Problem P, Work w, int unpack_t,
-                                                       int unpack_n) {
-  gather_active_body(P, w, unpack_t, unpack_n);
-}
-
 __global__ __launch_bounds__(256) void k_gather_active_m(const BatchDesc* __restrict__ bd, int unpack_t, int unpack_n) {
   gather_active_body(bd[blockIdx.y].P, bd[blockIdx.y].w, unpack_t, unpack_n);
+}
+
+// Whole-run state: nothing done yet, totals cleared, the covered count of the
+// starting mask.
+__device__ __forceinline__ void run_begin_body(const Problem& P, const Work& w, int max_rounds) {
+  RoundState* st = w.st;
+  const int lane = threadIdx.x;
+  int c = 0;
+  for (int k = lane; k < P.wt; k += 64) c += __popcll(w.U[k]);
+  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+  if (lane == 0) {
+    st->done = (P.n_tumor - c) >= w.target || c == 0;
+    st->rounds = 0;
+    st->executed = 0;
+    st->max_rounds = max_rounds;
+    st->covered = P.n_tumor - c;
+    st->n_unc = c;
+    st->tx_vis3 = st->tx_vis4 = st->tx_leaves = st->tx_fp_leaves = st->tx_pair_macs = 0;
+    st->tx_vis_words3 = st->tx_vis_words4 = 0;
+    // nothing of an earlier run (a failed one included) carries over
+    st->overflow = 0;
+    st->found = 0;
+    st->n_tri = 0;
+  }
+  for (int l = lane; l <= kMaxH; l += 64) {
+    st->tot.visited[l] = 0;
+    st->tot.nonempty[l] = 0;
+    st->tot.bound_pruned[l] = 0;
+  }
+}
+
+// ------------------------------------------------------------- round front
+// The start of a round of one cohort in two launches (k_round_begin,
+// k_active_flags, k_active_scan and k_gather_active do it in four, with a
+// one-block scan between: 42 us against 30 us at G = 20000).  The genes
+// that meet U come as one bit each, so that every block of the second launch
+// can count the active genes before its own by itself.
+//
+// run_rounds >= 0: the run starts here too (its round cap; 0 = none), and with
+// `full` its mask is every sample.
+__global__ __launch_bounds__(256) void k_front_flags(Problem P, Work w, int run_rounds, int full) {
+  RoundState* st = w.st;
+  if (run_rounds < 0 && st->done) return;   // rounds queued past the stop are no-ops
+  const int g = blockIdx.x * 256 + threadIdx.x;
+  bool meets = false;
+  if (g < P.G) {
+    const uint64_t* row = w.Ts + (size_t)g * P.wt;
+    uint64_t acc = 0;
+    if (full) {
+#pragma unroll 4
+      for (int k = 0; k < P.wt; ++k) acc |= row[k];
+    } else {
+#pragma unroll 4
+      for (int k = 0; k < P.wt; ++k) acc |= row[k] & w.U[k];
+    }
+    meets = acc != 0;
+  }
+  const unsigned long long word = __ballot(meets);
+  if ((threadIdx.x & 63) == 0 && g < P.G) reinterpret_cast<uint64_t*>(w.flags)[g >> 6] = word;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    if (full) {
+      for (int k = threadIdx.x; k < P.wt; k += 64) {
+        const int lo = 64 * k;
+        w.U[k] = P.n_tumor - lo >= 64 ? ~0ull : (1ull << (P.n_tumor - lo)) - 1ull;
+      }
+      __threadfence_block();
+    }
+    if (run_rounds >= 0) {
+      run_begin_body(P, w, run_rounds);
+      __threadfence_block();
+    }
+    round_begin_body(P, w);
+  }
+}
+
+// Genes of word wd that a round walks: those that meet U, or all of them in
+// exhaustive mode.
+__device__ __forceinline__ uint64_t active_word(const Problem& P, uint64_t meets, int wd) {
+  if (P.mode != kPruneNone) return meets;
+  const int left = P.G - 64 * wd;
+  return left >= 64 ? ~0ull : (1ull << left) - 1ull;
+}
+
+// Sum of the set bits' positions.
+__device__ __forceinline__ int bit_sum(uint64_t x) {
+  return __popcll(x & 0xaaaaaaaaaaaaaaaaull) + 2 * __popcll(x & 0xccccccccccccccccull) +
+         4 * __popcll(x & 0xf0f0f0f0f0f0f0f0ull) + 8 * __popcll(x & 0xff00ff00ff00ff00ull) +
+         16 * __popcll(x & 0xffff0000ffff0000ull) + 32 * __popcll(x & 0xffffffff00000000ull);
+}
+
+// Block b < n_rows takes genes 16 b .. 16 b + 15: their places in the active
+// list and their rows (as k_gather_active).  The last block makes the round's
+// counts of depths 1 and 2 and the per-depth limits (as k_active_scan).
+__global__ __launch_bounds__(256) void k_front_rows(Problem P, Work w, int n_rows, int unpack_t,
+                                                    int unpack_n) {
+  RoundState* st = w.st;
+  if (st->done) return;
+  __shared__ int wsum[4];
+  __shared__ unsigned long long vsum[4];
+  __shared__ int nsum[4];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint64_t* bits = reinterpret_cast<const uint64_t*>(w.flags);
+  const int words = (P.G + 63) >> 6;
+  const int h = P.h;
+  const bool tally = (int)blockIdx.x == n_rows;
+  const int upto = tally ? words : (int)(blockIdx.x >> 2);   // words before this block's
+  int c = 0, ne1 = 0;
+  unsigned long long vis2 = 0;
+  for (int k = tid; k < upto; k += 256) {
+    const uint64_t meets = bits[k];
+    const uint64_t a = active_word(P, meets, k);
+    c += __popcll(a);
+    if (tally) {
+      const int last = P.G - h - 64 * k;   // genes up to G - h
+      const uint64_t in = last >= 63 ? ~0ull : (last < 0 ? 0ull : (2ull << last) - 1ull);
+      ne1 += __popcll(meets & in);
+      const uint64_t x = a & in;
+      if (h >= 2)
+        vis2 += (unsigned long long)__popcll(x) * (unsigned long long)(P.G - h + 1 - 64 * k) -
+                (unsigned long long)bit_sum(x);
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    c += __shfl_xor(c, o, 64);
+    if (tally) {
+      ne1 += __shfl_xor(ne1, o, 64);
+      vis2 += __shfl_xor(vis2, o, 64);
+    }
+  }
+  if (lane == 0) {
+    wsum[wid] = c;
+    nsum[wid] = ne1;
+    vsum[wid] = vis2;
+  }
+  __syncthreads();
+  const int base = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  if (tally) {
+    if (tid == 0) {
+      st->nA = base;
+      st->cnt.visited[1] = (unsigned long long)(P.G - h + 1);
+      st->cnt.nonempty[1] = (unsigned long long)(nsum[0] + nsum[1] + nsum[2] + nsum[3]);
+      if (h >= 2) st->cnt.visited[2] = vsum[0] + vsum[1] + vsum[2] + vsum[3];
+    }
+    // amax[l] = number of active genes with sorted index <= G-h+l-1
+    if (tid >= 1 && tid <= h) {
+      int above = 0;
+      for (int g = max(P.G - h + tid, 0); g < P.G; ++g)
+        above += (int)((active_word(P, bits[g >> 6], g >> 6) >> (g & 63)) & 1ull);
+      st->amax[tid] = base - above;
+    }
+    return;
+  }
+  const int wd = (int)(blockIdx.x >> 2), lo = 16 * (int)(blockIdx.x & 3);
+  const uint64_t act = active_word(P, bits[wd], wd);
+  const int n_unc = st->n_unc;
+  const bool all = n_unc == P.n_tumor;   // the columns are the samples
+  const int W32 = 2 * w.w64;
+  const int kpad = unpacked_row_bytes(w.w64);
+  const int knpad = unpacked_row_bytes(P.wn);
+  const uint32_t* Ns32 = reinterpret_cast<const uint32_t*>(w.Ns);
+  for (int j = lo + wid; j < lo + 16; j += 4) {
+    if (!((act >> j) & 1ull)) continue;
+    const int g = 64 * wd + j;
+    const int a = base + __popcll(act & ((1ull << j) - 1ull));
+    const uint64_t* row = w.Ts + (size_t)g * P.wt;
+    if (lane == 0) w.act[a] = g;
+    for (int k0 = 0; k0 < w.w64; ++k0) {
+      const int k = 64 * k0 + lane;
+      unsigned long long word;
+      if (all) {
+        word = k0 < P.wt ? row[k0] : 0ull;
+      } else {
+        int bit = 0;
+        if (k < n_unc) {
+          const int s = w.cols[k];
+          bit = (int)((row[s >> 6] >> (s & 63)) & 1ull);
+        }
+        word = __ballot(bit);
+      }
+      if (lane < 2) w.TA[(size_t)a * W32 + 2 * k0 + lane] = (uint32_t)(word >> (32 * lane));
+      if (unpack_t) w.A8[(size_t)a * kpad + k] = (int8_t)((word >> lane) & 1ull);
+    }
+    if (unpack_t)
+      for (int k = 64 * w.w64 + lane; k < kpad; k += 64) w.A8[(size_t)a * kpad + k] = 0;
+    if (lane < kMaxWN32)
+      w.NA[(size_t)a * kMaxWN32 + lane] = lane < 2 * P.wn ? Ns32[(size_t)g * 2 * P.wn + lane] : 0u;
+    if (unpack_n) {
+      const uint64_t* nrow = w.Ns + (size_t)g * P.wn;
+      for (int k = lane; k < knpad; k += 64)
+        w.N8[(size_t)a * knpad + k] =
+            k < 64 * P.wn ? (int8_t)((nrow[k >> 6] >> (k & 63)) & 1ull) : (int8_t)0;
+    }
+  }
 }
 
 // ------------------------------------------------------------- h = 1
@@ -434,6 +610,10 @@ __device__ __forceinline__ void finish_round_body(const Problem& P, const Work& 
   }
   __shared__ Slot red[16];
   __shared__ int s_found;
+  // blocks of the pair kernel that had a tile (the others write nothing)
+  const int rows0 = P.h == 1 ? kSlotsPerPhase
+                             : pair_blocks(w.st->nA, w.slot_log ? kPersistBlocks / 4
+                                                                : kPersistBlocks);
   __shared__ Slot s_best;
   __shared__ int32_t s_sidx[kMaxH];
   __shared__ int32_t s_gene[kMaxH];
@@ -459,7 +639,8 @@ __device__ __forceinline__ void finish_round_body(const Problem& P, const Work& 
       const unsigned long long* base = w.tallies + (size_t)ph * kPersistBlocks * kTallyN + tid;
       unsigned long long part[kIter];
 #pragma unroll
-      for (int i = 0; i < kIter; ++i) part[i] = base[(size_t)i * 1024];   // all loads in flight
+      for (int i = 0; i < kIter; ++i)   // all loads in flight
+        part[i] = ph > 0 || i * 1024 + tid < rows0 * kTallyN ? base[(size_t)i * 1024] : 0ull;
 #pragma unroll
       for (int i = 0; i < kIter; ++i) v += part[i];
     }
@@ -497,7 +678,7 @@ __device__ __forceinline__ void finish_round_body(const Problem& P, const Work& 
     // leaves the log of the waves that worked on this instance
     const Slot* src = w.slot_log ? w.slot_log + (size_t)ph * kLogCap
                                  : w.slots + (size_t)ph * kSlotsPerPhase;
-    const int n = w.slot_log ? min((int)st->nlog[ph], kLogCap) : kSlotsPerPhase;
+    const int n = w.slot_log ? min((int)st->nlog[ph], kLogCap) : (ph > 0 ? kSlotsPerPhase : rows0);
     for (int i = tid; i < n; i += 1024) {
       Slot c = src[i];
       take_if(b, c, slot_wins(c, b, h));
@@ -605,35 +786,6 @@ __global__ __launch_bounds__(1024) void k_finish_round_m(const BatchDesc* __rest
   finish_round_body(bd[blockIdx.y].P, bd[blockIdx.y].w, phase_mask, tally_mask);
 }
 
-// Whole-run state: nothing done yet, totals cleared, the covered count of the
-// starting mask.
-__device__ __forceinline__ void run_begin_body(const Problem& P, const Work& w, int max_rounds) {
-  RoundState* st = w.st;
-  const int lane = threadIdx.x;
-  int c = 0;
-  for (int k = lane; k < P.wt; k += 64) c += __popcll(w.U[k]);
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-  if (lane == 0) {
-    st->done = (P.n_tumor - c) >= w.target || c == 0;
-    st->rounds = 0;
-    st->executed = 0;
-    st->max_rounds = max_rounds;
-    st->covered = P.n_tumor - c;
-    st->n_unc = c;
-    st->tx_vis3 = st->tx_vis4 = st->tx_leaves = st->tx_fp_leaves = st->tx_pair_macs = 0;
-    st->tx_vis_words3 = st->tx_vis_words4 = 0;
-    // nothing of an earlier run (a failed one included) carries over
-    st->overflow = 0;
-    st->found = 0;
-    st->n_tri = 0;
-  }
-  for (int l = lane; l <= kMaxH; l += 64) {
-    st->tot.visited[l] = 0;
-    st->tot.nonempty[l] = 0;
-    st->tot.bound_pruned[l] = 0;
-  }
-}
-
 // After the host grew a list the stopped round overflowed: the run goes on
 // from the same state (that round was not committed).
 __global__ void k_run_resume(Work w) {
@@ -641,10 +793,6 @@ __global__ void k_run_resume(Work w) {
     w.st->overflow = 0;
     w.st->done = 0;
   }
-}
-
-__global__ void k_run_begin(Problem P, Work w, int max_rounds) {
-  run_begin_body(P, w, max_rounds);
 }
 
 __global__ void k_run_begin_m(const BatchDesc* __restrict__ bd, int max_rounds) {
@@ -709,11 +857,6 @@ hipError_t launch_run_resume(const Work& w, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_run_begin(const Problem& P, const Work& w, int max_rounds, hipStream_t s) {
-  k_run_begin<<<1, 64, 0, s>>>(P, w, max_rounds);
-  return hipGetLastError();
-}
-
 hipError_t launch_zero_u32(void* p, size_t n32, hipStream_t s) {
   if (n32 == 0) return hipSuccess;
   const size_t blocks = (n32 + 255) / 256;
@@ -727,22 +870,12 @@ hipError_t launch_fill_u(uint64_t* U, int wt, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_round_begin(const Problem& P, const Work& w, hipStream_t s) {
-  k_round_begin<<<1, 64, 0, s>>>(P, w);
-  return hipGetLastError();
-}
-
-hipError_t launch_active(const Problem& P, const Work& w, hipStream_t s) {
-  k_active_flags<<<(P.G + 255) / 256, 256, 0, s>>>(P, w);
-  k_active_scan<<<1, 1024, 0, s>>>(P, w);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_active(const Problem& P, const Work& w, bool unpack_tumor,
-                                bool unpack_normal, hipStream_t s) {
-  int blocks = (P.G + 3) / 4;
-  if (blocks > 4096) blocks = 4096;
-  k_gather_active<<<blocks, 256, 0, s>>>(P, w, unpack_tumor ? 1 : 0, unpack_normal ? 1 : 0);
+hipError_t launch_front(const Problem& P, const Work& w, int run_rounds, bool full, bool rows,
+                        bool unpack_tumor, bool unpack_normal, hipStream_t s) {
+  k_front_flags<<<(P.G + 255) / 256, 256, 0, s>>>(P, w, run_rounds, full ? 1 : 0);
+  const int n_rows = rows ? (P.G + 63) / 64 * 4 : 0;
+  k_front_rows<<<n_rows + 1, 256, 0, s>>>(P, w, n_rows, unpack_tumor ? 1 : 0,
+                                          unpack_normal ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -369,14 +369,23 @@ Problem make_problem(const pdfs_ctx* c, int h, uint32_t p, uint32_t q) {
 // already done).  ev = the round's five timing events (used when timing);
 // two_phase: h = 4 under empty-prefix pruning lists long-stream prefixes for
 // the tile kernel (the lists must be in w).
+int32_t enqueue_front(pdfs_ctx* c, const Problem& P, const Work& w, int run_rounds, bool rows,
+                      bool unpack_tumor, bool unpack_normal) {
+  const bool full = run_rounds >= 0 && c->fill_u;
+  CK(c, launch_front(P, w, run_rounds, full, rows, unpack_tumor, unpack_normal, c->stream));
+  if (run_rounds >= 0) c->fill_u = false;
+  return PDFS_OK;
+}
+
 int32_t enqueue_round(pdfs_ctx* c, const Problem& P, const Work& w, hipEvent_t* ev,
-                      bool two_phase) {
+                      bool two_phase, int run_rounds) {
   const int h = P.h;
   hipStream_t s = c->stream;
   const bool tk = c->time_kernels;
-  CK(c, launch_round_begin(P, w, s));
-  CK(c, launch_active(P, w, s));
-  CK(c, launch_gather_active(P, w, h >= 2, h == 2, s));
+  {
+    const int32_t rc = enqueue_front(c, P, w, run_rounds, true, h >= 2, h == 2);
+    if (rc != PDFS_OK) return rc;
+  }
   if (h == 1) {
     CK(c, launch_h1(P, w, s));
   } else {
@@ -475,6 +484,11 @@ static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int 
     return PDFS_OK;
   }
   if (c->use_graphs && !c->time_kernels) {
+    if (!r.begun) {   // outside the captured round
+      const int32_t rc = enqueue_front(c, P, w, r.max_rounds, false, false, false);
+      if (rc != PDFS_OK) return rc;
+      r.begun = true;
+    }
     const auto key = std::make_tuple(P.h, w.w64, r.p, r.q, r.target, c->prune_mode,
                                      c->chunk_items, c->seed_pairs_n, c->two_phase,
                                      c->long_stream);
@@ -483,7 +497,7 @@ static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int 
       hipGraph_t g = nullptr;
       hipGraphExec_t e = nullptr;
       CK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      const int32_t rc = enqueue_round(c, P, w, c->ev[slot][0], c->two_phase);
+      const int32_t rc = enqueue_round(c, P, w, c->ev[slot][0], c->two_phase, -1);
       hipGraph_t g2 = nullptr;
       const hipError_t ec = hipStreamEndCapture(c->stream, &g2);
       if (rc != PDFS_OK) {
@@ -500,8 +514,10 @@ static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int 
     return PDFS_OK;
   }
   for (int k = 0; k < chunk; ++k) {
-    const int32_t rc = enqueue_round(c, P, w, c->ev[slot][k], c->two_phase);
+    const int32_t rc = enqueue_round(c, P, w, c->ev[slot][k], c->two_phase,
+                                     r.begun ? -1 : r.max_rounds);
     if (rc != PDFS_OK) return rc;
+    r.begun = true;
   }
   return PDFS_OK;
 }
@@ -511,9 +527,12 @@ static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int 
 static int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, int slot) {
   hipStream_t s = c->stream;
   const bool tk = c->time_kernels;
-  CK(c, launch_round_begin(P, w, s));
-  CK(c, launch_active(P, w, s));
-  CK(c, launch_gather_active(P, w, true, false, s));
+  {
+    const int32_t rc = enqueue_front(c, P, w, c->run.begun ? -1 : c->run.max_rounds, true, true,
+                                     false);
+    if (rc != PDFS_OK) return rc;
+    c->run.begun = true;
+  }
   if (tk) CK(c, hipEventRecord(c->ev[slot][0][0], s));
   CK(c, launch_pair_list(P, w, s));
   if (tk) CK(c, hipEventRecord(c->ev[slot][0][1], s));
@@ -541,10 +560,10 @@ static int32_t size_triples(pdfs_ctx* c, int h, int n_unc) {
     const Problem P = make_problem(c, 4, 1, 1);
     Work w = make_work(c, w64, c->n_tumor + 1);
     w.tri_cap = 0;
-    CK(c, launch_run_begin(P, w, 1, s));
-    CK(c, launch_round_begin(P, w, s));
-    CK(c, launch_active(P, w, s));
-    CK(c, launch_gather_active(P, w, true, false, s));
+    {
+      const int32_t rc = enqueue_front(c, P, w, 1, true, true, false);
+      if (rc != PDFS_OK) return rc;
+    }
     CK(c, launch_pairs(P, w, s));
     CK(c, launch_use_all_pairs(w, s));
     CK(c, launch_make_items(P, w, false, s));
@@ -628,9 +647,6 @@ int32_t run_start(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int ma
   r.h = h; r.p = p; r.q = q; r.target = target; r.max_rounds = max_rounds; r.n_unc = n_unc;
   r.lazy = lazy; r.w64 = w64;
   if (lazy) r.chunk = 8;   // rounds of 10-30 us, no-ops past the end of 2 us
-  const Problem P = make_problem(c, h, p, q);
-  Work w0 = make_work(c, 1, target);
-  CK(c, launch_run_begin(P, w0, max_rounds, c->stream));
   r.active = true;
   r.t_prev = std::chrono::steady_clock::now();
   return PDFS_OK;
@@ -663,6 +679,9 @@ int32_t run_enqueue(pdfs_ctx* c) {
     if (rc != PDFS_OK) return rc;
     CK(c, hipMemcpyAsync(&c->h_slots[slot], c->st, sizeof(RoundState), hipMemcpyDeviceToHost,
                          c->stream));
+    if (r.max_rounds == 1)   // the one record comes along, without another wait
+      CK(c, hipMemcpyAsync(c->h_rec, c->recs, sizeof(RoundRecord), hipMemcpyDeviceToHost,
+                           c->stream));
     CK(c, hipEventRecord(c->chunk_done[slot], c->stream));
     c->chunk_rounds[slot] = n;
     c->next_slot = (slot + 1) % kDepth;
@@ -903,11 +922,12 @@ int32_t set_uncovered(pdfs_ctx* c, const uint64_t* mask) {
   if (mask) {
     if (!mask_pad_ok(mask, c->n_tumor, c->wt))
       return fail(c, PDFS_ERR_INVALID_ARG, "uncovered mask has bits past n_tumor");
+    c->fill_u = false;
     CK(c, hipMemcpyAsync(c->U, mask, sizeof(uint64_t) * c->wt, hipMemcpyHostToDevice,
                          c->stream));
     return popcount_mask(mask, c->wt);
   }
-  CK(c, launch_fill_u(c->U, c->wt, c->n_tumor, c->stream));
+  c->fill_u = true;
   return c->n_tumor;
 }
 
@@ -926,9 +946,13 @@ int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds,
   const int n = *rounds < cap ? *rounds : cap;
   if (n > 0 && out) {
     std::vector<RoundRecord> recs((size_t)n);
-    CK(c, hipMemcpyAsync(recs.data(), c->recs, sizeof(RoundRecord) * recs.size(),
-                         hipMemcpyDeviceToHost, over));
-    CK(c, hipStreamSynchronize(over));
+    if (c->run.max_rounds == 1) {
+      recs[0] = *c->h_rec;
+    } else {
+      CK(c, hipMemcpyAsync(recs.data(), c->recs, sizeof(RoundRecord) * recs.size(),
+                           hipMemcpyDeviceToHost, over));
+      CK(c, hipStreamSynchronize(over));
+    }
     for (int i = 0; i < n; ++i) {
       if (c->run.lazy)   // recorded by sorted index only
         for (int k = 0; k < c->run.h; ++k) recs[i].genes[k] = c->h_perm[recs[i].sorted_idx[k]];
@@ -1170,11 +1194,9 @@ int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out
     Problem P;
     P.G = G; P.n_tumor = m->n_tumor; P.n_normal = m->n_normal; P.wt = wt; P.wn = c->wn;
     P.h = 1; P.p = 1; P.q = 1; P.mode = mode; P.n_cu = c->n_cu; P.tn_literal = 0;
-    Work w = make_work(c, 1, 0);
+    Work w = make_work(c, 1, m->n_tumor + 1);   // (a target in reach would end it here)
     CKC(launch_total_bits(c->Ts, (size_t)G * wt, c->st, s));
-    CKC(launch_fill_u(c->U, wt, m->n_tumor, s));
-    CKC(launch_round_begin(P, w, s));
-    CKC(launch_active(P, w, s));
+    CKC(launch_front(P, w, 0, true, false, false, false, s));
     CKC(hipMemcpyAsync(c->h_st, c->st, sizeof(RoundState), hipMemcpyDeviceToHost, s));
     CKC(hipStreamSynchronize(s));
     c->nA_max = c->h_st->nA;

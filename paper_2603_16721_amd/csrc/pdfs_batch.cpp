@@ -541,6 +541,8 @@ int32_t run_multi(pdfs_batch* b, const int32_t* h, uint32_t p, uint32_t q, const
     c->stream = b->ms;
     const int32_t u = set_uncovered(c, nullptr);
     if (u < 0) return batch_fail(b, u, i);
+    BCK(launch_fill_u(c->U, c->wt, c->n_tumor, b->ms));
+    c->fill_u = false;
     rc = prepare_run(c, h[i], u);
     if (rc != PDFS_OK) return batch_fail(b, rc, i);
     m.tiles = m.tiles || c->two_phase;

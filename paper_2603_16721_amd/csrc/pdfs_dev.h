@@ -55,6 +55,13 @@ enum PruneMode { kPruneNone = 0, kPruneEmpty = 1, kPruneBound = 2 };
 // RoundState::overflow: the pair list was too small for the round's pairs
 constexpr int32_t kOverflowPairs = 1 | 8;
 
+// Blocks of the pair kernel, out of `grid`, that get a 128 x 128 tile of nA
+// active genes.
+__host__ __device__ constexpr int pair_blocks(int nA, int grid) {
+  const long long T = (nA + 127) / 128, n = T * (T + 1) / 2;
+  return n < grid ? (int)n : grid;
+}
+
 // Bytes per unpacked (one byte per sample) row for the MFMA pair table: the
 // row's 64-bit words times 64, rounded up to the kernel's 128-byte K chunk.
 __host__ __device__ constexpr int unpacked_row_bytes(int w64) { return 128 * ((w64 + 1) / 2); }
@@ -312,10 +319,11 @@ hipError_t launch_total_bits(const uint64_t* Ts, size_t words, RoundState* st, h
 hipError_t launch_check_pad(const uint64_t* T, int64_t ts, int G, int n, int* bad, hipStream_t s);
 
 // per round
-hipError_t launch_round_begin(const Problem& P, const Work& w, hipStream_t s);
-hipError_t launch_active(const Problem& P, const Work& w, hipStream_t s);
-hipError_t launch_gather_active(const Problem& P, const Work& w, bool unpack_tumor,
-                                bool unpack_normal, hipStream_t s);
+// The round's state, active genes and (rows) re-packed rows.  run_rounds >= 0:
+// a run starts here, with that round cap (0: none); full: from every sample,
+// whatever U holds (it is set).
+hipError_t launch_front(const Problem& P, const Work& w, int run_rounds, bool full, bool rows,
+                        bool unpack_tumor, bool unpack_normal, hipStream_t s);
 hipError_t launch_h1(const Problem& P, const Work& w, hipStream_t s);
 hipError_t launch_pairs(const Problem& P, const Work& w, hipStream_t s);
 // the pair list at any h >= 2 (launch_pairs scores the pairs at h = 2)
@@ -354,7 +362,6 @@ hipError_t launch_clear_slots(Slot* slots, int n, hipStream_t s);
 // n32 32-bit words at p set to zero by a fill kernel (no memset node)
 hipError_t launch_zero_u32(void* p, size_t n32, hipStream_t s);
 hipError_t launch_fill_u(uint64_t* U, int wt, int n, hipStream_t s);
-hipError_t launch_run_begin(const Problem& P, const Work& w, int max_rounds, hipStream_t s);
 hipError_t launch_run_resume(const Work& w, hipStream_t s);
 // 32-bit words of the h >= 5 walk's rings and frames for rows of up to
 // w64_max words on a device of n_cu compute units (the launched grids' size).

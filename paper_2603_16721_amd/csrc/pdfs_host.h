@@ -45,6 +45,7 @@ struct Run {
   int executed_before = 0;
   bool lazy = false;        // lazy rounds (k_lazy.hip)
   bool listed = false;      // lazy rounds: the run's pair lists are queued
+  bool begun = false;       // the run's first launch is queued
   int w64 = 1;              // lazy rounds: row width of the run
   int launches = 0;         // lazy rounds: launches queued since the lists
   int count_slot = -1;      // lazy rounds: the counters are queued, read with this slot
@@ -133,6 +134,7 @@ struct pdfs_ctx {
   std::map<std::tuple<int, int, uint32_t, uint32_t, int, int, int, int, bool, int>, hipGraphExec_t>
       graphs;
   size_t bytes = 0;                    // device bytes held (admission accounting)
+  bool fill_u = false;                 // the run's first launch sets U to every sample
   std::vector<void*> blocks;           // allocations that hold several of the buffers above
   bool async_alloc = false;            // stream-ordered allocation (batched / served)
   hipMemPool_t pool = nullptr;         // from this pool (the server's), or the device's
@@ -181,14 +183,20 @@ int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds,
 // whose state copies write the pinned slots) are through; does not wait.
 bool run_drained(pdfs_ctx* c);
 int32_t check_call(pdfs_ctx* c, int h, uint32_t p, uint32_t q);
-// Sets U from a host mask (NULL = all samples); returns |U| or -1.
+// Sets U from a host mask (NULL = all samples, left to the run's first launch:
+// pdfs_ctx::fill_u); returns |U| or -1.
 int32_t set_uncovered(pdfs_ctx* c, const uint64_t* mask);
 // Round workspace pointers and problem description of a context.
 Work make_work(pdfs_ctx* c, int w64, int target);
 Problem make_problem(const pdfs_ctx* c, int h, uint32_t p, uint32_t q);
 // Enqueues one round on c->stream with workspace w (see pdfs_api.cpp).
+// run_rounds >= 0: the round starts a run with that round cap.
 int32_t enqueue_round(pdfs_ctx* c, const Problem& P, const Work& w, hipEvent_t* ev,
-                      bool two_phase);
+                      bool two_phase, int run_rounds);
+// Starts a run (or one round) on the device: launch_front with the context's
+// pending mask.
+int32_t enqueue_front(pdfs_ctx* c, const Problem& P, const Work& w, int run_rounds, bool rows,
+                      bool unpack_tumor, bool unpack_normal);
 // Gets the static scratch array's device address on `device` once (the
 // allocation-free entry point's workspace); called by create_ctx with the
 // device current.

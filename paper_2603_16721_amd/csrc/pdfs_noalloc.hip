@@ -206,9 +206,8 @@ int32_t pdfs_best_combo_noalloc(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q,
   // what a round expects to start from zero; the rest is written before use
   NCK(launch_zero_u32(base + L.st, (L.zero_end - L.st) / 4, s));
   NCK(launch_clear_slots(w.slots, kSlotPhases * kSlotsPerPhase, s));
-  NCK(launch_run_begin(P, w, 1, s));
   const int slot = c->next_slot;
-  rc = enqueue_round(c, P, w, c->ev[slot][0], false);
+  rc = enqueue_round(c, P, w, c->ev[slot][0], false, 1);
   if (rc != PDFS_OK) return rc;
   RoundState* hs = &c->h_slots[slot];
   NCK(hipMemcpyAsync(hs, w.st, sizeof(RoundState), hipMemcpyDeviceToHost, s));
