@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_lazy_deal(Problem P, Work w, LazyWork L
       run += w.hist[v];
     }
   }
-  const int chunks = L.seg / kWave;
+  const int chunks = (L.seg + kWave - 1) / kWave;
   for (unsigned long long i0 = (unsigned long long)blockIdx.x * kDeal; i0 < np;
        i0 += (unsigned long long)gridDim.x * kDeal) {
     __syncthreads();
@@ -1191,7 +1191,7 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
                          : 0;
   const int n_chunk = (n_mine + kWave - 1) / kWave;
   unsigned long long* list = L.list + (size_t)wv * L.seg;
-  int32_t* cmax = L.cmax + (size_t)wv * (L.seg / kWave);
+  int32_t* cmax = L.cmax + (size_t)wv * ((L.seg + kWave - 1) / kWave);
   uint64_t* bits = L.bits + (size_t)wv * L.levels * L.gw;
 
   // No incumbent yet (a run's first round): a greedy leaf below the wave's

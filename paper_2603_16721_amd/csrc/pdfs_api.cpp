@@ -175,18 +175,6 @@ static int32_t alloc_pair_lists(pdfs_ctx* c, unsigned long long n) {
   return PDFS_OK;
 }
 
-// Waves of a lazy round for a pair list of n pairs: a share of 128 pairs at
-// least, at most one block per compute unit.
-static int lazy_waves(unsigned long long n) {
-  unsigned long long nw = (n + 127) / 128;
-  nw = (nw + 3) / 4 * 4;
-  return (int)(nw > (unsigned long long)kLazyWaves ? (unsigned long long)kLazyWaves : nw);
-}
-
-static int lazy_seg(unsigned long long n, int nw) {
-  return (int)((n + nw - 1) / nw + kWave - 1) / kWave * kWave;
-}
-
 // The lazy rounds' buffers for a run of depth h at row width w64.
 static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
   LazyWork& L = c->lz;
@@ -334,6 +322,18 @@ int32_t ensure_workspace(pdfs_ctx* c, int h, bool lazy) {
 }  // namespace
 
 namespace pdfs {
+
+// Waves of a lazy round for a pair list of n pairs: a share of 128 pairs at
+// least, at most one block per compute unit.
+int lazy_waves(unsigned long long n) {
+  unsigned long long nw = (n + 127) / 128;
+  nw = (nw + 3) / 4 * 4;
+  return (int)(nw > (unsigned long long)kLazyWaves ? (unsigned long long)kLazyWaves : nw);
+}
+
+int lazy_seg(unsigned long long n, int nw) {
+  return (int)((n + nw - 1) / nw + kWave - 1) / kWave * kWave;
+}
 
 Work make_work(pdfs_ctx* c, int w64, int target) {
   Work w;
@@ -522,23 +522,18 @@ static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int 
   return PDFS_OK;
 }
 
-// Start of a lazy run: the run's rows and pair table, made once, and the pairs
-// dealt to the round kernel's waves.
-static int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, int slot) {
+int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, const LazyWork& L,
+                      int run_rounds, hipEvent_t* ev) {
   hipStream_t s = c->stream;
   const bool tk = c->time_kernels;
-  {
-    const int32_t rc = enqueue_front(c, P, w, c->run.begun ? -1 : c->run.max_rounds, true, true,
-                                     false);
-    if (rc != PDFS_OK) return rc;
-    c->run.begun = true;
-  }
-  if (tk) CK(c, hipEventRecord(c->ev[slot][0][0], s));
+  const int32_t rc = enqueue_front(c, P, w, run_rounds, true, true, false);
+  if (rc != PDFS_OK) return rc;
+  if (tk) CK(c, hipEventRecord(ev[0], s));
   CK(c, launch_pair_list(P, w, s));
-  if (tk) CK(c, hipEventRecord(c->ev[slot][0][1], s));
-  CK(c, launch_lazy_begin(P, w, c->lz, s));
+  if (tk) CK(c, hipEventRecord(ev[1], s));
+  CK(c, launch_lazy_begin(P, w, L, s));
   CK(c, launch_pair_hist(w, s));
-  CK(c, launch_lazy_deal(P, w, c->lz, s));
+  CK(c, launch_lazy_deal(P, w, L, s));
   return PDFS_OK;
 }
 
@@ -669,8 +664,10 @@ int32_t run_enqueue(pdfs_ctx* c) {
     const Problem P = make_problem(c, r.h, r.p, r.q);
     const Work w = make_work(c, w64, r.target);
     if (r.lazy && !r.listed) {
-      const int32_t rc = enqueue_lists(c, P, w, slot);
+      const int32_t rc = enqueue_lists(c, P, w, c->lz, r.begun ? -1 : r.max_rounds,
+                                       c->ev[slot][0]);
       if (rc != PDFS_OK) return rc;
+      r.begun = true;
       r.listed = true;
       r.launches = 0;
       r.time_pairs = c->time_kernels;

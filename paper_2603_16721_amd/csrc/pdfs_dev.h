@@ -234,7 +234,7 @@ struct LazyWork {
   uint64_t* U2;               // [2][kMaxW64] uncovered masks, by launch as S
   uint64_t* Uc;               // [kMaxW64] the mask at the run's end
   unsigned long long* list;   // [nw][seg] pairs a | b << 16 | bound << 32
-  int32_t* cmax;              // [nw][seg / 64] a chunk's largest bound
+  int32_t* cmax;              // [nw][ceil(seg / 64)] a chunk's largest bound
   uint32_t* cursor;           // [kMaxCount + 1] pairs of a count dealt so far
   Slot* pool;                 // [nw] a wave's best known leaf
   Slot* wins;                 // [3][kLazyWaves / 4] leaves that may be a launch's answer
@@ -246,7 +246,7 @@ struct LazyWork {
   unsigned long long* shard;  // [2][kIncShards * kCursorStride] incumbents of a part of the blocks
   int32_t gw;                 // words of a row of B
   int32_t nw;                 // waves of the round kernel (a multiple of 4)
-  int32_t seg;                // entries of a wave's share (a multiple of 64)
+  int32_t seg;                // entries of a wave's share
   int32_t levels;             // bitmaps per wave
   int32_t wave_bytes;         // LDS per wave (set by the launcher)
 };

@@ -193,6 +193,14 @@ Problem make_problem(const pdfs_ctx* c, int h, uint32_t p, uint32_t q);
 // run_rounds >= 0: the round starts a run with that round cap.
 int32_t enqueue_round(pdfs_ctx* c, const Problem& P, const Work& w, hipEvent_t* ev,
                       bool two_phase, int run_rounds);
+// Start of a lazy run with the lists in w and L: the run's rows and pair table,
+// made once, and the pairs dealt to the round kernel's waves.  run_rounds as
+// for enqueue_round; ev[0..1] around the pair table (used when timing).
+int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, const LazyWork& L,
+                      int run_rounds, hipEvent_t* ev);
+// Waves of a lazy round for a pair list of n pairs, and pairs per wave's share.
+int lazy_waves(unsigned long long n);
+int lazy_seg(unsigned long long n, int nw);
 // Starts a run (or one round) on the device: launch_front with the context's
 // pending mask.
 int32_t enqueue_front(pdfs_ctx* c, const Problem& P, const Work& w, int run_rounds, bool rows,

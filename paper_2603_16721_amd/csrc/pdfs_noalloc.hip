@@ -17,10 +17,12 @@
 // counter rows) itself.  Calls that overlap on one device race.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "../../include/pdfs.h"
 #include "pdfs_dev.h"
@@ -47,16 +49,44 @@ hipError_t g_scratch_rc[kMaxDevices] = {};
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// The lazy round's small buffers, each on a 256-byte boundary.
+size_t lazy_small(LazyWork& W, unsigned char* at, int n_tumor) {
+  size_t o = 0;
+  auto put = [&](auto** p, size_t n) {
+    *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(at + o);
+    o = align256(o + n * sizeof(**p));
+  };
+  put(&W.Uc, kMaxW64);
+  put(&W.cursor, kMaxCount + 1);
+  put(&W.pool, kLazyWaves);
+  put(&W.wins, 3 * (kLazyWaves / 4));
+  put(&W.n_win, 3 * 64);
+  put(&W.inc, 2 * kCursorStride);
+  put(&W.S, 2);
+  put(&W.U2, 2 * kMaxW64);
+  put(&W.tcov, 64 * kMaxW64);
+  put(&W.uncs, (size_t)n_tumor + 2);
+  put(&W.shard, 2 * kIncShards * kCursorStride);
+  return o;
+}
+
+const size_t kLazyBytes = [] {
+  LazyWork W;
+  return lazy_small(W, reinterpret_cast<unsigned char*>((uintptr_t)256), 64 * kMaxW64);
+}();
+
 // Byte offsets of the round workspace inside the scratch array.
 struct Layout {
   size_t st, recs, slots, tallies, zero_end;   // [st, zero_end) is cleared per call
   size_t cols, act, flags, TA, NA, A8, N8, hist, cursors, seed, pairs, work, items;
+  size_t B, bits, list, cmax, lazy;   // lazy round (bound mode, h >= 3)
+  int nw = 0, seg = 0, gw = 0;
   size_t total;
   unsigned long long pair_cap = 0, item_cap = 0;
 };
 
 // Plans the workspace of one round at row width w64max.  The fixed part is
-// sized exactly; the pair list (and its bound-mode copy) and the item list
+// sized exactly; the pair list and its bound-mode shares or the item list
 // take what is left, up to the exact bound of nA(nA-1)/2 pairs.  Returns
 // false (with the bytes the fixed part needs) when it does not fit.
 bool plan(const pdfs_ctx* c, int h, Layout& L, size_t* need) {
@@ -70,9 +100,12 @@ bool plan(const pdfs_ctx* c, int h, Layout& L, size_t* need) {
   };
   L.st = take(sizeof(RoundState));
   L.recs = take(sizeof(RoundRecord));
-  L.tallies = take((size_t)kSlotPhases * kPersistBlocks * kTallyN * 8);
+  // (a lazy round has the pair table's counter rows only, and no slots)
+  const bool bound = c->prune_mode == PDFS_PRUNE_BOUND;
+  const bool lazy = h >= 3 && bound;
+  L.tallies = take((size_t)(lazy ? 1 : kSlotPhases) * kPersistBlocks * kTallyN * 8);
   L.zero_end = o;
-  L.slots = take((size_t)kSlotPhases * kSlotsPerPhase * sizeof(Slot));
+  L.slots = take(lazy ? 0 : (size_t)kSlotPhases * kSlotsPerPhase * sizeof(Slot));
   L.cols = take((size_t)c->n_tumor * 4);
   L.act = take((size_t)c->G * 4);
   L.flags = take((size_t)c->G);
@@ -83,25 +116,50 @@ bool plan(const pdfs_ctx* c, int h, Layout& L, size_t* need) {
   L.hist = take((size_t)(kMaxCount + 1) * 4);
   L.cursors = take((size_t)kSubQueues * kCursorStride * 8);
   L.seed = take((size_t)kSeedCap * 8);
+  size_t nw_max = 0;
+  if (lazy) {
+    // The transposed rows (8 w64 bytes a gene) and the general walk's bitmaps
+    // (nw / 8) lie over the unpacked rows (128 ceil(w64 / 2) a gene), which the
+    // pair table is done with: 1024 waves fit from w64 = 3 on, 768 always.
+    L.gw = (nA + 63) / 64 > 0 ? (nA + 63) / 64 : 1;
+    const size_t nb = align256((size_t)64 * c->w64_max * L.gw * 8);
+    const size_t per_wave = (size_t)lazy_levels(h) * L.gw * 8;
+    const size_t room = rows * (size_t)unpacked_row_bytes(c->w64_max);
+    nw_max = nb + kLazyWaves * per_wave <= room ? kLazyWaves : kLazyWaves / 4 * 3;
+    L.B = L.A8;
+    L.bits = L.B + nb;
+    if (nb + nw_max * per_wave > room) return false;   // (cannot happen, by the sizes above)
+    L.lazy = take(kLazyBytes);
+  }
   *need = o;
   if (o >= kScratchBytes) return false;
   L.pairs = L.work = L.items = o;
   if (h >= 3) {
-    // The rest holds the pair list (and its bound-mode work copy) and the
-    // item list: 8 (16) bytes per pair, plus two 16-byte items per 64-pair
-    // batch and 2048 spare items.
-    const bool bound = c->prune_mode == PDFS_PRUNE_BOUND;
-    const size_t fixed = (size_t)2048 * sizeof(Item) + 3 * 256;
+    // The rest holds the pair list and, for a lazy round, its waves' shares (8
+    // bytes a pair, and a bound per 64); otherwise the item list: two 16-byte
+    // items per 64-pair batch and 2048 spare items.
+    const size_t fixed = lazy ? 4 * 256 + (size_t)kLazyWaves * (8 + 4)   // the shares' round-up
+                              : (size_t)2048 * sizeof(Item) + 3 * 256;
     const size_t avail = kScratchBytes - o;
     if (avail <= fixed + 64 * 17) return false;
-    const double per_pair = (bound ? 16.0 : 8.0) + 2.0 * sizeof(Item) / kPairBatch;
+    const double per_pair = lazy ? 16.0 + 4.0 / kWave : 8.0 + 2.0 * sizeof(Item) / kPairBatch;
     unsigned long long cap = (unsigned long long)((double)(avail - fixed) / per_pair);
     const unsigned long long exact = (unsigned long long)nA * (nA > 0 ? nA - 1 : 0) / 2;
     if (cap > exact) cap = exact;
     if (cap < 64) cap = 64;
     L.pair_cap = cap;
     L.pairs = take(cap * 8);
-    L.work = bound ? take(cap * 8) : L.pairs;
+    if (lazy) {
+      L.nw = std::min(lazy_waves(cap), (int)nw_max);
+      L.seg = (int)((cap + L.nw - 1) / L.nw);
+      const size_t chunks = (size_t)L.nw * ((L.seg + kWave - 1) / kWave);
+      L.list = take((size_t)L.nw * L.seg * 8);
+      L.cmax = take(chunks * 4);
+      L.total = o;
+      *need = o;
+      return o <= kScratchBytes;
+    }
+    L.work = L.pairs;
     L.item_cap = 2 * ((cap + kPairBatch - 1) / kPairBatch) + 2048;
     L.items = take(L.item_cap * sizeof(Item));
   }
@@ -205,10 +263,34 @@ int32_t pdfs_best_combo_noalloc(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q,
   hipStream_t s = c->stream;
   // what a round expects to start from zero; the rest is written before use
   NCK(launch_zero_u32(base + L.st, (L.zero_end - L.st) / 4, s));
-  NCK(launch_clear_slots(w.slots, kSlotPhases * kSlotsPerPhase, s));
+  if (!(h >= 3 && c->prune_mode == PDFS_PRUNE_BOUND))
+    NCK(launch_clear_slots(w.slots, kSlotPhases * kSlotsPerPhase, s));
   const int slot = c->next_slot;
-  rc = enqueue_round(c, P, w, c->ev[slot][0], false, 1);
-  if (rc != PDFS_OK) return rc;
+  const bool lazy = h >= 3 && c->prune_mode == PDFS_PRUNE_BOUND;
+  if (lazy) {
+    // as the rounds of a bound-pruned run (14 launches 183 us, so 115 us
+    // at G = 3067)
+    LazyWork W = {};
+    lazy_small(W, base + L.lazy, c->n_tumor);
+    W.B = reinterpret_cast<uint64_t*>(base + L.B);
+    W.bits = reinterpret_cast<uint64_t*>(base + L.bits);
+    W.list = reinterpret_cast<unsigned long long*>(base + L.list);
+    W.cmax = reinterpret_cast<int32_t*>(base + L.cmax);
+    W.gw = L.gw;
+    W.nw = L.nw;
+    W.seg = L.seg;
+    W.levels = lazy_levels(h);
+    hipEvent_t* ev = c->ev[slot][0];
+    rc = enqueue_lists(c, P, w, W, 1, ev);
+    if (rc != PDFS_OK) return rc;
+    if (c->time_kernels) NCK(hipEventRecord(ev[2], s));
+    NCK(launch_lazy_round(P, w, W, 0, true, s));
+    if (c->time_kernels) NCK(hipEventRecord(ev[3], s));
+    NCK(launch_lazy_round(P, w, W, 1, false, s));
+  } else {
+    rc = enqueue_round(c, P, w, c->ev[slot][0], false, 1);
+    if (rc != PDFS_OK) return rc;
+  }
   RoundState* hs = &c->h_slots[slot];
   NCK(hipMemcpyAsync(hs, w.st, sizeof(RoundState), hipMemcpyDeviceToHost, s));
   NCK(hipMemcpyAsync(c->h_rec, w.recs, sizeof(RoundRecord), hipMemcpyDeviceToHost, s));
@@ -236,6 +318,8 @@ int32_t pdfs_best_combo_noalloc(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q,
                      std::to_string(L.pair_cap));
   end_stats(c, stats, t0);
   if (hs->rounds < 1 || !c->h_rec->found) return PDFS_NO_COMBO;
+  if (lazy)   // recorded by sorted index only
+    for (int k = 0; k < h; ++k) c->h_rec->genes[k] = c->h_perm[c->h_rec->sorted_idx[k]];
   fill_combo(out, *c->h_rec, h);
   return PDFS_OK;
 }

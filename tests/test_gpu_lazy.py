@@ -46,3 +46,17 @@ def test_lazy_edges(pdfs, case, mode):  # noqa: F811
             assert np.array_equal(final, exp.final_uncovered)
             if mode == "empty":
                 _counters_equal(st, exp.counters, h)
+
+
+# The allocation-free lazy round lays the transposed rows and the general walk's
+# bitmaps over the unpacked rows: one to three row words, and wider.
+@pytest.mark.parametrize("G,nt", [(70, 50), (600, 64), (4200, 100), (900, 130), (700, 700)])
+@pytest.mark.parametrize("h", [3, 4])
+def test_noalloc_lazy(pdfs, G, nt, h):  # noqa: F811
+    I = synth.random_tiny(77, G, nt, 60, min(0.4, 12.0 / G + 0.02), h)
+    T, N = I.packed()
+    with pdfs.Solver(T, N, nt, 60, "bound") as s:
+        for u in (None, mask_of_bits(np.arange(nt) % 4 != 1)):
+            ref, _ = s.best(h, 1, 10, u)
+            got, _ = s.best_noalloc(h, 1, 10, u)
+            assert got == ref
