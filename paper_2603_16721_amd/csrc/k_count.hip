@@ -53,6 +53,7 @@ constexpr int kTabSeg = 512;      // genes per block of the table kernels
 // the row words of the first k rounds (wc[k]).
 __global__ __launch_bounds__(1024) void k_count_order(Work w, LazyWork L, CountWork C) {
   __shared__ uint32_t hist[kCountMaxT + 2];
+  __shared__ uint32_t part[1024];
   const int tid = threadIdx.x;
   const int n0 = L.uncs[0], R = min(w.st->executed, kCountMaxT);
   for (int i = tid; i < kCountMaxT + 2; i += 1024) hist[i] = 0u;
@@ -65,19 +66,34 @@ __global__ __launch_bounds__(1024) void k_count_order(Work w, LazyWork L, CountW
     atomicAdd(&hist[t[u]], 1u);
   }
   __syncthreads();
-  if (tid == 0) {
-    uint32_t run = 0;
-    for (int v = R; v >= 0; --v) {
-      const uint32_t x = hist[v];
-      hist[v] = run;
-      run += x;
+  // two scans over the rounds, two entries per thread: samples with more
+  // rounds, and row words of earlier rounds
+  auto scan = [&](uint32_t x, uint32_t y, uint32_t& before) {
+    part[tid] = x + y;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+      const uint32_t add = tid >= o ? part[tid - o] : 0u;
+      __syncthreads();
+      part[tid] += add;
+      __syncthreads();
     }
-    uint32_t words = 0;
-    C.wc[0] = 0;
-    for (int r = 0; r < R; ++r) {
-      words += (uint32_t)((L.uncs[r] + 63) / 64);
-      C.wc[r + 1] = words;
-    }
+    before = part[tid] - x - y;
+    __syncthreads();
+  };
+  {
+    const int v0 = R - 2 * tid, v1 = v0 - 1;
+    const uint32_t x = v0 >= 0 ? hist[v0] : 0u, y = v1 >= 0 ? hist[v1] : 0u;
+    uint32_t run;
+    scan(x, y, run);
+    if (v0 >= 0) hist[v0] = run;
+    if (v1 >= 0) hist[v1] = run + x;
+    const int r0 = 2 * tid, r1 = r0 + 1;
+    const uint32_t a = r0 < R ? (uint32_t)((L.uncs[r0] + 63) / 64) : 0u;
+    const uint32_t b = r1 < R ? (uint32_t)((L.uncs[r1] + 63) / 64) : 0u;
+    scan(a, b, run);
+    if (tid == 0) C.wc[0] = 0;
+    if (r0 < R) C.wc[r0 + 1] = run + a;
+    if (r1 < R) C.wc[r1 + 1] = run + a + b;
   }
   __syncthreads();
   for (int u = 0; u < 2; ++u) {
@@ -314,14 +330,13 @@ __global__ __launch_bounds__(256) void k_count_lists(Problem P, Work w, LazyWork
 }
 
 // ------------------------------------------------------------- enumeration
-constexpr int count_cap(int h) { return h <= 4 ? 768 : (h == 5 ? 384 : (h == 6 ? 256 : 160)); }
+constexpr int count_cap(int h) { return h <= 4 ? 384 : (h == 5 ? 256 : 192); }
 constexpr int count_levels(int h) { return h <= 4 ? 1 : h - 3; }
 
 // A wave's share of LDS.
 struct CountLds {
-  unsigned long long* acc;   // [kTallyN][kWave] per-lane sums (h >= 5)
   uint64_t* mask;            // [levels][cap]
-  uint64_t* y;               // [kMaxH][kMaxW64]
+  uint64_t* y;               // [levels + 1][kMaxW64]
   uint32_t* ts;              // [kWave] rounds of the pair's samples
   uint16_t* idx;             // [levels][cap]
   uint16_t* smp;             // [kMaxCount]
@@ -329,23 +344,23 @@ struct CountLds {
 
 size_t count_wave_bytes(int h) {
   const size_t lv = (size_t)count_levels(h), cap = (size_t)count_cap(h);
-  size_t b = (h >= 5 ? (size_t)kTallyN * kWave * 8 : 0) + lv * cap * 8 +
-             (size_t)kMaxH * kMaxW64 * 8 + kWave * 4 + lv * cap * 2 + kMaxCount * 2;
+  const size_t b = lv * cap * 8 + (lv + 1) * kMaxW64 * 8 + kWave * 4 + lv * cap * 2 + kMaxCount * 2;
   return (b + 15) / 16 * 16;
 }
 
 __device__ __forceinline__ CountLds count_lds(char* p, int h) {
   const int lv = count_levels(h), cap = count_cap(h);
   CountLds s;
-  s.acc = reinterpret_cast<unsigned long long*>(p);
-  s.mask = reinterpret_cast<uint64_t*>(s.acc + (h >= 5 ? kTallyN * kWave : 0));
+  s.mask = reinterpret_cast<uint64_t*>(p);
   s.y = s.mask + lv * cap;
-  s.ts = reinterpret_cast<uint32_t*>(s.y + kMaxH * kMaxW64);
+  s.ts = reinterpret_cast<uint32_t*>(s.y + (lv + 1) * kMaxW64);
   s.idx = reinterpret_cast<uint16_t*>(s.ts + kWave);
   s.smp = s.idx + lv * cap;
   return s;
 }
 
+// Depths are template arguments throughout, so that the per-lane sums of every
+// depth stay in registers.
 template <int H>
 struct Count {
   const Problem& P;
@@ -354,25 +369,17 @@ struct Count {
   const CountWork& C;
   CountLds s;
   const uint64_t* T;
+  const uint16_t* order;   // LDS: [kMaxCount] samples by falling rounds
+  const uint16_t* tt;      // LDS: their rounds
   int lane, nA, w64, h, R;
-  // h <= 4: per-lane sums
-  unsigned long long ne2, vis3, ne3, vis4, ne4, xv3, xw3, xv4, xw4;
+  unsigned long long ne2, vis3, xv3, xw3, xv4, xw4;
+  unsigned long long ne[kMaxH + 1], vis[kMaxH + 1];   // depths 3.., 4..
 
-  // c := C(n, k) sums for nonempty[l], visited[l]
-  __device__ __forceinline__ void add_ne(int l, unsigned long long v) {
-    if (H == 0) s.acc[(kCNe3 + l - 3) * kWave + lane] += v;
-    else if (l == 3) ne3 += v;
-    else ne4 += v;
-  }
-  __device__ __forceinline__ void add_vis(int l, unsigned long long v) {
-    if (H == 0) s.acc[(kCVis4 + l - 4) * kWave + lane] += v;
-    else vis4 += v;
-  }
   // 0-based loop bound of depth l
   __device__ __forceinline__ int lim(int l) const { return P.G - h + l - 1; }
 
   __device__ __forceinline__ const uint64_t* brow(int p) const {
-    return L.B + (size_t)C.order[p] * L.gw;
+    return L.B + (size_t)order[p] * L.gw;
   }
 
   // Position of gene g in the list of sample p (which carries it).
@@ -384,17 +391,22 @@ struct Count {
 
   // Everything below a depth-l prefix whose only sample is p and whose last
   // gene is at `pos` of the sample's list.
-  __device__ __forceinline__ void below_single(int l, int p, int pos, unsigned long long t) {
+  template <int l>
+  __device__ __forceinline__ void below_single(int p, int pos, unsigned long long t) {
     const int n = C.kc[p];
     const size_t off = C.off[p];
-    for (int i = 1; l + i <= h; ++i) {
+    constexpr int top = H > 0 ? H : kMaxH;
+#pragma unroll
+    for (int i = 1; l + i <= top; ++i) {
       const int d = l + i;   // depth counted
+      if (d > h) continue;
       const int e = C.ecnt[(size_t)p * 16 + (h - d)];
       const int r = n - 1 - pos - e;
       unsigned long long c = 1;
+#pragma unroll
       for (int k = 1; k <= i; ++k)
         c = c * (unsigned long long)(r - k + 1 > 0 ? r - k + 1 : 0) / (unsigned long long)k;
-      add_ne(d, t * c);
+      ne[d] += t * c;
       if (d + 1 > h) continue;
       // visits below them: sum of lim(d + 1) - largest index
       unsigned long long q = C.q[(size_t)(i - 1) * C.q_n + off + pos];
@@ -402,11 +414,12 @@ struct Count {
         const int at = n - 1 - x;
         const int u = at - pos;       // 1-based among the later genes
         unsigned long long b = 1;
+#pragma unroll
         for (int k = 1; k <= i - 1; ++k)
           b = b * (unsigned long long)(u - k > 0 ? u - k : 0) / (unsigned long long)k;
         q -= b * (unsigned long long)w.act[C.genes[off + at]];
       }
-      add_vis(d + 1, t * ((unsigned long long)lim(d + 1) * c - q));
+      if (d + 1 <= kMaxH) vis[d + 1 <= kMaxH ? d + 1 : kMaxH] += t * ((unsigned long long)lim(d + 1) * c - q);
     }
     if (H == 4 && l == 2) {
       xv4 += C.sv[off + pos];
@@ -414,23 +427,27 @@ struct Count {
     }
   }
 
-  // One depth-l prefix ending in gene c, living t rounds.
-  __device__ __forceinline__ void node(int l, int c, unsigned long long t) {
+  // One depth-l prefix ending in gene c, living t rounds; false past the loop
+  // bound (nothing below it counts either).
+  template <int l>
+  __device__ __forceinline__ bool node(int c, unsigned long long t) {
     const int ai = w.act[c];
-    if (ai > lim(l)) return;
-    add_ne(l, t);
-    if (l + 1 <= h) add_vis(l + 1, t * (unsigned long long)(lim(l + 1) - ai));
+    if (ai > lim(l)) return false;
+    ne[l] += t;
+    if (l < kMaxH && l + 1 <= h)
+      vis[l < kMaxH ? l + 1 : l] += t * (unsigned long long)(lim(l + 1) - ai);
     if (H == 4 && l == 3) {
       unsigned long long a, b;
       later_visits(C, R, c, (int)t, a, b);
       xv4 += a;
       xw4 += b;
     }
+    return true;
   }
 
-  // Leaves below a prefix with the m listed samples and last gene c, counted
-  // at their first sample; `in` (may be null) limits them.
-  __device__ __forceinline__ void leaves(int m, int lo) {
+  // Leaves below a prefix with the m listed samples and last gene lo - 1,
+  // counted at their first sample.
+  __device__ __forceinline__ unsigned long long leaves(int m, int lo) {
     const int w_hi = (nA + 63) >> 6;
     unsigned long long sum = 0;
     for (int w0 = lo >> 6; w0 < w_hi; w0 += kWave) {
@@ -441,11 +458,11 @@ struct Count {
       for (int j = 0; j < m; ++j) {
         const int p = s.smp[j];
         const uint64_t x = wd < w_hi ? brow(p)[wd] : 0ull;
-        sum += (unsigned long long)C.tt[p] * (unsigned long long)popc64(x & ~acc);
+        sum += (unsigned long long)tt[p] * (unsigned long long)popc64(x & ~acc);
         acc |= x;
       }
     }
-    add_ne(h, sum);
+    return sum;
   }
 
   // Union of the m listed samples' genes in [lo, nA).
@@ -459,125 +476,123 @@ struct Count {
     return x;
   }
 
-  __device__ __forceinline__ void general(uint64_t y2, int b, uint64_t* bits) {
-    int l = 0;
-    wave_lds_sync();
-    if (lane < w64) s.y[lane] = y2;
-    int m = list_samples(y2, s.smp, lane);
-    auto fill = [&](uint64_t* bm, int lo) {
-      const int w_hi = (nA + 63) >> 6;
-      for (int w0 = lo >> 6; w0 < w_hi; w0 += kWave) {
-        const uint64_t x = union_word(m, w0 + lane, w_hi, lo);
-        if (w0 + lane < w_hi) bm[w0 + lane] = x;
-      }
-      __threadfence_block();
-    };
-    fill(bits, b + 1);
-    int at = b + 1;
-    int keep = 0;   // lane l: where level l goes on
-    for (;;) {
-      uint64_t* bm = bits + (size_t)l * L.gw;
-      const int c = next_bit(bm, at, nA, lane);
-      if (c < 0) {
-        if (l == 0) break;
-        --l;
-        at = __builtin_amdgcn_readlane(keep, l);
-        continue;
-      }
-      at = c + 1;
+  // The general walk (any number of samples and candidates): level LV, the
+  // candidates of depth LV + 3 as a bitmap, below the prefix with samples
+  // s.y[LV] (listed, m of them) and last gene lo - 1.
+  template <int LV>
+  __device__ __forceinline__ void general(int m, int lo, uint64_t* bits) {
+    uint64_t* bm = bits + (size_t)LV * L.gw;
+    const int w_hi = (nA + 63) >> 6;
+    for (int w0 = lo >> 6; w0 < w_hi; w0 += kWave) {
+      const uint64_t x = union_word(m, w0 + lane, w_hi, lo);
+      if (w0 + lane < w_hi) bm[w0 + lane] = x;
+    }
+    __threadfence_block();
+    for (int c = next_bit(bm, lo, nA, lane); c >= 0; c = next_bit(bm, c + 1, nA, lane)) {
       uint64_t y = 0;
-      if (lane < w64) y = s.y[l * kMaxW64 + lane] & T[(size_t)c * w64 + lane];
-      m = list_samples(y, s.smp, lane);
+      if (lane < w64) y = s.y[LV * kMaxW64 + lane] & T[(size_t)c * w64 + lane];
+      const int mc = list_samples(y, s.smp, lane);
       const int p = uniform(s.smp[0]);
-      const unsigned long long t = (unsigned long long)C.tt[p];
-      const bool in = w.act[c] <= lim(l + 3);
+      const unsigned long long t = (unsigned long long)tt[p];
+      if (w.act[c] > lim(LV + 3)) continue;
       if (lane == 0) {
-        node(l + 3, c, t);
-        if (m == 1 && in) below_single(l + 3, p, pos_in(p, c), t);
+        node<LV + 3>(c, t);
+        if (mc == 1) below_single<LV + 3>(p, pos_in(p, c), t);
       }
-      if (m == 1 || !in) continue;
-      if (l + 4 == h) {
-        leaves(m, c + 1);
+      if (mc == 1) continue;
+      if (LV + 4 == h) {
+        ne[LV + 4] += leaves(mc, c + 1);
         continue;
       }
-      wave_lds_sync();
-      if (lane < w64) s.y[(l + 1) * kMaxW64 + lane] = y;
-      wave_lds_sync();
-      fill(bits + (size_t)(l + 1) * L.gw, c + 1);
-      keep = lane == l ? at : keep;
-      ++l;
-    }
-  }
-
-  // The nodes of a fresh level list; returns nothing below multi-sample ones.
-  __device__ __forceinline__ void list_nodes(int l, int n, const uint64_t* mk, const uint16_t* ix) {
-    for (int i0 = 0; i0 < n; i0 += kWave) {
-      const int i = i0 + lane;
-      if (i >= n) continue;
-      const uint64_t x = mk[i];
-      const int c = ix[i];
-      const int f = __builtin_ctzll(x);
-      const unsigned long long t = s.ts[f];
-      node(l + 3, c, t);
-      if ((x & (x - 1)) == 0 && w.act[c] <= lim(l + 3) && l + 3 < h) {
-        const int p = s.smp[f];
-        below_single(l + 3, p, pos_in(p, c), t);
+      if constexpr (LV + 4 < (H > 0 ? H : kMaxH)) {
+        wave_lds_sync();
+        if (lane < w64) s.y[(LV + 1) * kMaxW64 + lane] = y;
+        wave_lds_sync();
+        general<LV + 1>(mc, c + 1, bits);
       }
     }
   }
 
-  // The subtree over the level lists.
-  __device__ __forceinline__ void lists(int n0) {
+  // One depth-(LV + 3) candidate per lane (samples mk, gene ix): its node, and
+  // all below it where one sample is left.
+  template <int LV>
+  __device__ __forceinline__ void candidate(uint64_t mk, int ix) {
+    const int f = __builtin_ctzll(mk);
+    const unsigned long long t = s.ts[f];
+    if (!node<LV + 3>(ix, t)) return;
+    if ((mk & (mk - 1)) == 0 && LV + 3 < h) {
+      const int p = s.smp[f];
+      below_single<LV + 3>(p, pos_in(p, ix), t);
+    }
+  }
+
+  // The subtree over at most 64 candidates held one per lane (`set`): below an
+  // entry with several samples lie the later lanes that share one.
+  template <int LV>
+  __device__ __forceinline__ void lanes(uint64_t mk, int ix, unsigned long long set) {
+    const bool on = __builtin_amdgcn_inverse_ballot_w64(set);
+    if (on) candidate<LV>(mk, ix);
+    unsigned long long many = __ballot(on && (mk & (mk - 1)) != 0);
+    while (many) {
+      const int i = __builtin_ctzll(many);
+      many &= many - 1;
+      const unsigned long long later = set & ~((2ull << i) - 1ull);
+      if (!later) break;
+      const uint64_t mi = readlane64(mk, i) & mk;
+      const unsigned long long kids =
+          __ballot(__builtin_amdgcn_inverse_ballot_w64(later) && mi != 0);
+      if (!kids) continue;
+      if (LV + 4 == h) {
+        if (__builtin_amdgcn_inverse_ballot_w64(kids))
+          ne[LV + 4] += (unsigned long long)s.ts[__builtin_ctzll(mi)];
+      } else {
+        if constexpr (LV + 4 < (H > 0 ? H : kMaxH)) lanes<LV + 1>(mi, ix, kids);
+      }
+    }
+  }
+
+  // The same over a longer list in LDS.
+  template <int LV>
+  __device__ __forceinline__ void lists(int n) {
     const int cap = count_cap(h);
-    int l = 0, n = n0, i = 0;
-    int keep_n = 0, keep_i = 0;
-    list_nodes(0, n0, s.mask, s.idx);
-    for (;;) {
-      uint64_t* mk = s.mask + l * cap;
-      uint16_t* ix = s.idx + l * cap;
-      if (i + 1 >= n) {
-        if (l == 0) break;
-        --l;
-        n = __builtin_amdgcn_readlane(keep_n, l);
-        i = __builtin_amdgcn_readlane(keep_i, l) + 1;
-        continue;
-      }
-      const uint64_t mi = mk[i];
-      if ((mi & (mi - 1)) == 0) {   // a single sample: counted with the list
-        ++i;
-        continue;
-      }
-      if (l + 4 == h) {
-        unsigned long long sum = 0;
+    const uint64_t* mk = s.mask + LV * cap;
+    const uint16_t* ix = s.idx + LV * cap;
+    for (int i = lane; i < n; i += kWave) candidate<LV>(mk[i], ix[i]);
+    for (int i = 0; i + 1 < n; ++i) {
+      const uint64_t mi = readlane64(mk[i], 0);
+      if ((mi & (mi - 1)) == 0) continue;   // a single sample: counted above
+      if (LV + 4 == h) {
         for (int j = i + 1 + lane; j < n; j += kWave) {
           const uint64_t x = mi & mk[j];
-          if (x) sum += s.ts[__builtin_ctzll(x)];
+          if (x) ne[LV + 4] += (unsigned long long)s.ts[__builtin_ctzll(x)];
         }
-        add_ne(h, sum);
-        ++i;
         continue;
       }
-      uint64_t* mo = mk + cap;
-      uint16_t* io = ix + cap;
-      int k = 0;
-      for (int j0 = i + 1; j0 < n; j0 += kWave) {
-        const int j = j0 + lane;
-        const uint64_t x = j < n ? (mi & mk[j]) : 0ull;
-        const unsigned long long hm = __ballot(x != 0);
-        if (x) {
-          const int pos = rank_below(hm, k);
-          mo[pos] = x;
-          io[pos] = ix[j];
+      if constexpr (LV + 4 < (H > 0 ? H : kMaxH)) {
+        uint64_t* mo = s.mask + (LV + 1) * cap;
+        uint16_t* io = s.idx + (LV + 1) * cap;
+        int k = 0;
+        for (int j0 = i + 1; j0 < n; j0 += kWave) {
+          const int j = j0 + lane;
+          const uint64_t x = j < n ? (mi & mk[j]) : 0ull;
+          const unsigned long long hm = __ballot(x != 0);
+          if (x) {
+            const int pos = rank_below(hm, k);
+            mo[pos] = x;
+            io[pos] = ix[j];
+          }
+          k += __popcll(hm);
         }
-        k += __popcll(hm);
+        wave_lds_sync();
+        if (k > kWave) {
+          lists<LV + 1>(k);
+        } else if (k > 0) {
+          const uint64_t x = lane < k ? mo[lane] : 0ull;
+          const int g = lane < k ? (int)io[lane] : 0;
+          wave_lds_sync();
+          lanes<LV + 1>(x, g, k < 64 ? (1ull << k) - 1ull : ~0ull);
+        }
       }
-      wave_lds_sync();
-      keep_n = lane == l ? n : keep_n;
-      keep_i = lane == l ? i : keep_i;
-      ++l;
-      n = k;
-      i = 0;
-      list_nodes(l, n, mo, io);
     }
   }
 
@@ -587,79 +602,101 @@ struct Count {
     if (lane < w64) y2 = T[(size_t)a * w64 + lane] & T[(size_t)b * w64 + lane];
     const int m = list_samples(y2, s.smp, lane);
     if (h == 3) {
-      leaves(m, b + 1);
+      ne[3] += leaves(m, b + 1);
       return;
     }
-    const int cap = count_cap(h);
-    bool listed = m <= 64;
-    int n = 0;
-    if (listed) {
-      const int w_hi = (nA + 63) >> 6;
-      for (int w0 = (b + 1) >> 6; w0 < w_hi && listed; w0 += kWave) {
-        const int wd = w0 + lane;
-        uint64_t x = union_word(m, wd, w_hi, b + 1);
-        const int c = popc64(x);
-        int pos = wave_before(c, lane);
-        const int tot = uniform(__shfl(pos + c, 63, 64));
-        if (n + tot > cap) {
-          listed = false;
-          break;
+    if constexpr (H != 2 && H != 3) {
+      const int cap = count_cap(h);
+      bool listed = m <= 64;
+      int n = 0;
+      if (listed) {
+        const int w_hi = (nA + 63) >> 6;
+        for (int w0 = (b + 1) >> 6; w0 < w_hi && listed; w0 += kWave) {
+          const int wd = w0 + lane;
+          uint64_t x = union_word(m, wd, w_hi, b + 1);
+          const int c = popc64(x);
+          int pos = wave_before(c, lane);
+          const int tot = uniform(__shfl(pos + c, 63, 64));
+          if (n + tot > cap) {
+            listed = false;
+            break;
+          }
+          pos += n;
+          while (x) {
+            s.idx[pos++] = (uint16_t)(wd * 64 + __builtin_ctzll(x));
+            x &= x - 1;
+          }
+          n += tot;
         }
-        pos += n;
-        while (x) {
-          s.idx[pos++] = (uint16_t)(wd * 64 + __builtin_ctzll(x));
-          x &= x - 1;
-        }
-        n += tot;
       }
-    }
-    if (!listed) {
-      general(y2, b, bits);
-      return;
-    }
-    if (lane < m) s.ts[lane] = (uint32_t)C.tt[s.smp[lane]];
-    wave_lds_sync();
-    for (int i = lane; i < n; i += kWave) {
-      const uint64_t* row = T + (size_t)s.idx[i] * w64;
-      uint64_t mk = 0;
+      if (!listed) {
+        wave_lds_sync();
+        if (lane < w64) s.y[lane] = y2;
+        wave_lds_sync();
+        general<0>(m, b + 1, bits);
+        return;
+      }
+      if (lane < m) s.ts[lane] = (uint32_t)tt[s.smp[lane]];
+      wave_lds_sync();
+      auto mask_of = [&](int g) {
+        const uint64_t* row = T + (size_t)g * w64;
+        uint64_t mk = 0;
 #pragma unroll 4
-      for (int j = 0; j < m; ++j) {
-        const int p = s.smp[j];
-        mk |= ((row[p >> 6] >> (p & 63)) & 1ull) << j;
+        for (int j = 0; j < m; ++j) {
+          const int p = s.smp[j];
+          mk |= ((row[p >> 6] >> (p & 63)) & 1ull) << j;
+        }
+        return mk;
+      };
+      if (n <= kWave) {
+        const int ix = lane < n ? (int)s.idx[lane] : 0;
+        const uint64_t mk = lane < n ? mask_of(ix) : 0ull;
+        lanes<0>(mk, ix, n < 64 ? (1ull << n) - 1ull : ~0ull);
+        return;
       }
-      s.mask[i] = mk;
+      for (int i = lane; i < n; i += kWave) s.mask[i] = mask_of(s.idx[i]);
+      wave_lds_sync();
+      lists<0>(n);
     }
-    wave_lds_sync();
-    lists(n);
   }
 };
 
 // One lane per pair: pairs with a single sample in closed form, the others by
 // the wave in turn.  Wave q takes every nsub-th pair of share q % nw, so that
 // the pairs with most samples (first in every share) spread over all waves.
+// Bound by chains of dependent loads: the sample order sits in LDS, the lists
+// of most pairs in lanes, and 25 KB of LDS a block keep six blocks on a compute
+// unit (48 KB, lists in LDS and the order in memory: G = 20000, h = 4 1251 us,
+// 954 us now; one round of G = 5000, h = 5 837 us, 314 us now).
 template <int H>
 __global__ __launch_bounds__(256) void k_count_pairs(Problem P, Work w, LazyWork L, CountWork C) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ uint16_t s_order[kMaxCount], s_tt[kMaxCount];
   RoundState* st = w.st;
   const int lane = threadIdx.x & 63;
   const int wib = uniform(threadIdx.x >> 6);
   const int q = blockIdx.x * (kBlock / kWave) + wib;
   const int h = H > 0 ? H : P.h;
+  const int n0 = L.uncs[0];
+  for (int i = threadIdx.x; i < n0; i += kBlock) {
+    s_order[i] = (uint16_t)C.order[i];
+    s_tt[i] = (uint16_t)C.tt[i];
+  }
+  __syncthreads();
   Count<H> v{P, w, L, C, count_lds(lds + (size_t)wib * C.wave_bytes, h),
-             reinterpret_cast<const uint64_t*>(w.TA)};
+             reinterpret_cast<const uint64_t*>(w.TA), s_order, s_tt};
   v.lane = lane;
   v.nA = uniform(st->nA);
   v.w64 = w.w64;
   v.h = h;
   v.R = min(uniform(st->executed), kCountMaxT);
-  v.ne2 = v.vis3 = v.ne3 = v.vis4 = v.ne4 = v.xv3 = v.xw3 = v.xv4 = v.xw4 = 0;
-  if (H == 0)
-    for (int f = 0; f < kTallyN; ++f) v.s.acc[f * kWave + lane] = 0ull;
-  wave_lds_sync();
+  v.ne2 = v.vis3 = v.xv3 = v.xw3 = v.xv4 = v.xw4 = 0;
+#pragma unroll
+  for (int d = 0; d <= kMaxH; ++d) v.ne[d] = v.vis[d] = 0;
   const int nsub = gridDim.x * (kBlock / kWave) / L.nw;
   const int seg = q % L.nw, sub = q / L.nw;
   const unsigned long long E = st->n_pairs < w.pair_cap ? st->n_pairs : w.pair_cap;
-  const int n_mine = (unsigned long long)seg < E
+  const int n_mine = sub < nsub && (unsigned long long)seg < E
                          ? (int)((E - (unsigned long long)seg + (unsigned long long)L.nw - 1ull) /
                                  (unsigned long long)L.nw)
                          : 0;
@@ -683,7 +720,7 @@ __global__ __launch_bounds__(256) void k_count_pairs(Problem P, Work w, LazyWork
       }
     }
     if (m > 0) {
-      const unsigned long long t = (unsigned long long)C.tt[p];
+      const unsigned long long t = (unsigned long long)s_tt[p];
       v.ne2 += t;
       if (h >= 3) {
         v.vis3 += t * (unsigned long long)(v.lim(3) - w.act[b]);
@@ -698,7 +735,7 @@ __global__ __launch_bounds__(256) void k_count_pairs(Problem P, Work w, LazyWork
           v.xv3 += x;
           v.xw3 += y;
         }
-        if (m == 1) v.below_single(2, p, v.pos_in(p, b), t);
+        if (m == 1) v.template below_single<2>(p, v.pos_in(p, b), t);
       }
     }
     if (h >= 3) {
@@ -710,16 +747,14 @@ __global__ __launch_bounds__(256) void k_count_pairs(Problem P, Work w, LazyWork
       }
     }
   }
-  unsigned long long row[kTallyN];
-  wave_lds_sync();
-#pragma unroll
-  for (int f = 0; f < kTallyN; ++f) row[f] = H == 0 ? v.s.acc[f * kWave + lane] : 0ull;
+  unsigned long long row[kTallyN] = {0};
   row[kCNe2] = v.ne2;
   row[kCVis3] = v.vis3;
-  if (H != 0) {
-    row[kCNe3] = v.ne3;
-    row[kCNe3 + 1] = v.ne4;
-    row[kCVis4] = v.vis4;
+#pragma unroll
+  for (int d = 3; d <= kMaxH; ++d) row[kCNe3 + d - 3] = v.ne[d];
+#pragma unroll
+  for (int d = 4; d <= kMaxH; ++d) row[kCVis4 + d - 4] = v.vis[d];
+  if (H == 3 || H == 4) {
     row[kCXv3] = v.xv3;
     row[kCXw3] = v.xw3;
     row[kCXv4] = v.xv4;
@@ -733,7 +768,7 @@ __global__ __launch_bounds__(256) void k_count_pairs(Problem P, Work w, LazyWork
 __global__ __launch_bounds__(1024) void k_count_finish(Problem P, Work w, LazyWork L, CountWork C,
                                                        int rows) {
   __shared__ unsigned long long tsum[16][kTallyN];
-  __shared__ unsigned long long gsum[16][2];
+  __shared__ unsigned long long gsum[16][2], msum[16];
   __shared__ uint32_t h1[kCountMaxT + 2], h2[kCountMaxT + 2];
   RoundState* st = w.st;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -758,6 +793,36 @@ __global__ __launch_bounds__(1024) void k_count_finish(Problem P, Work w, LazyWo
     ne1 += (unsigned long long)__shfl_xor((long long)ne1, o, 64);
     vis2 += (unsigned long long)__shfl_xor((long long)vis2, o, 64);
   }
+  __syncthreads();   // the histograms are whole
+  // genes active in round r: those with at least r rounds
+  for (int o = 1; o < 2048; o <<= 1) {
+    uint32_t x[2][2] = {{0, 0}, {0, 0}};
+    for (int u = 0; u < 2; ++u) {
+      const int r = tid + 1024 * u;
+      if (r + o < kCountMaxT + 2) {
+        x[u][0] = h1[r + o];
+        x[u][1] = h2[r + o];
+      }
+    }
+    __syncthreads();
+    for (int u = 0; u < 2; ++u) {
+      const int r = tid + 1024 * u;
+      if (r < kCountMaxT + 2) {
+        h1[r] += x[u][0];
+        h2[r] += x[u][1];
+      }
+    }
+    __syncthreads();
+  }
+  // round r: every active pair inside the depth-1/2 bounds, times |U|
+  unsigned long long macs = 0;
+  for (int r = tid + 1; r <= R; r += 1024) {
+    const unsigned long long a1 = h1[r], a2 = h2[r];
+    macs += (a1 ? a1 * a2 - a1 * (a1 + 1) / 2 : 0) * (unsigned long long)L.uncs[r - 1];
+  }
+  for (int o = 32; o > 0; o >>= 1)
+    macs += (unsigned long long)__shfl_xor((long long)macs, o, 64);
+  if (lane == 0) msum[wid] = macs;
   if (lane < kTallyN) tsum[wid][lane] = v;
   if (lane == 0) {
     gsum[wid][0] = ne1;
@@ -785,7 +850,8 @@ __global__ __launch_bounds__(1024) void k_count_finish(Problem P, Work w, LazyWo
     }
   }
   if (tid == 0) {
-    unsigned long long n1 = 0, v2 = 0, macs = 0;
+    unsigned long long n1 = 0, v2 = 0;
+    macs = 0;
     for (int i = 0; i < 16; ++i) {
       n1 += gsum[i][0];
       v2 += gsum[i][1];
@@ -793,14 +859,7 @@ __global__ __launch_bounds__(1024) void k_count_finish(Problem P, Work w, LazyWo
     st->tot.visited[1] = (unsigned long long)R * (unsigned long long)(P.G - h + 1);
     st->tot.nonempty[1] = n1;
     st->tot.visited[2] = v2;
-    // round r: every active pair inside the depth-1/2 bounds, times |U|
-    unsigned long long a1 = 0, a2 = 0;
-    for (int r = R; r >= 1; --r) {
-      a1 += h1[r];
-      a2 += h2[r];
-      const unsigned long long pairs = a1 ? a1 * a2 - a1 * (a1 + 1) / 2 : 0;
-      macs += pairs * (unsigned long long)L.uncs[r - 1];
-    }
+    for (int i = 0; i < 16; ++i) macs += msum[i];
     st->tx_pair_macs = macs;
   }
 }
@@ -835,6 +894,8 @@ hipError_t launch_count(const Problem& P, const Work& w, const LazyWork& L, cons
     case 2: k_count_pairs<2><<<grid, kBlock, lds, s>>>(P, w, L, C); break;
     case 3: k_count_pairs<3><<<grid, kBlock, lds, s>>>(P, w, L, C); break;
     case 4: k_count_pairs<4><<<grid, kBlock, lds, s>>>(P, w, L, C); break;
+    case 5: k_count_pairs<5><<<grid, kBlock, lds, s>>>(P, w, L, C); break;
+    case 6: k_count_pairs<6><<<grid, kBlock, lds, s>>>(P, w, L, C); break;
     default: k_count_pairs<0><<<grid, kBlock, lds, s>>>(P, w, L, C); break;
   }
   k_count_finish<<<1, 1024, 0, s>>>(P, w, L, C, grid);

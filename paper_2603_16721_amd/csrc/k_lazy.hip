@@ -712,12 +712,6 @@ __device__ __forceinline__ void open_lists(Wave& v, int n0) {
   }
 }
 
-__device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l);
-  return (uint64_t)hi << 32 | lo;
-}
-
 // A candidate's samples as a mask over the pair's m <= 64 * MW.
 template <int MW>
 struct Mask {
@@ -807,10 +801,26 @@ __device__ __forceinline__ void open_lanes(Wave& v, const Mask<MW>& mk, int ix,
   }
 }
 
+// (few samples: their words are fetched four at a time, in flight together)
 template <int MW>
-__device__ __forceinline__ void open_few(Wave& v, uint64_t y2, int n) {
-  const int ix = v.lane < n ? (int)v.s.idx[v.lane] : 0;
-  const Mask<MW> mk = sample_mask<MW>(v, y2, ix, v.lane < n);
+__device__ __forceinline__ void open_few(Wave& v, uint64_t y2, int m, int n) {
+  const bool on = v.lane < n;
+  const int ix = on ? (int)v.s.idx[v.lane] : 0;
+  Mask<MW> mk;
+  if (MW == 1 && m <= 24) {
+    const uint64_t* row = v.T + (size_t)ix * v.w64;
+    uint64_t x = 0;
+    if (on) {
+#pragma unroll 4
+      for (int j = 0; j < m; ++j) {
+        const int sid = v.s.smp[j];
+        x |= ((row[sid >> 6] >> (sid & 63)) & 1ull) << j;
+      }
+    }
+    mk.w[0] = x;
+  } else {
+    mk = sample_mask<MW>(v, y2, ix, on);
+  }
   open_lanes<0, MW>(v, mk, ix, n < 64 ? (1ull << n) - 1ull : ~0ull);
 }
 
@@ -857,9 +867,9 @@ __device__ __forceinline__ int open_pair(Wave& v, int a, int b, uint64_t* bits) 
       else PDFS_BY_SLICES(m, listed = list_by_slices<NB>(v, m, b + 1, cap, n));
     }
     if (listed && n <= kWave) {
-      if (m <= 64) open_few<1>(v, y2, n);
-      else if (m <= 128) open_few<2>(v, y2, n);
-      else open_few<4>(v, y2, n);
+      if (m <= 64) open_few<1>(v, y2, m, n);
+      else if (m <= 128) open_few<2>(v, y2, m, n);
+      else open_few<4>(v, y2, m, n);
     } else if (listed) {
       // the candidates' samples as masks over the pair's
       for (int i0 = 0; i0 < n; i0 += kWave) {

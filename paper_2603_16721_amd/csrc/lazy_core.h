@@ -33,6 +33,12 @@ __device__ __forceinline__ int wave_before(int v, int lane) {
   return incl - v;
 }
 
+__device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l);
+  return (uint64_t)hi << 32 | lo;
+}
+
 // Samples of y (lane k < w64 holds word k) as ids in smp; returns how many.
 __device__ __forceinline__ int list_samples(uint64_t y, uint16_t* smp, int lane) {
   const int c = popc64(y);

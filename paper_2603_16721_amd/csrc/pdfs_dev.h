@@ -253,7 +253,7 @@ struct LazyWork {
 
 // Counters of an empty-intersection run (k_count.hip), made after its rounds.
 constexpr int kCountMaxT = 1281;    // rounds a run can take (each covers a sample, or is the last)
-constexpr int kCountWaves = 4096;   // waves of the enumeration at most
+constexpr int kCountWaves = 8192;   // waves of the enumeration at most
 
 struct CountWork {
   int32_t* order;     // [64 * kMaxW64] samples by falling rounds
