@@ -104,20 +104,23 @@ typedef struct {
                                      default: normals not carrying all of them */
 #define PDFS_OPT_GRAPHS 2         /* capture one round as a HIP graph per row width
                                      and replay it (needs a non-NULL stream; ignored
-                                     together with PDFS_OPT_TIME_KERNELS) */
+                                     together with PDFS_OPT_TIME_KERNELS, and where a
+                                     round is one launch: runs of h >= 2 under empty
+                                     or bound pruning) */
 
 typedef struct {
     int32_t prune_mode; /* PDFS_PRUNE_*                                  */
     int32_t device;     /* HIP device ordinal                            */
     void *stream;       /* hipStream_t on that device, or NULL           */
     int32_t flags;      /* PDFS_OPT_* bits                               */
-    int32_t pair_cap;   /* initial capacity of the round's pair list
-                           (pairs); <= 0: the default, max(2^21, 128 x
-                           the active genes of the first round), at most
-                           every pair.  A round that emits more pairs
-                           grows the list to its count + 1/4 and is run
-                           again, so this only trades memory for an
-                           occasional repeated round. */
+    int32_t pair_cap;   /* initial capacity of the pair list (pairs);
+                           <= 0: the default, max(2^21, 128 x the active
+                           genes of the first round), at most every pair.
+                           A pair table (one per run; one per round of an
+                           exhaustive run) that emits more pairs grows the
+                           list to its count + 1/4 and is made again, so
+                           this only trades memory for an occasional
+                           repeated table. */
 } pdfs_options;
 
 /* One chosen combination (one greedy round). */

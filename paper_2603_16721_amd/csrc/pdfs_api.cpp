@@ -1,8 +1,7 @@
 // C ABI of libpdfs: context setup (ingest + sparsest-first sort) and the
 // per-round orchestration of the greedy weighted-set-cover loop.  All
-// arithmetic of the search runs in the kernels of k_round.hip, k_pairs.hip
-// and k_dfs.hip; this file moves buffers, picks kernel variants and reads the
-// per-round record back.
+// arithmetic of the search runs in the kernels (k_*.hip); this file moves
+// buffers, picks kernel variants and reads the per-round record back.
 #include <hip/hip_runtime.h>
 
 #include <chrono>
@@ -509,16 +508,34 @@ static int32_t enqueue_rounds(pdfs_ctx* c, const Problem& P, const Work& w, int 
   return PDFS_OK;
 }
 
+// How a lazy run makes its pair list: by the genes' samples (words added: one per
+// mutation and 64 genes) or by the matrix cores' table (128 x 128 tiles, 128
+// samples at a time).  Samples against table, us, at even densities, with the words
+// added per tile and 128 samples in brackets: G = 2000, 500 samples 7 | 19 (176),
+// 8 | 19 (590), 27 | 20 (1770); G = 5000, 1000 samples 13 | 55 (181), 19 | 75
+// (600), 89 | 82 (1810), 120 | 106 (6020); G = 20000 33 | 676 (190), 415 | 804
+// (630).  The line is drawn where the smaller cohorts cross.
+constexpr unsigned long long kListWords = 1024;
+
+static bool lists_by_samples(const pdfs_ctx* c, int w64) {
+  const unsigned long long tiles = (unsigned long long)(c->nA_max + 127) / 128;
+  return c->tumor_bits * (unsigned long long)((c->nA_max + 63) / 64) <=
+         kListWords * (tiles * (tiles + 1) / 2) * (unsigned long long)((w64 + 1) / 2);
+}
+
 int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, const LazyWork& L,
                       int run_rounds, hipEvent_t* ev) {
   hipStream_t s = c->stream;
   const bool tk = c->time_kernels;
-  const int32_t rc = enqueue_front(c, P, w, run_rounds, true, true, false);
+  const bool by_samples = lists_by_samples(c, w.w64);
+  const int32_t rc = enqueue_front(c, P, w, run_rounds, true, !by_samples, false);
   if (rc != PDFS_OK) return rc;
+  if (by_samples) CK(c, launch_lazy_begin(P, w, L, s));
   if (tk) CK(c, hipEventRecord(ev[0], s));
-  CK(c, launch_pair_list(P, w, s));
+  CK(c, by_samples ? launch_list_pairs(w, L, c->nA_max, s) : launch_pair_list(P, w, s));
   if (tk) CK(c, hipEventRecord(ev[1], s));
-  CK(c, launch_lazy_begin(P, w, L, s));
+  // (after the table: an allocation-free round keeps B where the table's bytes were)
+  if (!by_samples) CK(c, launch_lazy_begin(P, w, L, s));
   CK(c, launch_pair_hist(w, s));
   CK(c, launch_lazy_deal(P, w, L, s));
   return PDFS_OK;

@@ -348,6 +348,7 @@ hipError_t launch_finish_round(const Problem& P, const Work& w, int phase_mask, 
                                hipStream_t s);
 // Lazy rounds: the run's lists from the pair list, then a launch per round.
 int lazy_levels(int h);
+hipError_t launch_list_pairs(const Work& w, const LazyWork& L, int nA_max, hipStream_t s);
 hipError_t launch_lazy_begin(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
 hipError_t launch_lazy_deal(const Problem& P, const Work& w, const LazyWork& L, hipStream_t s);
 // Launch n of the run: commits the answer of launch n - 1, then searches the

@@ -60,3 +60,33 @@ def test_noalloc_lazy(pdfs, G, nt, h):  # noqa: F811
             ref, _ = s.best(h, 1, 10, u)
             got, _ = s.best_noalloc(h, 1, 10, u)
             assert got == ref
+
+
+# Pair lists made from the genes' samples: genes at the edges of the slice widths
+# (3 | 4, 15 | 16, 127 | 128 samples), spans of 64 words with more pairs than a wave
+# stages, more genes than the launch has waves, two genes, and lists regrown from 64.
+@pytest.mark.parametrize("G,nt,per_gene,heavy", [
+    (2, 64, 1, (64,)), (63, 64, 2, (3, 4)), (65, 65, 1, (65,)),
+    (700, 300, 1, (3, 4, 15, 16, 127, 128, 300)),
+    (4200, 600, 9, (600,)),
+    (9000, 1280, 1, (1280, 127, 128)),
+])
+@pytest.mark.parametrize("mode", ["bound", "empty"])
+def test_pair_lists_by_samples(pdfs, G, nt, per_gene, heavy, mode):  # noqa: F811
+    rng = np.random.Generator(np.random.PCG64(91))
+    rows = np.zeros((G, nt), bool)
+    for g in range(G):
+        k = heavy[g] if g < len(heavy) else per_gene
+        rows[g, rng.choice(nt, k, replace=False)] = True
+    T = synth.pack_rows(rows)
+    N = synth.pack_rows(rng.random((G, 30)) < 0.05)
+    # (the oracle's empty-mode walk of h = 3 takes minutes at the larger sizes)
+    for h in range(2, min(G, 2 if mode == "empty" and G > 1000 else 3) + 1):
+        exp = cpu.wsc(T, N, nt, 30, h, 1, 10, mode=mode, max_rounds=3)
+        for cap in (0, 64):
+            with pdfs.Solver(T, N, nt, 30, mode, pair_cap=cap) as s:
+                got, st, final = s.wsc(h, 1, 10, 0, 3)
+                _same_rounds(got, exp.rounds)
+                assert np.array_equal(final, exp.final_uncovered)
+                if mode == "empty":
+                    _counters_equal(st, exp.counters, h)
