@@ -963,7 +963,8 @@ int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds,
   return PDFS_OK;
 }
 
-size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int prune_mode) {
+size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int prune_mode,
+                       bool lazy) {
   if (prune_mode == PDFS_PRUNE_NONE) nA_max = G;   // exhaustive mode: every gene is a row
   const size_t wt = (size_t)words(n_tumor), wn = (size_t)(n_normal > 0 ? words(n_normal) : 1);
   const size_t rows = (size_t)((nA_max + 127) / 128 * 128 + 128);
@@ -974,11 +975,11 @@ size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int 
   b += (size_t)kSlotPhases * kPersistBlocks * kTallyN * 8;
   if (h >= 3) {
     const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
-    b += pairs * 8;
-    if (prune_mode == PDFS_PRUNE_NONE)
+    b += pairs * 8 * (!lazy && prune_mode == PDFS_PRUNE_BOUND ? 2 : 1);
+    if (!lazy || prune_mode == PDFS_PRUNE_NONE)
       b += (size_t)item_cap_for(pairs) * sizeof(Item) + (size_t)kSeedCap * 8;
   }
-  if (h >= 2 && prune_mode != PDFS_PRUNE_NONE) {   // lazy rounds
+  if (lazy && h >= 2 && prune_mode != PDFS_PRUNE_NONE) {   // lazy rounds
     const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
     const size_t nw = (size_t)lazy_waves(pairs), gw = (size_t)(nA_max + 63) / 64;
     if (h == 2) b += pairs * 8;

@@ -875,6 +875,7 @@ struct Request {
   pdfs_matrix m{};
   std::vector<uint64_t> T, N;   // copies, row stride = words
   size_t bytes = 0;              // estimated device footprint
+  bool walked = false;           // the budget holds walked rounds' lists only
   Clock::time_point t_submit, t_done;
   pdfs_ctx* ctx = nullptr;
   RoundState* pinned = nullptr;
@@ -996,7 +997,10 @@ bool admit_one(pdfs_server* s) {
   o.stream = s->admit_stream;
   o.flags = PDFS_OPT_GRAPHS;
   int32_t rc = create_ctx(&r->m, &o, &r->ctx, r->pinned, true, s->pool);
-  if (rc == PDFS_OK) r->ctx->want_counters = false;   // answers carry no statistics
+  if (rc == PDFS_OK) {
+    r->ctx->want_counters = false;   // answers carry no statistics
+    r->ctx->lazy_off = r->walked;
+  }
   if (rc == PDFS_OK) {
     r->ctx->stream = s->streams[s->next_stream++ % (int)s->streams.size()];
     rc = check_call(r->ctx, r->h, r->p, r->q);
@@ -1176,7 +1180,14 @@ int32_t pdfs_server_submit(pdfs_server* s, const pdfs_matrix* m, int32_t h, uint
   r->m.tumor_stride_words = wt;
   r->m.normal = wn ? r->N.data() : nullptr;
   r->m.normal_stride_words = wn;
-  r->bytes = footprint_bytes(m->G, m->n_tumor, m->n_normal, nA, h, s->prune_mode);
+  r->bytes = footprint_bytes(m->G, m->n_tumor, m->n_normal, nA, h, s->prune_mode, true);
+  // Lazy rounds keep 17 bytes a pair, walked ones of h = 2 none: a budget that
+  // holds only those takes them (h <= 4; deeper walks need more, not less).
+  if (r->bytes > s->budget && h <= 4) {
+    const size_t b = footprint_bytes(m->G, m->n_tumor, m->n_normal, nA, h, s->prune_mode, false);
+    r->walked = b <= s->budget;
+    if (r->walked) r->bytes = b;
+  }
   std::lock_guard<std::mutex> g(s->mu);
   if (r->bytes > s->budget) {
     s->err = "request footprint " + std::to_string(r->bytes) + " B above the server budget " +

@@ -100,7 +100,7 @@ struct pdfs_ctx {
   pdfs::CountWork cw = {};
   size_t cw_tab_n = 0, cw_seg_n = 0, cw_bits_n = 0, cw_q_n = 0, cw_pref_n = 0;
   unsigned long long tumor_bits = 0;   // tumour mutations of the cohort
-  bool lazy_off = false;               // the tuner times the other rounds
+  bool lazy_off = false;               // walked rounds (the tuner; a tight server budget)
   bool want_counters = true;           // callers that report no counters skip them
   bool two_phase = false;              // this run uses the two-phase path
   pdfs::Slot* slots = nullptr;
@@ -210,6 +210,8 @@ int32_t enqueue_front(pdfs_ctx* c, const Problem& P, const Work& w, int run_roun
 // device current.
 void scratch_init(int device);
 // Device bytes a context of this shape will hold (admission control).
-size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int prune_mode);
+// (lazy: with the lists of lazy rounds, else with those of walked ones)
+size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int prune_mode,
+                       bool lazy);
 
 }  // namespace pdfs

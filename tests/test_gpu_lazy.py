@@ -4,6 +4,8 @@ pairs with more samples than one mask word (the general walk), more candidates
 than a level list holds, every list depth, candidate words past one wave, and
 runs resumed from a mask on the same context.  Results are whole numbers, so
 the comparison is equality."""
+import time
+
 import numpy as np
 import pytest
 
@@ -90,3 +92,22 @@ def test_pair_lists_by_samples(pdfs, G, nt, per_gene, heavy, mode):  # noqa: F81
                 assert np.array_equal(final, exp.final_uncovered)
                 if mode == "empty":
                     _counters_equal(st, exp.counters, h)
+
+
+# A server budget that holds a walked cover of h = 2 but not the lazy rounds' 19 MB
+# of pairs: the request is accepted and solved.
+@pytest.mark.parametrize("budget", [8 << 20, 1 << 30])
+def test_served_h2_tight_budget(pdfs, budget):  # noqa: F811
+    I = synth.random_tiny(45, 1500, 200, 40, 0.02, 2)
+    T, N = I.packed()
+    exp = cpu.wsc(T, N, 200, 40, 2, 1, 10, mode="bound")
+    srv = pdfs.pdfs_server_create("bound", 0, budget, 2)
+    try:
+        t = pdfs.pdfs_server_submit(srv, T, N, 200, 40, 2, 1, 10)
+        deadline = time.time() + 60
+        r = None
+        while r is None and time.time() < deadline:
+            r = pdfs.pdfs_server_poll(srv, t, cap=201)
+        _same_rounds(r[0], exp.rounds)
+    finally:
+        pdfs.pdfs_server_destroy(srv)
