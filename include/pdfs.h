@@ -116,11 +116,10 @@ typedef struct {
     int32_t pair_cap;   /* initial capacity of the pair list (pairs);
                            <= 0: the default, max(2^21, 128 x the active
                            genes of the first round), at most every pair.
-                           A pair table (one per run; one per round of an
-                           exhaustive run) that emits more pairs grows the
-                           list to its count + 1/4 and is made again, so
-                           this only trades memory for an occasional
-                           repeated table. */
+                           A longer list (made once per run; once per round
+                           of an exhaustive run) grows it to its count + 1/4
+                           and is made again, so this only trades memory for
+                           an occasional repeated listing. */
 } pdfs_options;
 
 /* One chosen combination (one greedy round). */

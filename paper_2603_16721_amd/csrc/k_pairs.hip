@@ -12,6 +12,8 @@
 //  h > 2: the epilogue emits every pair with C > 0 inside Alg. 2's loop
 //         bounds as a 64-bit record (a | b<<16 | C<<32); these are the
 //         subtrees the depth-first kernels expand.
+//         (A lazy run of a sparse cohort lists them from the genes' samples
+//         instead, in less time than the tiles take.)
 //
 // Tiles: 128x128 block tiles of the upper triangle, staged through LDS.  A
 // and B fragments use the same byte-to-k assignment, so the sum over k is the
