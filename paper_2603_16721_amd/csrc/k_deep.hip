@@ -22,7 +22,11 @@
 // best's) are scored S = p*TP + q*(N_n - FP) and compared under (S desc,
 // tuple asc); the normal join of a prefix is formed at its first such leaf.
 //
-// Counters: non-empty prefixes per depth,
+// Bound mode: a prefix whose score bound p*TP + q*N_n cannot reach the
+// round's incumbent (or ties it with larger first two indices) is not
+// extended; leaves that become a lane's best raise the incumbent.
+//
+// Counters: non-empty prefixes per depth, bound-pruned prefixes per depth,
 // and for every extended depth-l prefix the depth-(l+1) visits of Alg. 2's
 // loop bounds (sorted indices in (idx(g_l), G-h+l]), per wave in LDS, then
 // one atomic per wave and depth.  The depth-2 and depth-3 visit counts come
@@ -39,14 +43,16 @@ namespace {
 
 constexpr int kLv = kMaxH - 3;   // rings of depths 3..kMaxH-1, frames of depths 3..kMaxH-1
 
-template <int W64>
-__global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
+// kBound: bound mode (an instance of its own, so that the other modes do
+// not carry its registers)
+template <int W64, bool kBound>
+__global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w, int phase) {
   constexpr int W = 2 * W64;
   constexpr int KR = W <= 4 ? 4 : (W <= 16 ? 2 : 1);
   constexpr int kNone = 0x7fffffff;   // "last index" of an idle lane: masks every candidate
   constexpr int kWib = kBlock / kWave;
   __shared__ int s_amax[kMaxH + 1];
-  __shared__ unsigned long long s_cnt[kWib][2][kMaxH + 1];   // non-empty, visited
+  __shared__ unsigned long long s_cnt[kWib][3][kMaxH + 1];   // non-empty, visited, bound-pruned
   // per ring: entries taken, entries queued (running counts, modulo 2^32)
   __shared__ uint32_t s_q[kWib][2][kLv];
   __shared__ int s_f[kWib][2][kLv];   // per suspended frame: next candidate, end
@@ -55,18 +61,24 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
   const int lane = threadIdx.x & 63;
   const int wib = threadIdx.x >> 6;
   if (threadIdx.x <= kMaxH) s_amax[threadIdx.x] = st->amax[threadIdx.x];
-  if (lane <= kMaxH) s_cnt[wib][0][lane] = s_cnt[wib][1][lane] = 0ull;
+  if (lane <= kMaxH) s_cnt[wib][0][lane] = s_cnt[wib][1][lane] = s_cnt[wib][2][lane] = 0ull;
   if (lane < kLv) s_q[wib][0][lane] = s_q[wib][1][lane] = 0u;
   __syncthreads();
   unsigned long long* cne = s_cnt[wib][0];
   unsigned long long* cvis = s_cnt[wib][1];
+  unsigned long long* cbp = s_cnt[wib][2];
   uint32_t* q_taken = s_q[wib][0];
   uint32_t* q_queued = s_q[wib][1];
   const int h = P.h;
   const bool all_pre = P.mode == kPruneNone;
+  constexpr bool bound = kBound;
+  unsigned long long inc = 0;   // the round's incumbent key as last seen by this lane
   const bool lit = P.tn_literal != 0;
-  const unsigned long long* __restrict__ plist = w.work_pairs;
-  const unsigned long long npairs = st->n_work_pairs;
+  // bound mode: phase 1 expands the seed list, phase 2 the filtered work
+  // list; the other modes run phase 2 over every pair
+  const unsigned long long* __restrict__ plist = phase == 1 ? w.seed_pairs : w.work_pairs;
+  const unsigned long long npairs =
+      phase == 1 ? (st->n_seed < kSeedCap ? st->n_seed : kSeedCap) : st->n_work_pairs;
   const unsigned long long nit = st->n_items;
   const uint32_t nitems = (uint32_t)uniform((int)(nit < w.item_cap ? nit : w.item_cap));
   const int nA_all = uniform(st->nA);
@@ -75,6 +87,7 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
   const uint32_t* __restrict__ NA = w.NA;
   cu32* TAc = (cu32*)w.TA;
   cu32* NAc = (cu32*)w.NA;
+  const int qN = P.q * P.n_normal;
 
   // this wave's rings and frames
   constexpr size_t kRingWords = (size_t)(W + kMaxH) * kDeepQ;
@@ -128,6 +141,7 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
       if (v && i == l - 1) last = pix[i];
     }
     q_taken[l - 3] = qh + (uint32_t)n;
+    if (bound) inc = load_incumbent(st);
     L = l + 1;
     d = wave_first(last == kNone ? kNone : last + 1);
     hi = s_amax[L];
@@ -153,6 +167,7 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
     last = (int)f[(size_t)(W + kMaxH) * kWave + lane];
     d = uniform(s_f[wib][0][L - 3]);
     hi = uniform(s_f[wib][1][L - 3]);
+    if (bound) inc = load_incumbent(st);
   };
 
   // Inner depth L < h: candidates from d on until hi or until the depth-L
@@ -175,6 +190,17 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
       const unsigned long long mk = __ballot(dd > last);
       const unsigned long long mn = __ballot(any != 0) & mk;
       unsigned long long mx = all_pre ? mk : mn;   // extended
+      if (bound && mx) {
+        int t = 0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) t += __popc(yc[k]);
+        const unsigned long long md =
+            __ballot(((mx >> lane) & 1ull) && dominated(P.p * t + qN, pix[0], pix[1], inc));
+        if (md) {
+          mx &= ~md;
+          if (lane == 0) cbp[l] += (unsigned long long)__popcll(md);
+        }
+      }
       if (lane == 0) {
         cne[l] += (unsigned long long)__popcll(mn);
         // children of an extended prefix: the sorted indices (idx(dd), G-h+l]
@@ -278,6 +304,15 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
 #pragma unroll
       for (int i = 0; i < kMaxH; ++i)
         bidx[i] = take_it ? (i < h - 1 ? pix[i] : (i == h - 1 ? dd : 0)) : bidx[i];
+      if (take_it) {
+        if (bound) {
+          const unsigned long long key = leaf_key(sc, pix[0], pix[1]);
+          if (key > inc) {
+            const unsigned long long old = atomicMax(&st->incumbent, key);
+            inc = old > key ? old : key;
+          }
+        }
+      }
       // the best now comes from this prefix (or precedes it): later leaves
       // of the prefix lose ties
       thr = min_tp_for(P, bs, bs < 0 || prefix_first());
@@ -350,12 +385,27 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
             const int c_lo = uniform((int)w.items[it].c_lo);
             const int c_hi = uniform((int)w.items[it].c_hi);
             const uint32_t batch = (uint32_t)uniform((int)w.items[it].batch);
+            const uint32_t first_chunk = (uint32_t)uniform((int)w.items[it].pad) & 1u;
             const unsigned long long pi = (unsigned long long)batch * kPairBatch + lane;
             bool valid = pi < npairs;
             const unsigned long long e = valid ? plist[pi] : 0ull;
             const int a = (int)(e & 0xffff);
             const int b = (int)((e >> 16) & 0xffff);
+            const int ct = (int)((e >> 32) & 0xffff);
             valid = valid && a < b && b < nA_all;   // list entries always satisfy this
+            if (bound) {
+              // the pair's own bound against the incumbent; its depth-3
+              // visits (sorted indices (idx(b), G-h+2]) once per pair
+              inc = load_incumbent(st);
+              const bool drop = valid && dominated(P.p * ct + qN, a, b, inc);
+              const unsigned long long md = __ballot(drop);
+              if (first_chunk && lane == 0) cbp[2] += (unsigned long long)__popcll(md);
+              unsigned long long v3 = (valid && !drop) ? (unsigned long long)(P.G - h + 2 - w.act[b]) : 0ull;
+#pragma unroll
+              for (int o = 32; o > 0; o >>= 1) v3 += __shfl_xor(v3, o, 64);
+              if (first_chunk && lane == 0) cvis[3] += v3;
+              valid = valid && !drop;
+            }
             const int ra = valid ? a : 0, rb = valid ? b : 0;   // in-range rows for idle lanes
 #pragma unroll
             for (int k = 0; k < W; ++k)
@@ -422,16 +472,17 @@ __global__ __launch_bounds__(256) void k_dfs_deep(Problem P, Work w) {
 #pragma unroll
     for (int i = 0; i < kMaxH; ++i) sl.idx[i] = bidx[i];
   }
-  block_best_to(&w.slots[(size_t)2 * kSlotsPerPhase + blockIdx.x], sl);
+  block_best_to(&w.slots[(size_t)phase * kSlotsPerPhase + blockIdx.x], sl);
   // counters: one atomic per wave and depth
   if (lane == 0) {
-    for (int l = 3; l <= h; ++l) {
-      if (cne[l]) atomicAdd(&st->cnt.nonempty[l], cne[l]);
-      if (cvis[l]) atomicAdd(&st->cnt.visited[l], cvis[l]);
+    for (int l = 2; l <= h; ++l) {
+      if (l >= 3 && cne[l]) atomicAdd(&st->cnt.nonempty[l], cne[l]);
+      if (l >= 3 && cvis[l]) atomicAdd(&st->cnt.visited[l], cvis[l]);
+      if (cbp[l]) atomicAdd(&st->cnt.bound_pruned[l], cbp[l]);
     }
   }
   for (int vb = blockIdx.x + gridDim.x; vb < kPersistBlocks; vb += gridDim.x)
-    if (threadIdx.x == 0) w.slots[(size_t)2 * kSlotsPerPhase + vb] = empty_slot();
+    if (threadIdx.x == 0) w.slots[(size_t)phase * kSlotsPerPhase + vb] = empty_slot();
 }
 
 template <typename K>
@@ -444,21 +495,28 @@ int resident_deep(K kernel) {
   return per_cu;
 }
 
-template <int W64>
-hipError_t launch_deep_w(const Problem& P, const Work& w, hipStream_t s) {
-  static const int per_cu = resident_deep(&k_dfs_deep<W64>);
+template <int W64, bool kBound>
+hipError_t launch_deep_b(const Problem& P, const Work& w, int phase, hipStream_t s) {
+  static const int per_cu = resident_deep(&k_dfs_deep<W64, kBound>);
   int g = per_cu * (P.n_cu > 0 ? P.n_cu : 1);
   if (g > kPersistBlocks) g = kPersistBlocks;
-  k_dfs_deep<W64><<<g, kBlock, 0, s>>>(P, w);
+  k_dfs_deep<W64, kBound><<<g, kBlock, 0, s>>>(P, w, phase);
   return hipGetLastError();
+}
+
+template <int W64>
+hipError_t launch_deep_w(const Problem& P, const Work& w, int phase, hipStream_t s) {
+  return P.mode == kPruneBound ? launch_deep_b<W64, true>(P, w, phase, s)
+                               : launch_deep_b<W64, false>(P, w, phase, s);
 }
 
 // 32-bit words of the rings and frames a launch at row width w64 uses: one
 // area per wave of its grid (resident blocks x compute units, at most
-// kPersistBlocks blocks).
+// kPersistBlocks blocks), the larger of the two instantiations.
 template <int W64>
 size_t deep_words_w(int n_cu) {
-  static const int per_cu = resident_deep(&k_dfs_deep<W64>);
+  static const int per_cu = std::max(resident_deep(&k_dfs_deep<W64, false>),
+                                     resident_deep(&k_dfs_deep<W64, true>));
   size_t g = (size_t)per_cu * (size_t)(n_cu > 0 ? n_cu : 1);
   if (g > (size_t)kPersistBlocks) g = kPersistBlocks;
   const size_t W = 2 * (size_t)W64;
@@ -478,12 +536,14 @@ size_t deep_ring_words(int w64_max, int n_cu) {
   return m;
 }
 
-hipError_t launch_dfs_deep(const Problem& P, const Work& w, hipStream_t s) {
-  if (!w.deepq || P.h < 5 || P.h > kMaxH || P.mode == kPruneBound) return hipErrorInvalidValue;
+hipError_t launch_dfs_deep(const Problem& P, const Work& w, int phase, hipStream_t s) {
+  if (!w.deepq || P.h < 5 || P.h > kMaxH || phase < 1 || phase > 2 ||
+      (phase == 1 && P.mode != kPruneBound))
+    return hipErrorInvalidValue;
   switch (w.w64) {
 #define PDFS_CASE(n) \
   case n:            \
-    return launch_deep_w<n>(P, w, s);
+    return launch_deep_w<n>(P, w, phase, s);
     PDFS_CASE(1) PDFS_CASE(2) PDFS_CASE(3) PDFS_CASE(4) PDFS_CASE(5) PDFS_CASE(6)
     PDFS_CASE(7) PDFS_CASE(8) PDFS_CASE(10) PDFS_CASE(12) PDFS_CASE(14) PDFS_CASE(16)
     PDFS_CASE(18) PDFS_CASE(20)
