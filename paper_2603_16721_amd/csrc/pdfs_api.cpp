@@ -34,12 +34,20 @@ int32_t fail(pdfs_ctx* c, int32_t code, const std::string& msg) {
 
 // Device allocation of a context: stream-ordered on the context's stream when
 // async_alloc is set (no device-wide synchronisation on free), plain otherwise.
+// On failure *p is NULL and no error is left for the next launch to report.
 hipError_t dmalloc(pdfs_ctx* c, void** p, size_t bytes) {
   bytes += 256;
+  hipError_t e;
+  if (c->async_alloc && c->pool) e = hipMallocFromPoolAsync(p, bytes, c->pool, c->stream);
+  else if (c->async_alloc) e = hipMallocAsync(p, bytes, c->stream);
+  else e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+    return e;
+  }
   c->bytes += bytes;
-  if (c->async_alloc && c->pool) return hipMallocFromPoolAsync(p, bytes, c->pool, c->stream);
-  if (c->async_alloc) return hipMallocAsync(p, bytes, c->stream);
-  return hipMalloc(p, bytes);
+  return e;
 }
 
 void dfree(pdfs_ctx* c, void* p) {
@@ -51,6 +59,19 @@ void dfree(pdfs_ctx* c, void* p) {
 template <typename T>
 hipError_t dalloc(pdfs_ctx* c, T** p, size_t n) {
   return dmalloc(c, reinterpret_cast<void**>(p), n * sizeof(T));
+}
+
+// A buffer of at least n entries at *p, of which it holds *have; the contents
+// are not kept.  *have is the true size whatever fails.
+template <typename T>
+int32_t hold(pdfs_ctx* c, T** p, size_t* have, size_t n) {
+  if (*p && *have >= n) return PDFS_OK;
+  dfree(c, *p);
+  *p = nullptr;
+  *have = 0;
+  CK(c, dalloc(c, p, n));
+  *have = n;
+  return PDFS_OK;
 }
 
 // Several buffers in one allocation, kept until the context goes (a request's
@@ -83,8 +104,8 @@ hipError_t dalloc_kept(pdfs_ctx* c, std::initializer_list<Part> parts) {
 void release(pdfs_ctx* c) {
   void* ptrs[] = {c->TA, c->NA, c->A8, c->N8, c->pairs, c->work_pairs, c->seed_pairs, c->items,
                   c->tri, c->tri_s, c->tri_rank, c->c_hist, c->deepq, c->lz.B, c->lz.list,
-                  c->lz.cmax, c->lz.bits, c->cw.pref, c->cw.q, c->cw.seg_v, c->cw.seg_w,
-                  c->cw.tab_v, c->cw.tab_w, c->cw.bits};
+                  c->lz.cmax, c->lz.bits, c->cw.pref, c->cw.q, c->cw.seg_v, c->cw.tab_v,
+                  c->cw.bits};
   for (void* p : ptrs) dfree(c, p);
   for (void* p : c->blocks) dfree(c, p);
   c->blocks.clear();
@@ -100,6 +121,16 @@ void release(pdfs_ctx* c) {
 }
 
 int words(int n) { return (n + 63) / 64; }
+
+// The row-indexed buffers, where a change of size (or a failure in it) left none
+// (row padding: whole 128-row MFMA block tiles).
+static int32_t ensure_rows(pdfs_ctx* c) {
+  const size_t rows = (size_t)((c->nA_max + 127) / 128 * 128 + 128);
+  if (!c->TA) CK(c, dalloc(c, &c->TA, rows * 2 * (size_t)c->w64_max));
+  if (!c->NA) CK(c, dalloc(c, &c->NA, rows * (size_t)kMaxWN32));
+  if (!c->A8) CK(c, dalloc(c, &c->A8, rows * (size_t)unpacked_row_bytes(c->w64_max)));
+  return PDFS_OK;
+}
 
 // Exhaustive mode makes every gene a row of the round (its row over the
 // uncovered samples may be empty), so the row-indexed buffers must hold G rows
@@ -118,16 +149,12 @@ static int32_t grow_for_all_genes(pdfs_ctx* c) {
     *b = nullptr;
   }
   c->pair_cap = c->item_cap = c->tri_cap = 0;
-  c->lz_list_n = 0;
+  c->lz_list_n = c->lz_cmax_n = 0;
   c->two_phase = false;
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
   c->graphs.clear();
   c->nA_max = c->G;
-  const size_t rows = (size_t)((c->nA_max + 127) / 128 * 128 + 128);
-  CK(c, dalloc(c, &c->TA, rows * 2 * (size_t)c->w64_max));
-  CK(c, dalloc(c, &c->NA, rows * (size_t)kMaxWN32));
-  CK(c, dalloc(c, &c->A8, rows * (size_t)unpacked_row_bytes(c->w64_max)));
-  return PDFS_OK;
+  return ensure_rows(c);
 }
 
 // Pair-list capacity: every pair of nA rows at most; the default start is
@@ -151,26 +178,32 @@ static unsigned long long item_cap_for(unsigned long long n) {
 // (Re)allocates the pair list for n pairs, and the work copy and item list
 // where they were in use; the lazy rounds' shares and the captured rounds
 // holding the old addresses are dropped and re-made on demand.
-static int32_t alloc_pair_lists(pdfs_ctx* c, unsigned long long n) {
-  const bool work = c->work_pairs != nullptr, items = c->items != nullptr;
+static void drop_pair_lists(pdfs_ctx* c) {
   void** bufs[] = {(void**)&c->pairs, (void**)&c->work_pairs, (void**)&c->items,
                    (void**)&c->lz.list, (void**)&c->lz.cmax};
   for (void** b : bufs) {
     dfree(c, *b);
     *b = nullptr;
   }
-  c->lz_list_n = 0;
+  c->lz_list_n = c->lz_cmax_n = 0;
+  c->pair_cap = c->item_cap = 0;
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
   c->graphs.clear();
-  c->pair_cap = c->item_cap = 0;
-  CK(c, dalloc(c, &c->pairs, (size_t)n));
-  if (work) CK(c, dalloc(c, &c->work_pairs, (size_t)n));
-  if (items) {
-    const unsigned long long ic = item_cap_for(n);
-    CK(c, dalloc(c, &c->items, (size_t)ic));
-    c->item_cap = ic;
-  }
+}
+
+// All of them or none: a context that ran out of memory here holds no list, and
+// its next call makes them from the start.
+static int32_t alloc_pair_lists(pdfs_ctx* c, unsigned long long n) {
+  const bool work = c->work_pairs != nullptr, items = c->items != nullptr;
+  drop_pair_lists(c);
+  const unsigned long long ic = items ? item_cap_for(n) : 0;
+  hipError_t e = dalloc(c, &c->pairs, (size_t)n);
+  if (e == hipSuccess && work) e = dalloc(c, &c->work_pairs, (size_t)n);
+  if (e == hipSuccess && items) e = dalloc(c, &c->items, (size_t)ic);
+  if (e != hipSuccess) drop_pair_lists(c);
+  CK(c, e);
   c->pair_cap = n;
+  c->item_cap = ic;
   return PDFS_OK;
 }
 
@@ -181,15 +214,6 @@ static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
   L.seg = lazy_seg(c->pair_cap, L.nw);
   L.gw = (c->nA_max + 63) / 64 > 0 ? (c->nA_max + 63) / 64 : 1;
   L.levels = lazy_levels(h);
-  auto grow = [&](auto** p, size_t& have, size_t n) -> int32_t {
-    if (*p && have >= n) return PDFS_OK;
-    dfree(c, *p);
-    *p = nullptr;
-    have = 0;
-    CK(c, dalloc(c, p, n));
-    have = n;
-    return PDFS_OK;
-  };
   if (!L.Uc) {
     CK(c, dalloc_kept(c, {part(&L.Uc, kMaxW64), part(&L.cursor, kMaxCount + 1),
                           part(&L.pool, kLazyWaves), part(&L.wins, 3 * (kLazyWaves / 4)),
@@ -199,16 +223,10 @@ static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
                           part(&L.shard, 2 * kIncShards * kCursorStride)}));
   }
   const size_t ln = (size_t)L.nw * L.seg;
-  if (!L.list || c->lz_list_n < ln) {
-    dfree(c, L.cmax);
-    L.cmax = nullptr;
-    int32_t rc = grow(&L.list, c->lz_list_n, ln);
-    if (rc != PDFS_OK) return rc;
-    CK(c, dalloc(c, &L.cmax, ln / kWave));
-  }
-  int32_t rc = grow(&L.B, c->lz_b_n, (size_t)64 * w64 * L.gw);
-  if (rc != PDFS_OK) return rc;
-  if (h >= 4) rc = grow(&L.bits, c->lz_bits_n, (size_t)L.nw * L.levels * L.gw);
+  int32_t rc = hold(c, &L.list, &c->lz_list_n, ln);
+  if (rc == PDFS_OK) rc = hold(c, &L.cmax, &c->lz_cmax_n, ln / kWave);
+  if (rc == PDFS_OK) rc = hold(c, &L.B, &c->lz_b_n, (size_t)64 * w64 * L.gw);
+  if (rc == PDFS_OK && h >= 4) rc = hold(c, &L.bits, &c->lz_bits_n, (size_t)L.nw * L.levels * L.gw);
   return rc;
 }
 
@@ -235,15 +253,6 @@ static bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds) {
 // The counters' buffers for a run of `rounds` rounds of depth h.
 static int32_t ensure_count(pdfs_ctx* c, int h, int w64, int rounds) {
   CountWork& C = c->cw;
-  auto grow = [&](auto** p, size_t& have, size_t n) -> int32_t {
-    if (*p && have >= n) return PDFS_OK;
-    dfree(c, *p);
-    *p = nullptr;
-    have = 0;
-    CK(c, dalloc(c, p, n));
-    have = n;
-    return PDFS_OK;
-  };
   if (!C.order) {
     CK(c, dalloc_kept(c, {part(&C.order, 64 * kMaxW64), part(&C.tt, 64 * kMaxW64),
                           part(&C.wc, kCountMaxT + 1), part(&C.kc, 64 * kMaxW64),
@@ -252,24 +261,22 @@ static int32_t ensure_count(pdfs_ctx* c, int h, int w64, int rounds) {
                           part(&C.tg, (size_t)count_segments(c->G) * 512)}));
   }
   C.q_n = (size_t)c->tumor_bits;
-  int32_t rc = grow(&C.pref, c->cw_pref_n, (size_t)64 * w64 * c->lz.gw);
+  int32_t rc = hold(c, &C.pref, &c->cw_pref_n, (size_t)64 * w64 * c->lz.gw);
   const size_t sums = count_sums(h);
-  if (rc == PDFS_OK && sums > 0) rc = grow(&C.q, c->cw_q_n, sums * C.q_n);
+  if (rc == PDFS_OK && sums > 0) rc = hold(c, &C.q, &c->cw_q_n, sums * C.q_n);
   C.sv = C.q ? C.q + C.q_n : nullptr;
   C.sw = C.q ? C.q + 2 * C.q_n : nullptr;
-  if (rc == PDFS_OK && (h == 3 || h == 4)) {
+  if (h == 3 || h == 4) {   // both tables of a kind in one buffer
     const size_t seg = (size_t)count_segments(c->nA_max) * (rounds + 1);
     const size_t tab = count_table_rows(c->nA_max) * (size_t)(rounds + 1);
-    size_t n = c->cw_seg_n;
-    rc = grow(&C.seg_v, n, seg);
-    if (rc == PDFS_OK) rc = grow(&C.seg_w, c->cw_seg_n, seg);
-    n = c->cw_tab_n;
-    if (rc == PDFS_OK) rc = grow(&C.tab_v, n, tab);
-    if (rc == PDFS_OK) rc = grow(&C.tab_w, c->cw_tab_n, tab);
+    if (rc == PDFS_OK) rc = hold(c, &C.seg_v, &c->cw_seg_n, 2 * seg);
+    if (rc == PDFS_OK) rc = hold(c, &C.tab_v, &c->cw_tab_n, 2 * tab);
+    C.seg_w = C.seg_v ? C.seg_v + seg : nullptr;
+    C.tab_w = C.tab_v ? C.tab_v + tab : nullptr;
   }
   C.waves = kCountWaves / c->lz.nw * c->lz.nw;
   if (rc == PDFS_OK && h >= 4)
-    rc = grow(&C.bits, c->cw_bits_n, (size_t)C.waves * c->lz.levels * c->lz.gw);
+    rc = hold(c, &C.bits, &c->cw_bits_n, (size_t)C.waves * c->lz.levels * c->lz.gw);
   return rc;
 }
 
@@ -292,8 +299,9 @@ static int32_t regrow_pairs(pdfs_ctx* c, unsigned long long emitted) {
 // Allocates the pair list, item list and normal bytes when a call first needs
 // them (lazy: the lazy rounds' pair list only).
 int32_t ensure_workspace(pdfs_ctx* c, int h, bool lazy) {
-  if (c->prune_mode == PDFS_PRUNE_NONE) {
-    const int32_t rc = grow_for_all_genes(c);
+  {
+    int32_t rc = c->prune_mode == PDFS_PRUNE_NONE ? grow_for_all_genes(c) : PDFS_OK;
+    if (rc == PDFS_OK) rc = ensure_rows(c);
     if (rc != PDFS_OK) return rc;
   }
   if (h >= (lazy ? 2 : 3) && !c->pairs) {
@@ -630,10 +638,7 @@ int32_t grow_row_width(pdfs_ctx* c, int w64) {
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
   c->graphs.clear();
   c->w64_max = w64;
-  const size_t rows = (size_t)((c->nA_max + 127) / 128 * 128 + 128);
-  CK(c, dalloc(c, &c->TA, rows * 2 * (size_t)c->w64_max));
-  CK(c, dalloc(c, &c->A8, rows * (size_t)unpacked_row_bytes(c->w64_max)));
-  return PDFS_OK;
+  return ensure_rows(c);
 }
 
 int32_t prepare_run(pdfs_ctx* c, int h, int n_unc) {
@@ -1217,11 +1222,8 @@ int32_t create_ctx(const pdfs_matrix* m, const pdfs_options* opt, pdfs_ctx** out
     c->nA_max = c->h_st->nA;
     c->tumor_bits = c->h_st->tumor_bits > 0 ? c->h_st->tumor_bits : 1;
   }
-  // row padding: whole 128-row MFMA block tiles
-  const size_t rows = (size_t)((c->nA_max + 127) / 128 * 128 + 128);
-  CKC(dalloc(c, &c->TA, rows * 2 * (size_t)c->w64_max));
-  CKC(dalloc(c, &c->NA, rows * (size_t)kMaxWN32));
-  CKC(dalloc(c, &c->A8, rows * (size_t)unpacked_row_bytes(c->w64_max)));
+  const int32_t rc = ensure_rows(c);
+  if (rc != PDFS_OK) return bail(rc);
   *out = c;
   return PDFS_OK;
 #undef CKC

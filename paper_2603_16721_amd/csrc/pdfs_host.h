@@ -95,7 +95,7 @@ struct pdfs_ctx {
   unsigned long long tri_cap = 0;
   // lazy rounds: buffers sized by the pair list, the row width and h
   pdfs::LazyWork lz = {};
-  size_t lz_list_n = 0, lz_b_n = 0, lz_bits_n = 0;   // entries held by list, B and bits
+  size_t lz_list_n = 0, lz_cmax_n = 0, lz_b_n = 0, lz_bits_n = 0;   // entries held
   // counters of an empty-intersection run, made after its rounds
   pdfs::CountWork cw = {};
   size_t cw_tab_n = 0, cw_seg_n = 0, cw_bits_n = 0, cw_q_n = 0, cw_pref_n = 0;
