@@ -105,8 +105,8 @@ typedef struct {
 #define PDFS_OPT_GRAPHS 2         /* capture one round as a HIP graph per row width
                                      and replay it (needs a non-NULL stream; ignored
                                      together with PDFS_OPT_TIME_KERNELS, and where a
-                                     round is one launch: runs of h >= 2 under empty
-                                     or bound pruning) */
+                                     round is one launch: most runs of h >= 2 under
+                                     empty or bound pruning) */
 
 typedef struct {
     int32_t prune_mode; /* PDFS_PRUNE_*                                  */
@@ -192,9 +192,8 @@ int32_t pdfs_set_prune_mode(pdfs_ctx *ctx, int32_t prune_mode);
  * words, NULL = every tumour sample).  alpha = alpha_p / alpha_q with
  * alpha_q >= 1.  Returns PDFS_OK with *out filled, PDFS_NO_COMBO when no
  * subset has TP >= 1 (out->h = 0), or an error.  stats may be NULL; it is
- * overwritten.  h: 1..PDFS_MAX_H (h = 5..9 expand every depth below the
- * pair level wave-wide through per-depth prefix rings; the answers are the
- * same in every prune mode). */
+ * overwritten.  h: 1..PDFS_MAX_H; the answers are the same in every prune
+ * mode. */
 int32_t pdfs_best_combo(pdfs_ctx *ctx, int32_t h, uint32_t alpha_p, uint32_t alpha_q,
                         const uint64_t *uncovered, pdfs_combo *out, pdfs_stats *stats);
 
@@ -205,9 +204,11 @@ int32_t pdfs_best_combo(pdfs_ctx *ctx, int32_t h, uint32_t alpha_p, uint32_t alp
  * the number of rounds.  If more than cap rounds were needed the call returns
  * PDFS_ERR_TRUNCATED with *n_out = rounds needed (the first cap are written).
  * final_uncovered (host, may be NULL) receives the mask after the last round.
- * stats may be NULL.  The first call with h >= 5 under PDFS_PRUNE_NONE on a
- * context allocates the deep walk's prefix rings (about 0.8 GB at 1000 tumour
- * samples), kept until pdfs_destroy; PDFS_ERR_OUT_OF_MEMORY if that fails.  PDFS_ERR_DEVICE also
+ * stats may be NULL.  The first call with h >= 5 on a context whose rounds walk
+ * every node (PDFS_PRUNE_NONE; in the other modes cohorts so dense, or so small,
+ * that this is faster than keeping bounds from round to round) allocates the
+ * deep walk's prefix rings (about 0.8 GB at 1000 tumour samples), kept until
+ * pdfs_destroy; PDFS_ERR_OUT_OF_MEMORY if that fails.  PDFS_ERR_DEVICE also
  * reports a device-side consistency failure (a corrupt result slot, or the
  * deep walk's scheduler making no progress), with the run stopped. */
 int32_t pdfs_wsc_run(pdfs_ctx *ctx, int32_t h, uint32_t alpha_p, uint32_t alpha_q,
@@ -258,13 +259,15 @@ int32_t pdfs_measure_int_peak(int32_t device, double *lane_ops_per_s);
  * run concurrently on a small set of streams (one per hardware queue) while a
  * single host thread feeds them.  Results are those of pdfs_wsc_run on each
  * instance alone. */
-/* Tunes the split granularity of the launches of PDFS_OPT_BATCH_ONE_LAUNCH
- * (depth-3 candidates per work item, seed pairs in bound mode) per instance
- * class; without effect where the rounds have nothing to tune. */
+/* Tunes the split granularity of walked rounds (depth-3 candidates per work
+ * item, seed pairs in bound mode) per instance class; without effect on rounds
+ * of one launch, which have nothing to tune. */
 #define PDFS_OPT_AUTOTUNE 4
 /* Two ways to run a batch.  Each instance's own launches concurrently on the
- * batch's streams is the default and the faster one (8 cohorts under
- * PDFS_PRUNE_BOUND: 25 ms against 109 ms); PDFS_OPT_BATCH_STREAMS asks for it.
+ * batch's streams is the default, and the faster one where a round is one launch
+ * (8 cohorts under PDFS_PRUNE_BOUND: 12 ms against 109 ms); PDFS_OPT_BATCH_STREAMS
+ * asks for it.  Under PDFS_PRUNE_BOUND a batch of dense cohorts only, whose
+ * rounds are walked, takes the other by default.
  * PDFS_OPT_BATCH_ONE_LAUNCH asks for one launch per round step over all
  * instances where the batch allows it (up to 64 instances, all with h in
  * {3, 4}, under PDFS_PRUNE_EMPTY or PDFS_PRUNE_BOUND; streams otherwise):

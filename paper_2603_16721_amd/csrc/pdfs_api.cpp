@@ -4,6 +4,7 @@
 // buffers, picks kernel variants and reads the per-round record back.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cstring>
 #include <string>
@@ -233,23 +234,6 @@ static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
 // Sums along the samples' gene lists that the counters keep (k_count.hip).
 static size_t count_sums(int h) { return h >= 4 ? (size_t)(h - 3) + (h == 4 ? 2 : 0) : 0; }
 
-// Runs under score-bound and empty-intersection pruning go out as lazy rounds,
-// whose bounds carry over from one round to the next; an empty-intersection
-// run takes its counters from one enumeration after the rounds (its lists must
-// stay under kMaxCountBytes; G = 20000 at 66 mutations a sample needs 2 MB).
-// A single round of h = 2 is left to the pair table, which scores every pair
-// in its own epilogue: 115 us against 134 us with the lists (G = 500); a cover
-// of 82 rounds at G = 5000 takes 1.9 ms on the lists, 5.4 ms with a table per
-// round.
-constexpr size_t kMaxCountBytes = (size_t)1 << 30;
-
-static bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds) {
-  if (c->lazy_off || h < 2 || (h == 2 && max_rounds == 1)) return false;
-  if (c->prune_mode == PDFS_PRUNE_BOUND) return true;
-  return c->prune_mode == PDFS_PRUNE_EMPTY &&
-         c->tumor_bits * (8 * count_sums(h) + 2) <= kMaxCountBytes;
-}
-
 // The counters' buffers for a run of `rounds` rounds of depth h.
 static int32_t ensure_count(pdfs_ctx* c, int h, int w64, int rounds) {
   CountWork& C = c->cw;
@@ -329,6 +313,81 @@ int32_t ensure_workspace(pdfs_ctx* c, int h, bool lazy) {
 }  // namespace
 
 namespace pdfs {
+
+// Most nodes that any depth of one round's empty-intersection walk forms, were
+// every gene mutated in a share d of the n samples: C(nA, l) subsets of l genes,
+// times the share of their (l - 1)-prefixes that some sample keeps.
+static double walk_visits(int h, int nA, int n, double d) {
+  double v = 0.0, subsets = nA, kept = n;
+  for (int l = 2; l <= h && l <= nA; ++l) {
+    subsets *= (double)(nA - l + 1) / l;
+    kept *= d;
+    v = std::max(v, subsets * std::min(1.0, kept));
+  }
+  return v;
+}
+
+bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_PRUNE_NONE; }
+
+// Lazy rounds or walked ones (the pair table at h = 2).  A lazy round opens few
+// pairs, one wave each, and an open costs by the pair's samples: past 64 of them
+// its masks leave one word, past 256 its candidates leave the list.  The walk
+// visits every node, whatever its samples, over the whole device.  So what
+// decides is the samples that a pair shares, taken as m = n d^2 from the mean
+// density d (cohorts whose density sits in a few genes have many more pairs
+// without a sample than with many, and lazy rounds gain on them at every m that
+// was tried).  Measured over 6600 rounds and covers (G 20 .. 20000, n 60 .. 1200, d
+// 0.005 .. 0.45, even and heavy-tailed rates); lazy | walked, ms:
+//  - covers: h = 4, n = 1200 G = 400 m 12 1.4 | 13, m 48 4.6 | 2.6, m 108 96 | 5.9;
+//    h = 5, n = 1200 G = 250 m 48 6.8 | 7.7, m 75 46 | 10; under ~100 genes (~50 at
+//    h = 4) there are few pairs to open and many rounds: lazy at every m; h = 3,
+//    n = 1200 G = 1000 m 12 1.4 | 7.8, m 108 5.4 | 10, m 243 33 | 24.
+//  - h = 2 covers: every pair is one lane's count, so the cost is the list: n = 500
+//    G = 5000 d 0.1 3.2 | 4.9, d 0.2 3.5 | 2.7; G = 20000 d 0.1 20 | 26, d 0.2 33 |
+//    14; G = 2500 d 0.2 1.6 | 1.9.  A single round is left to the table, which
+//    scores every pair in its own epilogue: 115 us against 134 us with the lists
+//    (G = 500).
+//  - one round (or a few) has only its own opens to save: h = 3, n = 1200 G = 300
+//    m 12 0.42 | 0.32, G = 1000 m 12 0.83 | 1.4, m 108 4.8 | 1.8, G = 5000 m 48 96 |
+//    154; h = 4, n = 500 G = 300 m 5 0.32 | 0.33, n = 1200 G = 300 m 12 0.62 | 0.45.
+//  - counters of an empty-intersection run are 6 launches more (70 us): it takes a
+//    walk of some size to be worth them.  One round: h = 3, G = 400 m 0.1 0.18 |
+//    0.16, G = 2500 m 0.5 0.31 | 1.6; h = 5, G = 60 m 0.1 0.18 | 0.09, G = 400 m 0.5
+//    0.20 | 1.3.  Their enumeration opens each pair for itself as well: h = 4,
+//    n = 1200 G = 300 m 108 29 | 2.0 (but 1.5 | 21 ms at h = 5, m 12, whose walk
+//    visits every leaf).
+bool lazy_pays(const RunShape& s, int h, int prune_mode, int max_rounds, bool counters) {
+  if (!lazy_runs_at(h, prune_mode) || (h == 2 && max_rounds == 1)) return false;
+  const int nA = s.nA > 0 ? s.nA : 1, n = s.n_unc;
+  const double d = (double)s.bits / ((double)nA * s.n_tumor), m = d * d * n;
+  if (h == 2) return d < 0.15 || d * nA < 700.0;
+  counters = counters && prune_mode == PDFS_PRUNE_EMPTY;
+  const int few = max_rounds >= 1 && max_rounds <= 4 ? max_rounds : 0;
+  const double visits = counters ? walk_visits(h, nA, n, d) : 0.0;
+  if (few) {
+    if (!counters) return h == 3 ? m < 16.0 || (nA >= 2048 && m < 64.0) : m < 10.0;
+    if (h == 3) return few * visits >= 3e7 && m < 16.0;
+    if (h == 4) return m < 8.0 && nA >= 2.0 * m * words(n);
+    return few * visits >= (h == 5 ? 1e5 : 3e4) && m < 48.0;
+  }
+  if (counters && visits < (h <= 4 ? 1e2 : h == 5 ? 1e3 : h == 6 ? 3e3 : 1e4)) return false;
+  if (h == 3) return m < 128.0 || nA < 500;
+  if (h == 4) return m < 64.0 || nA < 48;
+  return counters || m < 64.0 || nA < 96;
+}
+
+// A run's lists for its counters must stay under kMaxCountBytes (G = 20000 at 66
+// mutations a sample needs 2 MB).
+constexpr size_t kMaxCountBytes = (size_t)1 << 30;
+
+bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds, int n_unc) {
+  if (c->route != Route::kByRule) return c->route == Route::kLazy && lazy_runs_at(h, c->prune_mode);
+  const RunShape s = {c->nA_max, c->n_tumor, n_unc, c->tumor_bits};
+  if (c->prune_mode == PDFS_PRUNE_EMPTY && c->want_counters &&
+      c->tumor_bits * (8 * count_sums(h) + 2) > kMaxCountBytes)
+    return false;
+  return lazy_pays(s, h, c->prune_mode, max_rounds, c->want_counters);
+}
 
 // Waves of a lazy round for a pair list of n pairs: a share of 128 pairs at
 // least, at most one block per compute unit.
@@ -649,7 +708,7 @@ int32_t prepare_run(pdfs_ctx* c, int h, int n_unc) {
 
 int32_t run_start(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int max_rounds,
                   int n_unc) {
-  const bool lazy = runs_lazy(c, h, max_rounds);
+  const bool lazy = runs_lazy(c, h, max_rounds, n_unc);
   const int w64 = dfs_row_words(words(n_unc > 0 ? n_unc : 1));
   int32_t rc = lazy ? ensure_workspace(c, h, true) : prepare_run(c, h, n_unc);
   if (rc == PDFS_OK && lazy) {
@@ -984,6 +1043,7 @@ int32_t run_records(pdfs_ctx* c, pdfs_combo* out, int32_t cap, int32_t* rounds,
 size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int prune_mode,
                        bool lazy) {
   if (prune_mode == PDFS_PRUNE_NONE) nA_max = G;   // exhaustive mode: every gene is a row
+  lazy = lazy && lazy_runs_at(h, prune_mode);
   const size_t wt = (size_t)words(n_tumor), wn = (size_t)(n_normal > 0 ? words(n_normal) : 1);
   const size_t rows = (size_t)((nA_max + 127) / 128 * 128 + 128);
   const int w64max = dfs_row_words((int)wt);
@@ -994,10 +1054,10 @@ size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int 
   if (h >= 3) {
     const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
     b += pairs * 8 * (!lazy && prune_mode == PDFS_PRUNE_BOUND ? 2 : 1);
-    if (!lazy || prune_mode == PDFS_PRUNE_NONE)
+    if (!lazy)
       b += (size_t)item_cap_for(pairs) * sizeof(Item) + (size_t)kSeedCap * 8;
   }
-  if (lazy && h >= 2 && prune_mode != PDFS_PRUNE_NONE) {   // lazy rounds
+  if (lazy) {
     const size_t pairs = (size_t)pair_cap_for(nA_max, 0);
     const size_t nw = (size_t)lazy_waves(pairs), gw = (size_t)(nA_max + 63) / 64;
     if (h == 2) b += pairs * 8;
@@ -1006,7 +1066,7 @@ size_t footprint_bytes(int G, int n_tumor, int n_normal, int nA_max, int h, int 
     b += (size_t)kLazyWaves * sizeof(Slot) * 2;
   }
   if (h == 2) b += rows * (size_t)unpacked_row_bytes((int)wn);
-  if (h >= 5 && prune_mode == PDFS_PRUNE_NONE) {
+  if (h >= 5 && !lazy) {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)

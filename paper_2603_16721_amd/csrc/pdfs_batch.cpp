@@ -157,9 +157,9 @@ double time_first_round(pdfs_ctx* c, int h, uint32_t p, uint32_t q) {
   (void)hipStreamSynchronize(c->stream);
   const auto t0 = Clock::now();
   // the launches that the choices are for, not the lazy rounds
-  c->lazy_off = true;
+  c->route = Route::kWalked;
   const int32_t rc = run_blocking(c, h, p, q, c->n_tumor + 1, 1, c->n_tumor);
-  c->lazy_off = false;
+  c->route = Route::kByRule;
   if (rc != PDFS_OK) return 1e30;
   return std::chrono::duration<double>(Clock::now() - t0).count();
 }
@@ -254,6 +254,7 @@ struct pdfs_batch {
   hipEvent_t fork_ev = nullptr;              // ranges' depth-first launches run side by side
   std::vector<hipEvent_t> join_ev;
   int n_alloc = 0;                           // instances the batched buffers hold
+  bool streams_only = false;                 // PDFS_OPT_BATCH_STREAMS: no batched launches
   bool one_launch = false;                   // PDFS_OPT_BATCH_ONE_LAUNCH: batched launches in every mode
 };
 
@@ -719,8 +720,9 @@ int32_t pdfs_batch_create(const pdfs_matrix* inst, int32_t n, const pdfs_options
   pdfs_batch* b = new pdfs_batch();
   b->device = opt ? opt->device : 0;
   b->autotune = opt && (opt->flags & PDFS_OPT_AUTOTUNE);
+  b->streams_only = opt && (opt->flags & PDFS_OPT_BATCH_STREAMS);
   b->one_launch = opt && (opt->flags & PDFS_OPT_BATCH_ONE_LAUNCH);
-  if (b->one_launch && (opt->flags & PDFS_OPT_BATCH_STREAMS)) {
+  if (b->streams_only && b->one_launch) {
     delete b;
     return ctx_fail(nullptr, PDFS_ERR_INVALID_ARG,
                     "PDFS_OPT_BATCH_STREAMS and PDFS_OPT_BATCH_ONE_LAUNCH exclude each other");
@@ -769,16 +771,23 @@ int32_t pdfs_batch_run(pdfs_batch* b, const int32_t* h, uint32_t p, uint32_t q,
     if (rc != PDFS_OK) return batch_fail(b, rc, i);
     n_outs[i] = 0;
   }
-  // one launch per round step over every instance where it is asked for and
-  // all take it (h = 3, 4 with empty or bound pruning); otherwise the
-  // stream-parallel runs below, whose rounds are lazy ones (8 cohorts under
-  // bound pruning: 109 ms in one launch per step, 25 ms on the streams)
+  // One launch per round step over every instance (all of h = 3, 4 with empty or
+  // bound pruning) where it is asked for, and by default under bound pruning
+  // where every instance's rounds are walked.  Otherwise the stream-parallel runs
+  // below: of lazy rounds 8 cohorts took 25 ms there, 109 ms in one launch per
+  // step (and 32 instances of walked ones 396 ms there, 215 ms in one launch).
   const int pm = b->ctx[0]->prune_mode;
-  bool multi = n <= kMaxBatch && pm != PDFS_PRUNE_NONE && b->one_launch;
-  for (int i = 0; i < n; ++i)
+  std::vector<bool> walked(n);
+  bool all_walked = true, multi = n <= kMaxBatch && pm != PDFS_PRUNE_NONE;
+  for (int i = 0; i < n; ++i) {
+    walked[i] = !runs_lazy(b->ctx[i], h[i], 0, b->ctx[i]->n_tumor);
+    all_walked = all_walked && walked[i];
     multi = multi && (h[i] == 3 || h[i] == 4) && b->ctx[i]->tn_literal == b->ctx[0]->tn_literal;
-  if (b->autotune && (multi || pm == PDFS_PRUNE_NONE))   // lazy rounds have nothing to tune
-    for (int i = 0; i < n; ++i) autotune(b->ctx[i], h[i], p, q);
+  }
+  multi = multi && (b->one_launch || (pm == PDFS_PRUNE_BOUND && all_walked && !b->streams_only));
+  if (b->autotune)
+    for (int i = 0; i < n; ++i)   // lazy rounds have nothing to tune
+      if (multi || walked[i]) autotune(b->ctx[i], h[i], p, q);
   if (multi) return run_multi(b, h, p, q, target, outs, caps, n_outs, stats, t0);
   for (int i = 0; i < n; ++i) {
     pdfs_ctx* c = b->ctx[i];
@@ -875,7 +884,7 @@ struct Request {
   pdfs_matrix m{};
   std::vector<uint64_t> T, N;   // copies, row stride = words
   size_t bytes = 0;              // estimated device footprint
-  bool walked = false;           // the budget holds walked rounds' lists only
+  Route route = Route::kByRule;  // chosen with the footprint
   Clock::time_point t_submit, t_done;
   pdfs_ctx* ctx = nullptr;
   RoundState* pinned = nullptr;
@@ -999,7 +1008,7 @@ bool admit_one(pdfs_server* s) {
   int32_t rc = create_ctx(&r->m, &o, &r->ctx, r->pinned, true, s->pool);
   if (rc == PDFS_OK) {
     r->ctx->want_counters = false;   // answers carry no statistics
-    r->ctx->lazy_off = r->walked;
+    r->ctx->route = r->route;
   }
   if (rc == PDFS_OK) {
     r->ctx->stream = s->streams[s->next_stream++ % (int)s->streams.size()];
@@ -1159,14 +1168,15 @@ int32_t pdfs_server_submit(pdfs_server* s, const pdfs_matrix* m, int32_t h, uint
   r->h = h; r->p = p; r->q = q; r->target = target;
   r->T.resize((size_t)m->G * wt);
   int nA = 0;
+  unsigned long long bits = 0;
   for (int g = 0; g < m->G; ++g) {
-    uint64_t any = 0;
+    const unsigned long long before = bits;
     for (int k = 0; k < wt; ++k) {
       const uint64_t v = m->tumor[(size_t)g * m->tumor_stride_words + k];
       r->T[(size_t)g * wt + k] = v;
-      any |= v;
+      bits += (unsigned long long)__builtin_popcountll(v);
     }
-    nA += any != 0;
+    nA += bits != before;
   }
   if (wn) {
     r->N.resize((size_t)m->G * wn);
@@ -1180,14 +1190,18 @@ int32_t pdfs_server_submit(pdfs_server* s, const pdfs_matrix* m, int32_t h, uint
   r->m.tumor_stride_words = wt;
   r->m.normal = wn ? r->N.data() : nullptr;
   r->m.normal_stride_words = wn;
-  r->bytes = footprint_bytes(m->G, m->n_tumor, m->n_normal, nA, h, s->prune_mode, true);
-  // Lazy rounds keep 17 bytes a pair, walked ones of h = 2 none: a budget that
-  // holds only those takes them (h <= 4; deeper walks need more, not less).
-  if (r->bytes > s->budget && h <= 4) {
-    const size_t b = footprint_bytes(m->G, m->n_tumor, m->n_normal, nA, h, s->prune_mode, false);
-    r->walked = b <= s->budget;
-    if (r->walked) r->bytes = b;
+  // Lazy rounds keep 17 bytes a pair (walked ones of h = 2 none), walked ones of
+  // h >= 5 their rings: a budget that holds only one of the two takes that one.
+  bool lazy = lazy_pays({nA, m->n_tumor, m->n_tumor, bits}, h, s->prune_mode, 0, false);
+  auto footprint = [&](bool lz) {
+    return footprint_bytes(m->G, m->n_tumor, m->n_normal, nA, h, s->prune_mode, lz);
+  };
+  r->bytes = footprint(lazy);
+  if (r->bytes > s->budget && footprint(!lazy) <= s->budget) {
+    lazy = !lazy;
+    r->bytes = footprint(lazy);
   }
+  r->route = lazy ? Route::kLazy : Route::kWalked;
   std::lock_guard<std::mutex> g(s->mu);
   if (r->bytes > s->budget) {
     s->err = "request footprint " + std::to_string(r->bytes) + " B above the server budget " +

@@ -27,6 +27,16 @@ constexpr int kDepth = 2;
 // (the allocation-free entry point's read-back).
 constexpr size_t kPinnedBytes = kDepth * sizeof(RoundState) + sizeof(RoundRecord);
 
+// How a run's rounds go out: lazy rounds (k_lazy.hip) or walked ones.
+enum class Route { kByRule, kLazy, kWalked };
+
+// What the choice goes by.
+struct RunShape {
+  int nA;                    // genes with a tumour mutation
+  int n_tumor, n_unc;        // samples, and the uncovered ones at the run's start
+  unsigned long long bits;   // tumour mutations
+};
+
 // Progress of one greedy run on a context, advanced without blocking.  The
 // run's rounds go out in chunks; each chunk ends with a copy of the device
 // state into its pinned slot and an event.  The row width of a chunk comes
@@ -100,7 +110,7 @@ struct pdfs_ctx {
   pdfs::CountWork cw = {};
   size_t cw_tab_n = 0, cw_seg_n = 0, cw_bits_n = 0, cw_q_n = 0, cw_pref_n = 0;
   unsigned long long tumor_bits = 0;   // tumour mutations of the cohort
-  bool lazy_off = false;               // walked rounds (the tuner; a tight server budget)
+  pdfs::Route route = pdfs::Route::kByRule;   // (the tuner and the server set it)
   bool want_counters = true;           // callers that report no counters skip them
   bool two_phase = false;              // this run uses the two-phase path
   pdfs::Slot* slots = nullptr;
@@ -198,6 +208,12 @@ int32_t enqueue_round(pdfs_ctx* c, const Problem& P, const Work& w, hipEvent_t* 
 // for enqueue_round; ev[0..1] around the pair table (used when timing).
 int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, const LazyWork& L,
                       int run_rounds, hipEvent_t* ev);
+// Whether lazy rounds take this depth and mode at all, and whether a run of at
+// most max_rounds (<= 0: any number) is faster as lazy rounds than walked
+// (counters: the caller wants those of an empty-intersection run).
+bool lazy_runs_at(int h, int prune_mode);
+bool lazy_pays(const RunShape& s, int h, int prune_mode, int max_rounds, bool counters);
+bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds, int n_unc);
 // Waves of a lazy round for a pair list of n pairs, and pairs per wave's share.
 int lazy_waves(unsigned long long n);
 int lazy_seg(unsigned long long n, int nw);

@@ -328,9 +328,9 @@ class Solver:
 def pdfs_batch_create(instances, prune_mode="bound", device=0, autotune=False,
                       path="auto", pair_cap=0):
     """instances: list of (tumor, normal, n_tumor, n_normal) host arrays.  Returns a handle.
-    path: "auto" (the faster way for the mode: one launch per round step over all
-    instances under bound pruning, each instance's own launches on the batch's
-    streams otherwise), "streams" or "one_launch" (PDFS_OPT_BATCH_STREAMS /
+    path: "auto" (each instance's own launches on the batch's streams; one launch
+    per round step over all instances where every cohort is dense, under bound
+    pruning), "streams" or "one_launch" (PDFS_OPT_BATCH_STREAMS /
     PDFS_OPT_BATCH_ONE_LAUNCH).  pair_cap: every instance's initial pair-list
     capacity (pdfs_options.pair_cap)."""
     if path not in BATCH_PATHS:
