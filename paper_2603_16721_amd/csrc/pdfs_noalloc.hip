@@ -79,17 +79,23 @@ const size_t kLazyBytes = [] {
 struct Layout {
   size_t st, recs, slots, tallies, zero_end;   // [st, zero_end) is cleared per call
   size_t cols, act, flags, TA, NA, A8, N8, hist, cursors, seed, pairs, work, items;
-  size_t B, bits, list, cmax, lazy;   // lazy round (bound mode, h >= 3)
+  size_t B, bits, list, cmax, lazy;   // lazy round
   int nw = 0, seg = 0, gw = 0;
   size_t total;
   unsigned long long pair_cap = 0, item_cap = 0;
 };
 
+// Every pair of nA rows.
+unsigned long long all_pairs(int nA) {
+  return (unsigned long long)nA * (nA > 0 ? nA - 1 : 0) / 2;
+}
+
 // Plans the workspace of one round at row width w64max.  The fixed part is
-// sized exactly; the pair list and its bound-mode shares or the item list
-// take what is left, up to the exact bound of nA(nA-1)/2 pairs.  Returns
-// false (with the bytes the fixed part needs) when it does not fit.
-bool plan(const pdfs_ctx* c, int h, Layout& L, size_t* need) {
+// sized exactly; the pair list and a lazy round's shares, or its bound-mode
+// copy and the item list, take what is left, up to every pair.  Returns false
+// (with the bytes the fixed part needs) when it does not fit.
+bool plan(const pdfs_ctx* c, int h, bool lazy, Layout& L, size_t* need) {
+  L = Layout();
   const int nA = c->prune_mode == PDFS_PRUNE_NONE ? c->G : c->nA_max;
   const size_t rows = (size_t)((nA + 127) / 128 * 128 + 128);
   size_t o = 0;
@@ -102,7 +108,6 @@ bool plan(const pdfs_ctx* c, int h, Layout& L, size_t* need) {
   L.recs = take(sizeof(RoundRecord));
   // (a lazy round has the pair table's counter rows only, and no slots)
   const bool bound = c->prune_mode == PDFS_PRUNE_BOUND;
-  const bool lazy = h >= 3 && bound;
   L.tallies = take((size_t)(lazy ? 1 : kSlotPhases) * kPersistBlocks * kTallyN * 8);
   L.zero_end = o;
   L.slots = take(lazy ? 0 : (size_t)kSlotPhases * kSlotsPerPhase * sizeof(Slot));
@@ -136,16 +141,16 @@ bool plan(const pdfs_ctx* c, int h, Layout& L, size_t* need) {
   L.pairs = L.work = L.items = o;
   if (h >= 3) {
     // The rest holds the pair list and, for a lazy round, its waves' shares (8
-    // bytes a pair, and a bound per 64); otherwise the item list: two 16-byte
-    // items per 64-pair batch and 2048 spare items.
+    // bytes a pair, and a bound per 64); otherwise the bound mode's work copy and
+    // the item list: two 16-byte items per 64-pair batch and 2048 spare items.
     const size_t fixed = lazy ? 4 * 256 + (size_t)kLazyWaves * (8 + 4)   // the shares' round-up
                               : (size_t)2048 * sizeof(Item) + 3 * 256;
     const size_t avail = kScratchBytes - o;
     if (avail <= fixed + 64 * 17) return false;
-    const double per_pair = lazy ? 16.0 + 4.0 / kWave : 8.0 + 2.0 * sizeof(Item) / kPairBatch;
+    const double per_pair = lazy ? 16.0 + 4.0 / kWave
+                                 : (bound ? 16.0 : 8.0) + 2.0 * sizeof(Item) / kPairBatch;
     unsigned long long cap = (unsigned long long)((double)(avail - fixed) / per_pair);
-    const unsigned long long exact = (unsigned long long)nA * (nA > 0 ? nA - 1 : 0) / 2;
-    if (cap > exact) cap = exact;
+    cap = std::min(cap, all_pairs(nA));
     if (cap < 64) cap = 64;
     L.pair_cap = cap;
     L.pairs = take(cap * 8);
@@ -159,7 +164,7 @@ bool plan(const pdfs_ctx* c, int h, Layout& L, size_t* need) {
       *need = o;
       return o <= kScratchBytes;
     }
-    L.work = L.pairs;
+    L.work = bound ? take(cap * 8) : L.pairs;
     L.item_cap = 2 * ((cap + kPairBatch - 1) / kPairBatch) + 2048;
     L.items = take(L.item_cap * sizeof(Item));
   }
@@ -216,9 +221,21 @@ int32_t pdfs_best_combo_noalloc(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q,
     }
   }
   if (!base) return nfail(c, PDFS_ERR_DEVICE, "static scratch not set up on this device");
+  // A bound-pruned round goes out lazily where that is the faster way, and where
+  // the walk's lists could not hold every pair beside its work copy.
   Layout L;
   size_t need = 0;
-  if (!plan(c, h, L, &need))
+  bool lazy = h >= 3 && c->prune_mode == PDFS_PRUNE_BOUND;
+  if (lazy) {
+    int n = c->n_tumor;
+    if (uncovered) {
+      n = 0;
+      for (int k = 0; k < c->wt; ++k) n += __builtin_popcountll(uncovered[k]);
+    }
+    lazy = lazy_pays({c->nA_max, c->n_tumor, n, c->tumor_bits}, h, c->prune_mode, 1, false) ||
+           !plan(c, h, false, L, &need) || L.pair_cap < all_pairs(c->nA_max);
+  }
+  if (!plan(c, h, lazy, L, &need))
     return nfail(c, PDFS_ERR_UNSUPPORTED,
                  "round workspace of " + std::to_string(need) + " bytes exceeds the " +
                      std::to_string(kScratchBytes) + "-byte static scratch");
@@ -263,10 +280,8 @@ int32_t pdfs_best_combo_noalloc(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q,
   hipStream_t s = c->stream;
   // what a round expects to start from zero; the rest is written before use
   NCK(launch_zero_u32(base + L.st, (L.zero_end - L.st) / 4, s));
-  if (!(h >= 3 && c->prune_mode == PDFS_PRUNE_BOUND))
-    NCK(launch_clear_slots(w.slots, kSlotPhases * kSlotsPerPhase, s));
+  if (!lazy) NCK(launch_clear_slots(w.slots, kSlotPhases * kSlotsPerPhase, s));
   const int slot = c->next_slot;
-  const bool lazy = h >= 3 && c->prune_mode == PDFS_PRUNE_BOUND;
   if (lazy) {
     // as the rounds of a bound-pruned run (14 launches 183 us, so 115 us
     // at G = 3067)

@@ -171,3 +171,29 @@ def test_served_walked(pdfs, case, mode):  # noqa: F811
             _same_rounds(r[0], exp.rounds)
     finally:
         pdfs.pdfs_server_destroy(srv)
+
+
+# The allocation-free round against the oracle: walked where the cohort is dense,
+# lazy elsewhere, and lazy where the walk's lists would not hold every pair (2850
+# genes, nearly all of whose 4.06 M pairs share a sample: a lazy round holds 4.12 M,
+# a walked one 3.99 M).  Row widths of one to three words
+# and wider place the lazy round's buffers differently.
+@pytest.mark.parametrize("h", [3, 4])
+@pytest.mark.parametrize("G,nt,d,tail", [(90, 400, 0.4, 0), (300, 700, 0.2, 0), (70, 50, 0.2, 0),
+                                         (600, 64, 0.03, 0), (250, 100, 0.04, 2000),
+                                         (900, 130, 0.03, 0), (60, 700, 0.5, 500)])
+def test_noalloc_against_oracle(pdfs, G, nt, d, tail, h):  # noqa: F811
+    T, N = _cohort(G, nt, 60, d, h, tail)
+    with pdfs.Solver(T, N, nt, 60, "bound") as s:
+        for u in (None, mask_of_bits(np.arange(nt) % 4 != 1)):
+            exp = cpu.wsc(T, N, nt, 60, h, 1, 10, mode="bound", max_rounds=1, U0=u)
+            got, _ = s.best_noalloc(h, 1, 10, u)
+            _same_rounds([got], exp.rounds)
+
+
+def test_noalloc_dense_and_large(pdfs):  # noqa: F811
+    T, N = _cohort(2850, 100, 20, 0.42, 3)
+    with pdfs.Solver(T, N, 100, 20, "bound") as s:
+        exp = cpu.wsc(T, N, 100, 20, 3, 1, 10, mode="bound", max_rounds=1)
+        got, _ = s.best_noalloc(3, 1, 10)
+        _same_rounds([got], exp.rounds)
