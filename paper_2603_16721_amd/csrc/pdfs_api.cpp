@@ -351,8 +351,9 @@ bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_P
 //    m 12 0.42 | 0.32, G = 1000 m 12 0.83 | 1.4, m 108 4.8 | 1.8, G = 5000 m 48 96 |
 //    154; h = 4, n = 500 G = 300 m 5 0.32 | 0.33, n = 1200 G = 300 m 12 0.62 | 0.45.
 //    Few genes make few waves, whose opens then follow one another and grow with
-//    the row's words too: h = 3, G = 100 n = 1200 m 12 0.45 | 0.25, n = 100 m 9 0.11 |
-//    0.21.
+//    the row's words too: h = 4, G = 100 n = 1200 m 12 0.58 | 0.29, n = 100 m 9 0.24 |
+//    0.23 (at h = 3 the same line would lose as much on heavy-tailed cohorts, n = 700
+//    G = 150 m 16 0.13 | 0.23, as it gains on even ones).
 //  - counters of an empty-intersection run are 6 launches more (70 us): it takes a
 //    walk of some size to be worth them.  One round: h = 3, G = 400 m 0.1 0.18 |
 //    0.16, G = 2500 m 0.5 0.31 | 1.6; h = 5, G = 60 m 0.1 0.18 | 0.09, G = 400 m 0.5
@@ -368,10 +369,9 @@ bool lazy_pays(const RunShape& s, int h, int prune_mode, int max_rounds, bool co
   const int few = max_rounds >= 1 && max_rounds <= 4 ? max_rounds : 0;
   const double visits = counters ? walk_visits(h, nA, n, d) : 0.0;
   if (few) {
-    const bool short_opens = h >= 5 || nA >= 500 || m * words(n) < 100.0;
     if (!counters) {
-      if (h == 3) return (m < 16.0 && short_opens) || (nA >= 2048 && m < 64.0);
-      return m < 10.0 && short_opens;
+      if (h == 3) return m < 16.0 || (nA >= 2048 && m < 64.0);
+      return m < 10.0 && (h >= 5 || nA >= 500 || m * words(n) < 100.0);
     }
     if (h == 3) return few * visits >= 3e7 && m < 16.0;
     if (h == 4) return m < 8.0 && nA >= 2.0 * m * words(n);
