@@ -144,7 +144,10 @@ typedef struct {
  *   bound_pruned[l]: non-empty prefixes dropped by the score bound.
  * Under PDFS_PRUNE_EMPTY the counts are exact and order-independent.  Under
  * PDFS_PRUNE_BOUND they depend on how fast the incumbent rises and are for
- * information only. */
+ * information only: the nodes that were formed.  A run that keeps its bounds from
+ * round to round forms the nodes of depths 1 and 2 at its start, and later the
+ * pairs whose bound has come into reach again; below them it forms the active
+ * candidates (also those past a depth's loop bound). */
 typedef struct {
     uint64_t visited[PDFS_MAX_H + 1];
     uint64_t nonempty[PDFS_MAX_H + 1];
@@ -160,11 +163,12 @@ typedef struct {
     int64_t kernel_ns[3];        /* summed HIP-event durations            */
     int32_t kernel_launches[3];  /* launches timed                        */
     /* Work the kernels had to do, counted inside them (always filled):
-     * pair_macs  = active pairs x |U| (one multiply-add per sample);
+     * pair_macs  = active pairs x |U| (one multiply-add per sample), per round
+     *   (per run where it keeps its bounds under PDFS_PRUNE_BOUND);
      * dfs_visits[l] = depth-l (l = 3, 4) candidate intersections over active
      *   genes; dfs_leaves = non-empty leaves (each compared with its
-     *   lane's best); dfs_fp_leaves = leaves whose
-     *   normal intersection had to be counted; dfs_visit_words3/4 = depth-3/4
+     *   lane's best; h = 3, 4); dfs_fp_leaves = leaves whose
+     *   normal intersection had to be counted (h = 3, 4); dfs_visit_words3/4 = depth-3/4
      *   visits times ceil(|U|/64) of their round, summed (so words / visits
      *   is the mean row length in 64-bit words). */
     uint64_t pair_macs;

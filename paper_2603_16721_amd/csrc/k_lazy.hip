@@ -104,6 +104,10 @@ __global__ __launch_bounds__(256) void k_lazy_begin(Problem P, Work w, LazyWork 
   }
   for (int i = blockIdx.x * kBlock + threadIdx.x; i < L.nw; i += gridDim.x * kBlock)
     L.pool[i].s = -1;
+  if (L.tally)
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < kWorkRows * kLazyFields;
+         i += gridDim.x * kBlock)
+      L.tally[i] = 0ull;
 }
 
 // The pair list in order of falling count, dealt one by one to the waves: the
@@ -438,7 +442,22 @@ struct Wave {
   bool own;                     // the wave's best leaf lies below this pair
   int tie_s;                    // a score this pair has reached: its later tuples lose the tie
   int a, b, need, sub, lmax;    // best score below it; per lane: largest TP pruned
+  // Work counted: lane f holds field f (LazyField), so that a depth known only at
+  // run time needs no indexed registers and the round's end one store: 0.6 us of a
+  // round of 21 at h = 5 (1.4 us with a register per depth, whose selects at the
+  // end are cold code); h = 2 and 3 covers 2 % longer than uncounted, h = 4 no
+  // longer, h = 5 3 %.
+  long long work;
+  uint32_t ne3;                 // h = 3, per lane: non-empty leaves of the slices
 };
+
+__device__ __forceinline__ int count_lanes(bool on) { return __popcll(__ballot(on)); }
+
+// Nodes of one depth: formed, non-empty, pruned (depth 2: pairs opened).
+__device__ __forceinline__ void count_nodes(Wave& v, int depth, int vis, int ne, int bp) {
+  const int x = v.lane < kLfNe ? vis : (v.lane < kLfBp ? ne : bp);
+  v.work += v.lane < kLfFp && (v.lane & 7) == depth - 2 ? x : 0;
+}
 
 __device__ __forceinline__ unsigned long long load_inc(const Wave& v) {
   return __hip_atomic_load(v.incp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -532,6 +551,10 @@ __device__ __forceinline__ bool score_leaves(Wave& v, int np, bool hit, int d, i
   }
   // normal words that can hold a false positive
   unsigned long long zm = __ballot(lit ? v.lane < v.w.wn32 : (v.lane < kMaxWN32 && z != 0));
+  if (zm) {
+    const int n = count_lanes(hit);
+    v.work += v.lane == kLfFp ? n : 0;
+  }
   int fp = 0;
   while (zm) {
     const int k = __builtin_ctzll(zm);
@@ -575,6 +598,7 @@ __device__ __forceinline__ int row_count(const Wave& v, const uint64_t* y, int d
 // leaves; `in` (may be null) limits them to a bitmap.
 __device__ __forceinline__ void leaves_by_rows(Wave& v, const uint64_t* y, int np, int lo,
                                                const uint64_t* in) {
+  int vis = 0, ne = 0;
   for (int d0 = lo & ~63; d0 < v.nA; d0 += kWave) {
     const int d = d0 + v.lane;
     bool on = d >= lo && d < v.nA;
@@ -582,15 +606,19 @@ __device__ __forceinline__ void leaves_by_rows(Wave& v, const uint64_t* y, int n
     const int tp = row_count(v, y, d, on);
     const bool hit = on && tp >= v.need;
     v.lmax = max(v.lmax, hit ? 0 : tp);
+    if (in) vis += count_lanes(on);
+    ne += count_lanes(tp > 0);
     score_leaves(v, np, hit, d, tp);
     refresh_need(v);
   }
+  count_nodes(v, np + 1, in ? vis : v.nA - lo, ne, 0);
 }
 
 // The candidates that keep at least `need` of y's samples as a list (false:
 // they do not fit), or as a bitmap.
 __device__ __forceinline__ bool list_by_rows(Wave& v, const uint64_t* y, int lo, int cap, int& n) {
   n = 0;
+  int ne = 0;
   for (int d0 = lo; d0 < v.nA; d0 += kWave) {
     const int d = d0 + v.lane;
     const int tp = row_count(v, y, d, d < v.nA);
@@ -600,13 +628,16 @@ __device__ __forceinline__ bool list_by_rows(Wave& v, const uint64_t* y, int lo,
     if (n + __popcll(hm) > cap) return false;
     if (hit) v.s.idx[rank_below(hm, n)] = (uint16_t)d;
     n += __popcll(hm);
+    ne += count_lanes(tp > 0);
   }
+  count_nodes(v, 3, v.nA - lo, ne, ne - n);
   wave_lds_sync();
   return true;
 }
 
-__device__ __forceinline__ void bits_by_rows(Wave& v, const uint64_t* y, int lo,
+__device__ __forceinline__ void bits_by_rows(Wave& v, const uint64_t* y, int depth, int lo,
                                              const uint64_t* in, uint64_t* out) {
+  int vis = 0, ne = 0, keep = 0;
   for (int d0 = lo & ~63; d0 < v.nA; d0 += kWave) {
     const int d = d0 + v.lane;
     bool on = d >= lo && d < v.nA;
@@ -616,7 +647,20 @@ __device__ __forceinline__ void bits_by_rows(Wave& v, const uint64_t* y, int lo,
     v.lmax = max(v.lmax, hit ? 0 : tp);
     const unsigned long long hm = __ballot(hit);
     if (v.lane == 0) out[d0 >> 6] = hm;
+    vis += count_lanes(on);
+    ne += count_lanes(tp > 0);
+    keep += __popcll(hm);
   }
+  count_nodes(v, depth, vis, ne, ne - keep);
+}
+
+// Genes of `in` that some listed sample carries.
+template <int NB>
+__device__ __forceinline__ uint64_t slices_any(const uint64_t (&s)[NB], uint64_t in) {
+  uint64_t x = 0;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) x |= s[k];
+  return x & in;
 }
 
 // All candidates in [lo, nA) against the m listed samples, as leaves below the
@@ -624,12 +668,15 @@ __device__ __forceinline__ void bits_by_rows(Wave& v, const uint64_t* y, int lo,
 template <int NB>
 __device__ __forceinline__ void leaves_by_slices(Wave& v, int m, int np, int lo, const uint64_t* in) {
   const int w_hi = (v.nA + 63) >> 6;
+  int vis = 0, ne = 0;
   for (int w0 = lo >> 6; w0 < w_hi; w0 += 64) {
     const int wd = w0 + v.lane;
     uint64_t s[NB];
     slice_count<NB>(v.L.B, v.L.gw, v.s.smp, m, wd, wd < w_hi, s);
     uint64_t r = wd < w_hi ? range_bits(wd, lo, v.nA) : 0ull;
     if (in && r) r &= in[wd];
+    ne += popc64(slices_any<NB>(s, r));
+    if (in) vis += popc64(r);
     uint64_t ge = slices_ge<NB>(s, v.need) & r;
     uint64_t rest = r & ~ge;
     v.lmax = max(v.lmax, slices_max<NB>(s, rest));
@@ -644,6 +691,12 @@ __device__ __forceinline__ void leaves_by_slices(Wave& v, int m, int np, int lo,
       refresh_need(v);
     }
   }
+  if (in) {
+    count_nodes(v, np + 1, wave_sum(vis), wave_sum(ne), 0);
+  } else {   // below the pair itself
+    count_nodes(v, 3, v.nA - lo, 0, 0);
+    v.ne3 += (uint32_t)ne;
+  }
 }
 
 // Candidates in [lo, nA) with a count of at least `need` into the level-0
@@ -652,6 +705,7 @@ template <int NB>
 __device__ __forceinline__ bool list_by_slices(Wave& v, int m, int lo, int cap, int& n) {
   const int w_hi = (v.nA + 63) >> 6;
   n = 0;
+  int ne = 0;
   for (int w0 = lo >> 6; w0 < w_hi; w0 += 64) {
     const int wd = w0 + v.lane;
     uint64_t s[NB];
@@ -660,17 +714,20 @@ __device__ __forceinline__ bool list_by_slices(Wave& v, int m, int lo, int cap, 
     uint64_t ge = slices_ge<NB>(s, v.need) & r;
     uint64_t rest = r & ~ge;
     v.lmax = max(v.lmax, slices_max<NB>(s, rest));
-    const int c = popc64(ge);
+    // (the non-empty ones in the upper half: at most 4096 of either)
+    const int c = popc64(ge) | popc64(slices_any<NB>(s, r)) << 16;
     int pos = wave_before(c, v.lane);
-    const int tot = uniform(__shfl(pos + c, 63, 64));
+    const int both = uniform(__shfl(pos + c, 63, 64)), tot = both & 0xffff;
     if (n + tot > cap) return false;
-    pos += n;
+    ne += both >> 16;
+    pos = (pos & 0xffff) + n;
     while (ge) {
       v.s.idx[pos++] = (uint16_t)(wd * 64 + __builtin_ctzll(ge));
       ge &= ge - 1;
     }
     n += tot;
   }
+  count_nodes(v, 3, v.nA - lo, ne, ne - n);
   wave_lds_sync();
   return true;
 }
@@ -678,8 +735,10 @@ __device__ __forceinline__ bool list_by_slices(Wave& v, int m, int lo, int cap, 
 // Candidate bitmap of one level of the general walk: genes of [lo, nA) (and
 // of `in`) with a count of at least `need`.
 template <int NB>
-__device__ __forceinline__ void bits_by_slices(Wave& v, int m, int lo, const uint64_t* in, uint64_t* out) {
+__device__ __forceinline__ void bits_by_slices(Wave& v, int m, int depth, int lo, const uint64_t* in,
+                                               uint64_t* out) {
   const int w_hi = (v.nA + 63) >> 6;
+  int vis = 0, ne = 0, keep = 0;
   for (int w0 = lo >> 6; w0 < w_hi; w0 += 64) {
     const int wd = w0 + v.lane;
     uint64_t s[NB];
@@ -690,7 +749,12 @@ __device__ __forceinline__ void bits_by_slices(Wave& v, int m, int lo, const uin
     uint64_t rest = r & ~ge;
     v.lmax = max(v.lmax, slices_max<NB>(s, rest));
     if (wd < w_hi) out[wd] = ge;
+    vis += popc64(r);
+    ne += popc64(slices_any<NB>(s, r));
+    keep += popc64(ge);
   }
+  ne = wave_sum(ne);
+  count_nodes(v, depth, wave_sum(vis), ne, ne - wave_sum(keep));
 }
 
 // The slice count that holds m.
@@ -712,10 +776,10 @@ __device__ __forceinline__ void open_general(Wave& v, uint64_t y2, uint64_t* bit
   // (s.y[0] holds y2)
   const int m2 = wave_sum(popc64(y2));
   if (count_by_rows(v, m2, v.b + 1)) {
-    bits_by_rows(v, v.s.y, v.b + 1, nullptr, bits);
+    bits_by_rows(v, v.s.y, 3, v.b + 1, nullptr, bits);
   } else {
     list_samples(y2, v.s.smp, lane);
-    PDFS_BY_SLICES(m2, (bits_by_slices<NB>(v, m2, v.b + 1, nullptr, bits)));
+    PDFS_BY_SLICES(m2, (bits_by_slices<NB>(v, m2, 3, v.b + 1, nullptr, bits)));
   }
   __threadfence_block();
   int at = v.b + 1;
@@ -741,6 +805,7 @@ __device__ __forceinline__ void open_general(Wave& v, uint64_t y2, uint64_t* bit
     at = c + 1;
     if (cnt < v.need) {
       v.lmax = max(v.lmax, cnt);
+      count_nodes(v, l + 3, 0, 0, 1);
       continue;
     }
     const bool by_rows = count_by_rows(v, cnt, c + 1);
@@ -754,8 +819,8 @@ __device__ __forceinline__ void open_general(Wave& v, uint64_t y2, uint64_t* bit
       continue;
     }
     uint64_t* nx = bits + (size_t)(l + 1) * v.L.gw;
-    if (by_rows) bits_by_rows(v, yl, c + 1, bm, nx);
-    else PDFS_BY_SLICES(cnt, (bits_by_slices<NB>(v, cnt, c + 1, bm, nx)));
+    if (by_rows) bits_by_rows(v, yl, l + 4, c + 1, bm, nx);
+    else PDFS_BY_SLICES(cnt, (bits_by_slices<NB>(v, cnt, l + 4, c + 1, bm, nx)));
     __threadfence_block();
     ++l;
   }
@@ -789,6 +854,7 @@ __device__ __forceinline__ void open_lists(Wave& v, int n0) {
     const int ci = uniform(popc64(mi));
     if (ci < v.need) {
       v.lmax = max(v.lmax, ci);
+      count_nodes(v, l + 3, 0, 0, 1);
       ++i;
       continue;
     }
@@ -799,16 +865,19 @@ __device__ __forceinline__ void open_lists(Wave& v, int n0) {
       pass_own_best(v, l + 3);
       if (ci < v.need) {
         v.lmax = max(v.lmax, ci);
+        count_nodes(v, l + 3, 0, 0, 1);
         ++i;
         continue;
       }
     }
+    int ne = 0;
     if (l + 4 == h) {
       for (int j0 = i + 1; j0 < n; j0 += kWave) {
         const int j = j0 + lane;
         const int tp = j < n ? popc64(mi & mk[j]) : 0;
         const bool hit = tp >= v.need;
         v.lmax = max(v.lmax, hit ? 0 : tp);
+        ne += count_lanes(tp > 0);
         if (__any(hit)) {
           // the lists are walked in tuple order: a leaf found here precedes
           // every later one of the pair with its score
@@ -816,6 +885,7 @@ __device__ __forceinline__ void open_lists(Wave& v, int n0) {
           refresh_need(v);
         }
       }
+      count_nodes(v, l + 4, n - i - 1, ne, 0);
       ++i;
       continue;
     }
@@ -836,7 +906,9 @@ __device__ __forceinline__ void open_lists(Wave& v, int n0) {
         io[pos] = ix[j];
       }
       k += __popcll(hm);
+      ne += count_lanes(tp > 0);
     }
+    count_nodes(v, l + 4, n - i - 1, ne, ne - k);
     wave_lds_sync();
     keep_n = lane == l ? n : keep_n;
     keep_i = lane == l ? i : keep_i;
@@ -916,6 +988,7 @@ __device__ __forceinline__ void open_lanes(Wave& v, const Mask<MW>& mk, int ix,
     }
     if (ci < v.need) {
       v.lmax = max(v.lmax, ci);
+      count_nodes(v, LV + 3, 0, 0, 1);
       continue;
     }
     const bool in = __builtin_amdgcn_inverse_ballot_w64(set);
@@ -923,6 +996,8 @@ __device__ __forceinline__ void open_lanes(Wave& v, const Mask<MW>& mk, int ix,
     const bool hit = in && tp >= v.need;
     v.lmax = max(v.lmax, hit ? 0 : tp);
     const unsigned long long hm = __ballot(hit);
+    const int ne = count_lanes(tp > 0);
+    count_nodes(v, LV + 4, __popcll(set), ne, LV + 4 == h ? 0 : ne - __popcll(hm));
     if (!hm) continue;
     if (LV + 4 == h) {
       // in tuple order: a leaf found here precedes every later one of the
@@ -979,6 +1054,7 @@ __device__ __forceinline__ int open_pair(Wave& v, int a, int b, uint64_t* bits) 
   refresh_need(v);
   const int ub = v.P.p * m + v.P.q * v.P.n_normal;
   if (m < v.need) return ub;
+  count_nodes(v, 2, 0, 0, 1);
   const bool by_rows = count_by_rows(v, m, b + 1);
   wave_lds_sync();
   if (lane == 0) {
@@ -1153,10 +1229,71 @@ __device__ __forceinline__ void last_answer(const LazyWork& L, int n, int nA, in
   __syncthreads();
 }
 
+// The rows of work, summed in parts by the waves behind the first, which is busy
+// with the answer.
+constexpr int kWorkParts = (kBlock - kWave) / kLazyFields;
+
+__device__ __forceinline__ unsigned long long rows_of_work(const LazyWork& L) {
+  unsigned long long x = 0;
+  if (threadIdx.x >= kWave) {
+    const int f = threadIdx.x % kLazyFields, r0 = (threadIdx.x - kWave) / kLazyFields;
+#pragma unroll
+    for (int r = r0; r < kWorkRows; r += kWorkParts) x += L.tally[r * kLazyFields + f];
+  }
+  return x;
+}
+
+// The work that a finished run's launches counted, into the run's totals (the
+// first block).  A pair's node is formed when it is listed, and again in a later
+// round that counts it.  Under empty-intersection pruning the counters follow
+// from an enumeration; only the leaves whose false positives were counted are
+// taken from here.
+__device__ __forceinline__ void total_work(const Problem& P, const Work& w, const LazyWork& L,
+                                           int h, unsigned long long x) {
+  __shared__ unsigned long long part[kWorkParts][kLazyFields];
+  RoundState* st = w.st;
+  const int tid = threadIdx.x, f = tid % kLazyFields;
+  if (tid >= kWave) part[(tid - kWave) / kLazyFields][f] = x;
+  __syncthreads();
+  if (tid >= kLazyFields) return;
+  x = 0;
+#pragma unroll
+  for (int r = 0; r < kWorkParts; ++r) x += part[r][f];
+  if (f == kLfFp && h <= 4) st->tx_fp_leaves = x;
+  if (P.mode != kPruneBound) return;
+  const int d = 2 + f % 8;
+  if (f < kLfFp && d <= h) {
+    const unsigned long long listed = st->n_pairs;
+    if (f < kLfNe) {
+      st->tot.visited[d] = x + (d == 2 ? st->cnt.visited[2] : 0ull);
+      if (d == 3 && h <= 4) st->tx_vis3 = x;
+      if (d == 4 && h == 4) st->tx_vis4 = x;
+    } else if (f < kLfBp) {
+      st->tot.nonempty[d] = x + (d == 2 ? listed : 0ull);
+      if (d == h && h >= 3 && h <= 4) st->tx_leaves = x;
+    } else if (d < h) {
+      // bp[2] holds the pairs opened: the others formed were pruned
+      unsigned long long formed = listed;
+      for (int r = 0; r < kWorkParts; ++r) formed += part[r][kLfNe];
+      st->tot.bound_pruned[d] = d == 2 ? formed - x : x;
+    }
+  }
+  if (f == kLfWords3 && h <= 4) st->tx_vis_words3 = x;
+  if (f == kLfWords4 && h == 4) st->tx_vis_words4 = x;
+  if (f == kLfFp) {
+    st->tot.visited[1] = st->cnt.visited[1];
+    st->tot.nonempty[1] = st->cnt.nonempty[1];
+    const unsigned long long a1 = (unsigned long long)st->amax[1];
+    const unsigned long long a2 = (unsigned long long)st->amax[2];
+    st->tx_pair_macs = (a1 ? a1 * a2 - a1 * (a1 + 1) / 2 : 0) * (unsigned long long)L.uncs[0];
+  }
+}
+
 // Commits it (the first block): the round's record, the state and the masks.
 __device__ __forceinline__ void commit_answer(const Problem& P, const Work& w, const LazyWork& L,
                                               int h, const LazyState& z, const LazyState& nz,
-                                              const Slot& best, bool found, uint64_t* un) {
+                                              const Slot& best, bool found, uint64_t* un,
+                                              bool early, unsigned long long work) {
   RoundState* st = w.st;
   const int tid = threadIdx.x, lane = tid & 63;
   const uint64_t* T = reinterpret_cast<const uint64_t*>(w.TA);
@@ -1204,6 +1341,7 @@ __device__ __forceinline__ void commit_answer(const Problem& P, const Work& w, c
     st->executed = nz.executed;
     st->done = nz.done;
   }
+  if (nz.done && L.tally) total_work(P, w, L, h, early ? work : rows_of_work(L));
 }
 
 // H: the combination size, or 0 for 5..9 (taken from P).
@@ -1214,6 +1352,7 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
   __shared__ Slot wave_slot[kBlock / kWave];
   __shared__ unsigned long long wave_key[kBlock / kWave];
   __shared__ Slot s_best;
+  __shared__ unsigned long long wave_work[kBlock / kWave][kLazyFields];
   RoundState* st = w.st;
   const int lane = threadIdx.x & 63;
   const int wib = uniform(threadIdx.x >> 6);
@@ -1238,6 +1377,9 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
       if (i < h && lane < w.w64) py &= T[(size_t)pool.idx[i] * w.w64 + lane];
   }
   LazyState nz = z;
+  // (a launch that only commits may end the run: its rows of work, meanwhile)
+  const bool early = !search && L.tally;
+  const unsigned long long work = early ? rows_of_work(L) : 0ull;
   if (z.searched) {
     last_answer(L, n, nA, h, &s_best);
     const Slot& best = s_best;
@@ -1265,7 +1407,8 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
       u &= ~c;
     }
     if (blockIdx.x == 0)
-      commit_answer(P, w, L, h, z, nz, best, found, L.U2 + cur * kMaxW64);
+      commit_answer(P, w, L, h, z, nz, best, found, L.U2 + cur * kMaxW64,
+                    early, work);
   } else if (blockIdx.x == 0 && threadIdx.x < w.w64) {
     L.U2[cur * kMaxW64 + lane] = u;
   }
@@ -1299,6 +1442,8 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
   v.need = 1;
   v.sub = -1;
   v.lmax = 0;
+  v.work = 0;
+  v.ne3 = 0u;
   wave_lds_sync();
   if (lane < w.w64) v.s.y[(kMaxH - 1) * kMaxW64 + lane] = v.u;   // the mask, for lane-wise counts
   const uint64_t* um = v.s.y + (kMaxH - 1) * kMaxW64;
@@ -1343,6 +1488,7 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
   if (h >= 3 && n_mine > 0 && v.inc == 0) {
     const unsigned long long e = list[0];
     dive(v, uniform((int)(e & 0xffff)), uniform((int)((e >> 16) & 0xffff)));
+    v.work = 0;   // (a leaf that is met again below its pair)
   }
 
   for (int k0 = 0; k0 < n_chunk; k0 += kWave) {
@@ -1368,8 +1514,10 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
             sb = ub;
             changed = true;
           }
-          nd = sb >= 0 && !dominated(sb, a, b, v.inc);
         }
+        // (the first round's are counted as they are listed)
+        if (nz.executed > 0) count_nodes(v, 2, count_lanes(nd), count_lanes(ct > 0), 0);
+        nd = nd && sb >= 0 && !dominated(sb, a, b, v.inc);
         if (h == 2) {
           e = (e & 0xffffffffull) | ((unsigned long long)(uint32_t)sb << 32);
           chunk_h2(v, e, nd, ct, changed);
@@ -1417,7 +1565,27 @@ __global__ __launch_bounds__(256) void k_lazy_round(Problem P, Work w, LazyWork 
     L.pool[wv] = sl;
     wave_slot[wib] = sl;
   }
+  if (L.tally) {
+    unsigned long long x = (unsigned long long)v.work;
+    if (h == 3) {
+      const int ne3 = wave_sum((int)v.ne3);
+      if (lane == kLfNe + 1) x += (unsigned long long)ne3;
+    }
+    if (h == 3 || h == 4) {
+      const unsigned long long words = (unsigned long long)((nz.n_unc + 63) / 64);
+      const unsigned long long x3 = readlane64(x, 1), x4 = readlane64(x, 2);
+      if (lane == kLfWords3) x = x3 * words;
+      if (lane == kLfWords4) x = x4 * words;
+    }
+    if (lane < kLazyFields) wave_work[wib][lane] = x;
+  }
   __syncthreads();
+  if (L.tally && wib == kBlock / kWave - 1 && lane < kLazyFields) {   // (the first one is busy)
+    unsigned long long x = 0;
+#pragma unroll
+    for (int i = 0; i < kBlock / kWave; ++i) x += wave_work[i][lane];
+    if (x) atomicAdd(&L.tally[(blockIdx.x % kWorkRows) * kLazyFields + lane], x);
+  }
   if (threadIdx.x == 0) {
     Slot r = wave_slot[0];
     for (int i = 1; i < kBlock / kWave; ++i)

@@ -215,6 +215,7 @@ static int32_t ensure_lazy(pdfs_ctx* c, int h, int w64) {
   L.seg = lazy_seg(c->pair_cap, L.nw);
   L.gw = (c->nA_max + 63) / 64 > 0 ? (c->nA_max + 63) / 64 : 1;
   L.levels = lazy_levels(h);
+  L.tally = c->want_counters ? c->tallies : nullptr;   // (the pair table is done with them)
   if (!L.Uc) {
     CK(c, dalloc_kept(c, {part(&L.Uc, kMaxW64), part(&L.cursor, kMaxCount + 1),
                           part(&L.pool, kLazyWaves), part(&L.wins, 3 * (kLazyWaves / 4)),

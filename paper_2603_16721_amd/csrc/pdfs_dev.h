@@ -226,6 +226,12 @@ struct LazyState {
   int32_t searched;   // the launch searched a round: its answer is to be committed
 };
 
+// Work of a lazy run, in rows shared by every kWorkRows-th block: nodes formed, non-empty and pruned of
+// depth d at offset d - 2 (kLfBp: the pairs opened), leaves whose false positives
+// were counted, and nodes of depths 3 and 4 times their round's row words.
+constexpr int kLazyFields = 32, kWorkRows = 16;
+enum LazyField { kLfVis = 0, kLfNe = 8, kLfBp = 16, kLfFp = 24, kLfWords3 = 25, kLfWords4 = 26 };
+
 // Run-long workspace of the lazy rounds (k_lazy.hip), in the index space of
 // the run's first round (its active genes, its uncovered samples).
 struct LazyWork {
@@ -244,6 +250,7 @@ struct LazyWork {
   int32_t* uncs;              // [n_tumor + 2] uncovered samples at a round's start
   uint64_t* bits;             // [nw][levels][gw] candidate bitmaps of the general walk
   unsigned long long* shard;  // [2][kIncShards * kCursorStride] incumbents of a part of the blocks
+  unsigned long long* tally;  // [kWorkRows][kLazyFields] (NULL: not counted)
   int32_t gw;                 // words of a row of B
   int32_t nw;                 // waves of the round kernel (a multiple of 4)
   int32_t seg;                // entries of a wave's share

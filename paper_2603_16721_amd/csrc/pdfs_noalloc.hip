@@ -295,6 +295,7 @@ int32_t pdfs_best_combo_noalloc(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q,
     W.nw = L.nw;
     W.seg = L.seg;
     W.levels = lazy_levels(h);
+    W.tally = stats ? w.tallies : nullptr;   // (the pair table is done with them)
     hipEvent_t* ev = c->ev[slot][0];
     rc = enqueue_lists(c, P, w, W, 1, ev);
     if (rc != PDFS_OK) return rc;
