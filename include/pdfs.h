@@ -60,7 +60,7 @@ extern "C" {
 /* PDFS_PRUNE_EMPTY: the paper's rule (Alg. 2) -- a prefix whose running tumour
  *   intersection is empty is not extended.  The combinations and the counters
  *   of that walk; the counters are made in one enumeration after the last
- *   round, not by walking every round.
+ *   round, not by walking every round, and only where the call takes statistics.
  * PDFS_PRUNE_BOUND: EMPTY plus the score bound of Sec. III-E -- a prefix
  *   covering c uncovered tumour samples can reach at most p*c + q*N_n, so it
  *   is not extended when that cannot beat the best combination found so far.

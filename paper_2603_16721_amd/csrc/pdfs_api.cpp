@@ -714,15 +714,29 @@ int32_t prepare_run(pdfs_ctx* c, int h, int n_unc) {
   return size_triples(c, h, n_unc);
 }
 
+// Everything a lazy run allocates, before its first launch: the pair list, the
+// shares and, under empty-intersection pruning, the buffers of the counters that
+// the caller asked for (for as many rounds as the run can take).
+static int32_t prepare_lazy(pdfs_ctx* c, int h, int w64, int max_rounds, int n_unc) {
+  int32_t rc = ensure_workspace(c, h, true);
+  if (rc == PDFS_OK) rc = ensure_lazy(c, h, w64);
+  if (rc == PDFS_OK && c->want_counters && c->prune_mode == PDFS_PRUNE_EMPTY) {
+    const int most = n_unc + 1;   // each round covers a sample, or is the last
+    rc = ensure_count(c, h, w64, max_rounds > 0 && max_rounds < most ? max_rounds : most);
+  }
+  return rc;
+}
+
 int32_t run_start(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int max_rounds,
                   int n_unc) {
   const bool lazy = runs_lazy(c, h, max_rounds, n_unc);
   const int w64 = dfs_row_words(words(n_unc > 0 ? n_unc : 1));
-  int32_t rc = lazy ? ensure_workspace(c, h, true) : prepare_run(c, h, n_unc);
-  if (rc == PDFS_OK && lazy) {
+  int32_t rc = PDFS_OK;
+  if (lazy) {
     if (w64 < 0 || w64 > c->w64_max) return fail(c, PDFS_ERR_UNSUPPORTED, "row too wide");
-    rc = ensure_lazy(c, h, w64);
+    rc = prepare_lazy(c, h, w64, max_rounds, n_unc);
   }
+  if (!lazy) rc = prepare_run(c, h, n_unc);
   if (rc != PDFS_OK) return rc;
   Run& r = c->run;
   // chunks of an earlier run still in flight are no-ops queued before
@@ -841,7 +855,7 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
     const unsigned long long emitted = st.n_pairs;
     const int executed = st.executed;
     int32_t rc = regrow_pairs(c, emitted);   // waits for the chunks in flight
-    if (rc == PDFS_OK && r.lazy) rc = ensure_lazy(c, r.h, r.w64);
+    if (rc == PDFS_OK && r.lazy) rc = prepare_lazy(c, r.h, r.w64, r.max_rounds, r.n_unc);
     r.listed = false;
     if (rc != PDFS_OK) {
       r.active = false;
@@ -870,11 +884,6 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
   }
   if (st.done || (r.max_rounds > 0 && r.enqueued >= r.max_rounds && r.inflight == 0)) {
     if (r.lazy && c->prune_mode == PDFS_PRUNE_EMPTY && c->want_counters && st.executed > 0) {
-      const int32_t rc = ensure_count(c, r.h, r.w64, st.executed);
-      if (rc != PDFS_OK) {
-        r.active = false;
-        return rc;
-      }
       const Problem P = make_problem(c, r.h, r.p, r.q);
       const Work w = make_work(c, r.w64, r.target);
       CK(c, launch_count(P, w, c->lz, c->cw, c->nA_max, c->stream));
@@ -1307,6 +1316,7 @@ int32_t pdfs_best_combo(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q, const ui
   if (rc != PDFS_OK) return rc;
   if (!out) return fail(c, PDFS_ERR_INVALID_ARG, "out is NULL");
   auto t0 = std::chrono::steady_clock::now();
+  c->want_counters = stats != nullptr;
   begin_stats(c, stats);
   memset(out, 0, sizeof(*out));
   const int32_t n_unc = set_uncovered(c, uncovered);
@@ -1330,6 +1340,7 @@ int32_t pdfs_wsc_run(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q, int32_t tar
   if (!n_out || cap < 0 || (cap > 0 && !out))
     return fail(c, PDFS_ERR_INVALID_ARG, "bad output arguments");
   auto t0 = std::chrono::steady_clock::now();
+  c->want_counters = stats != nullptr;
   begin_stats(c, stats);
   *n_out = 0;
   const int K = target_covered > 0 ? target_covered : c->n_tumor;

@@ -769,6 +769,7 @@ int32_t pdfs_batch_run(pdfs_batch* b, const int32_t* h, uint32_t p, uint32_t q,
   for (int i = 0; i < n; ++i) {
     const int32_t rc = check_call(b->ctx[i], h[i], p, q);
     if (rc != PDFS_OK) return batch_fail(b, rc, i);
+    b->ctx[i]->want_counters = stats != nullptr;
     n_outs[i] = 0;
   }
   // One launch per round step over every instance (all of h = 3, 4 with empty or

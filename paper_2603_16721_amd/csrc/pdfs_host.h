@@ -111,7 +111,7 @@ struct pdfs_ctx {
   size_t cw_tab_n = 0, cw_seg_n = 0, cw_bits_n = 0, cw_q_n = 0, cw_pref_n = 0;
   unsigned long long tumor_bits = 0;   // tumour mutations of the cohort
   pdfs::Route route = pdfs::Route::kByRule;   // (the tuner and the server set it)
-  bool want_counters = true;           // callers that report no counters skip them
+  bool want_counters = true;           // the call reports counters
   bool two_phase = false;              // this run uses the two-phase path
   pdfs::Slot* slots = nullptr;
   unsigned long long* tallies = nullptr;

@@ -1,5 +1,5 @@
-// Every allocation of a call in turn fails: the call says so (or does without),
-// and the context's next calls work on buffers that are held and long enough.
+// Every allocation of a call in turn fails: the call says so, and the context's
+// next calls work on buffers that are held and long enough.
 #include "stub.h"
 
 #include <vector>
