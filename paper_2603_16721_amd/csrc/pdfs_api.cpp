@@ -727,14 +727,32 @@ static int32_t prepare_lazy(pdfs_ctx* c, int h, int w64, int max_rounds, int n_u
   return rc;
 }
 
+// Gives back what only lazy runs use, and the pair lists: a run that they do not
+// fit goes out as walked rounds, which at h = 2 need no list at all.
+static void drop_lazy(pdfs_ctx* c) {
+  drop_pair_lists(c);
+  void** bufs[] = {(void**)&c->lz.B, (void**)&c->lz.bits, (void**)&c->cw.pref, (void**)&c->cw.q,
+                   (void**)&c->cw.seg_v, (void**)&c->cw.tab_v, (void**)&c->cw.bits};
+  for (void** b : bufs) {
+    dfree(c, *b);
+    *b = nullptr;
+  }
+  c->lz_b_n = c->lz_bits_n = 0;
+  c->cw_pref_n = c->cw_q_n = c->cw_seg_n = c->cw_tab_n = c->cw_bits_n = 0;
+}
+
 int32_t run_start(pdfs_ctx* c, int h, uint32_t p, uint32_t q, int target, int max_rounds,
                   int n_unc) {
-  const bool lazy = runs_lazy(c, h, max_rounds, n_unc);
+  bool lazy = runs_lazy(c, h, max_rounds, n_unc);
   const int w64 = dfs_row_words(words(n_unc > 0 ? n_unc : 1));
   int32_t rc = PDFS_OK;
   if (lazy) {
     if (w64 < 0 || w64 > c->w64_max) return fail(c, PDFS_ERR_UNSUPPORTED, "row too wide");
     rc = prepare_lazy(c, h, w64, max_rounds, n_unc);
+    if (rc == PDFS_ERR_OUT_OF_MEMORY) {
+      drop_lazy(c);
+      lazy = false;
+    }
   }
   if (!lazy) rc = prepare_run(c, h, n_unc);
   if (rc != PDFS_OK) return rc;
@@ -857,6 +875,12 @@ int32_t run_poll(pdfs_ctx* c, bool wait, bool* ready, bool* done) {
     int32_t rc = regrow_pairs(c, emitted);   // waits for the chunks in flight
     if (rc == PDFS_OK && r.lazy) rc = prepare_lazy(c, r.h, r.w64, r.max_rounds, r.n_unc);
     r.listed = false;
+    if (rc == PDFS_ERR_OUT_OF_MEMORY && r.lazy) {
+      // (stopped before its first round: the run begins again, walked)
+      drop_lazy(c);
+      r.lazy = r.begun = false;
+      rc = prepare_run(c, r.h, r.n_unc);
+    }
     if (rc != PDFS_OK) {
       r.active = false;
       return rc;

@@ -1,5 +1,6 @@
-// Every allocation of a call in turn fails: the call says so, and the context's
-// next calls work on buffers that are held and long enough.
+// Every allocation of a call in turn fails: the call says so (a lazy run goes out
+// as walked rounds), and the context's next calls work on buffers that are held
+// and long enough.
 #include "stub.h"
 
 #include <vector>
@@ -58,6 +59,7 @@ int main() {
         stub::fail_at = -1;
         if (rc != PDFS_OK && rc != PDFS_ERR_OUT_OF_MEMORY) stub::die("status");
         if (!failed && rc != PDFS_OK) stub::die("a call without a failure");
+        if (hit.mode != PDFS_PRUNE_NONE && rc != PDFS_OK) stub::die("walked rounds would have fit");
         // a shorter need, the same call, then everything else
         if (call(c, {hit.mode, hit.h, 1, 64}) != PDFS_OK) stub::die("the next call");
         if (call(c, hit) != PDFS_OK) stub::die("the same call again");

@@ -1,4 +1,5 @@
-// What a run does without: counters that nobody asked for.
+// What a run does without: counters that nobody asked for, and lists that do not
+// fit in device memory.
 #include "stub.h"
 
 #include <vector>
@@ -42,6 +43,32 @@ int main() {
     if (cover(c, h, true, &n, out, left) != PDFS_OK || n != 3) stub::die("counted cover");
     if (stub::counted != 1 || stub::bytes_held <= without) stub::die("counters asked for");
     pdfs_destroy(c);
+
+    // every limit on what may be held: the run goes out as lazy rounds, or walked
+    // ones, or is refused before it has run; h = 2 needs no list
+    for (int mode : {PDFS_PRUNE_EMPTY, PDFS_PRUNE_BOUND}) {
+      stub::lazy_launches = stub::walked_rounds = 0;
+      c = make(mode);
+      const size_t base = stub::bytes_held;
+      if (cover(c, h, true, &n, out, left) != PDFS_OK || !stub::lazy_launches) stub::die("lazy cover");
+      const size_t full = stub::bytes_held;
+      pdfs_destroy(c);
+      int walked = 0, refused = 0;
+      for (size_t room = full; room > base; room -= (full - base) / 64 + 1) {
+        c = make(mode);
+        stub::limit = room;
+        stub::walked_rounds = 0;
+        const int32_t rc = cover(c, h, true, &n, out, left);
+        stub::limit = ~(size_t)0;
+        if (rc == PDFS_OK && n != 3) stub::die("rounds under a limit");
+        if (rc != PDFS_OK && (rc != PDFS_ERR_OUT_OF_MEMORY || n != 0)) stub::die("status under a limit");
+        walked += stub::walked_rounds > 0;
+        refused += rc != PDFS_OK;
+        if (cover(c, h, true, &n, out, left) != PDFS_OK || n != 3) stub::die("after the limit");
+        pdfs_destroy(c);
+      }
+      if (h == 2 && !walked) stub::die("no cover of h = 2 was walked");
+    }
   }
   if (stub::bytes_held) stub::die("memory left behind");
   std::printf("ok\n");

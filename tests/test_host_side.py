@@ -1,7 +1,8 @@
 """The host side of a run (pdfs_api.cpp), compiled against stand-ins for the HIP
 calls and the launches (tests/host/stub.h).  alloc: device memory runs out, and
 every buffer that a launch is handed has to be held and long enough; memory:
-counters that nobody asked for; routes: lazy or walked rounds.  No GPU."""
+counters that nobody asked for, lists that do not fit; routes: lazy or walked
+rounds.  No GPU."""
 import os
 import subprocess
 
