@@ -328,6 +328,11 @@ static double walk_visits(int h, int nA, int n, double d) {
   return v;
 }
 
+double shared_samples(const RunShape& s) {
+  const double d = (double)s.bits / ((double)(s.nA > 0 ? s.nA : 1) * s.n_tumor);
+  return d * d * s.n_unc;
+}
+
 bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_PRUNE_NONE; }
 
 // Lazy rounds or walked ones (the pair table at h = 2).  A lazy round opens few
@@ -340,7 +345,7 @@ bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_P
 // was tried).  Measured over 6600 rounds and covers (G 20 .. 20000, n 60 .. 1200, d
 // 0.005 .. 0.45, even and heavy-tailed rates); lazy | walked, ms:
 //  - covers: h = 4, n = 1200 G = 400 m 12 1.4 | 13, m 48 4.6 | 2.6, m 108 96 | 5.9;
-//    h = 5, n = 1200 G = 250 m 48 6.8 | 7.7, m 75 46 | 10; under ~100 genes (~50 at
+//    h = 5, n = 1200 G = 250 m 48 6.8 | 7.7, m 75 46 | 10; under ~100 genes (~30 at
 //    h = 4) there are few pairs to open and many rounds: lazy at every m; h = 3,
 //    n = 1200 G = 1000 m 12 1.4 | 7.8, m 108 5.4 | 10, m 243 33 | 24.
 //  - h = 2 covers: every pair is one lane's count, so the cost is the list: n = 500
@@ -349,8 +354,8 @@ bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_P
 //    scores every pair in its own epilogue: 115 us against 134 us with the lists
 //    (G = 500).
 //  - one round (or a few) has only its own opens to save: h = 3, n = 1200 G = 300
-//    m 12 0.42 | 0.32, G = 1000 m 12 0.83 | 1.4, m 108 4.8 | 1.8, G = 5000 m 48 96 |
-//    154; h = 4, n = 500 G = 300 m 5 0.32 | 0.33, n = 1200 G = 300 m 12 0.62 | 0.45.
+//    m 12 0.42 | 0.32, G = 1000 m 12 0.83 | 1.4, m 108 4.8 | 1.8, n = 700
+//    G = 2500 m 63 25 | 15, n = 1200 G = 5000 m 48 96 | 154; h = 4, n = 500 G = 300 m 5 0.32 | 0.33, n = 1200 G = 300 m 12 0.62 | 0.45.
 //    Few genes make few waves, whose opens then follow one another and grow with
 //    the row's words too: h = 4, G = 100 n = 1200 m 12 0.58 | 0.29, n = 100 m 9 0.24 |
 //    0.23 (at h = 3 the same line would lose as much on heavy-tailed cohorts, n = 700
@@ -364,14 +369,14 @@ bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_P
 bool lazy_pays(const RunShape& s, int h, int prune_mode, int max_rounds, bool counters) {
   if (!lazy_runs_at(h, prune_mode) || (h == 2 && max_rounds == 1)) return false;
   const int nA = s.nA > 0 ? s.nA : 1, n = s.n_unc;
-  const double d = (double)s.bits / ((double)nA * s.n_tumor), m = d * d * n;
+  const double d = (double)s.bits / ((double)nA * s.n_tumor), m = shared_samples(s);
   if (h == 2) return d < 0.15 || d * nA < 700.0;
   counters = counters && prune_mode == PDFS_PRUNE_EMPTY;
   const int few = max_rounds >= 1 && max_rounds <= 4 ? max_rounds : 0;
   const double visits = counters ? walk_visits(h, nA, n, d) : 0.0;
   if (few) {
     if (!counters) {
-      if (h == 3) return m < 16.0 || (nA >= 2048 && m < 64.0);
+      if (h == 3) return m < 16.0 || 50.0 * m < nA;
       return m < 10.0 && (h >= 5 || nA >= 500 || m * words(n) < 100.0);
     }
     if (h == 3) return few * visits >= 3e7 && m < 16.0;
@@ -380,7 +385,7 @@ bool lazy_pays(const RunShape& s, int h, int prune_mode, int max_rounds, bool co
   }
   if (counters && visits < (h <= 4 ? 1e2 : h == 5 ? 1e3 : h == 6 ? 3e3 : 1e4)) return false;
   if (h == 3) return m < 128.0 || nA < 500;
-  if (h == 4) return m < 64.0 || nA < 48;
+  if (h == 4) return m < 64.0 || nA < 32;
   return counters || m < 64.0 || nA < 96;
 }
 

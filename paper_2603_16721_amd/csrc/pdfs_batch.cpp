@@ -774,18 +774,23 @@ int32_t pdfs_batch_run(pdfs_batch* b, const int32_t* h, uint32_t p, uint32_t q,
   }
   // One launch per round step over every instance (all of h = 3, 4 with empty or
   // bound pruning) where it is asked for, and by default under bound pruning
-  // where every instance's rounds are walked.  Otherwise the stream-parallel runs
-  // below: of lazy rounds 8 cohorts took 25 ms there, 109 ms in one launch per
-  // step (and 32 instances of walked ones 396 ms there, 215 ms in one launch).
+  // where the cohorts are dense: some instance's rounds are walked, and the others
+  // are not far from it (8 cohorts whose pairs share 48 to 93 samples: 12.9 ms,
+  // 16.5 on the streams).  Otherwise the stream-parallel runs below: 8 sparse
+  // cohorts took 25 ms there as lazy rounds, 109 ms in one launch per step.
   const int pm = b->ctx[0]->prune_mode;
   std::vector<bool> walked(n);
-  bool all_walked = true, multi = n <= kMaxBatch && pm != PDFS_PRUNE_NONE;
+  bool some_walked = false, all_dense = true, multi = n <= kMaxBatch && pm != PDFS_PRUNE_NONE;
   for (int i = 0; i < n; ++i) {
-    walked[i] = !runs_lazy(b->ctx[i], h[i], 0, b->ctx[i]->n_tumor);
-    all_walked = all_walked && walked[i];
+    const pdfs_ctx* c = b->ctx[i];
+    walked[i] = !runs_lazy(c, h[i], 0, c->n_tumor);
+    some_walked = some_walked || walked[i];
+    all_dense = all_dense &&
+                shared_samples({c->nA_max, c->n_tumor, c->n_tumor, c->tumor_bits}) >= 32.0;
     multi = multi && (h[i] == 3 || h[i] == 4) && b->ctx[i]->tn_literal == b->ctx[0]->tn_literal;
   }
-  multi = multi && (b->one_launch || (pm == PDFS_PRUNE_BOUND && all_walked && !b->streams_only));
+  multi = multi && (b->one_launch ||
+                    (pm == PDFS_PRUNE_BOUND && some_walked && all_dense && !b->streams_only));
   if (b->autotune)
     for (int i = 0; i < n; ++i)   // lazy rounds have nothing to tune
       if (multi || walked[i]) autotune(b->ctx[i], h[i], p, q);

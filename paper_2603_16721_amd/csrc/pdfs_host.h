@@ -208,6 +208,8 @@ int32_t enqueue_round(pdfs_ctx* c, const Problem& P, const Work& w, hipEvent_t* 
 // for enqueue_round; ev[0..1] around the pair table (used when timing).
 int32_t enqueue_lists(pdfs_ctx* c, const Problem& P, const Work& w, const LazyWork& L,
                       int run_rounds, hipEvent_t* ev);
+// Uncovered samples that a pair of genes shares at the cohort's mean density.
+double shared_samples(const RunShape& s);
 // Whether lazy rounds take this depth and mode at all, and whether a run of at
 // most max_rounds (<= 0: any number) is faster as lazy rounds than walked
 // (counters: the caller wants those of an empty-intersection run).
