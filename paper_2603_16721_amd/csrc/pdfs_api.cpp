@@ -351,8 +351,9 @@ bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_P
 //  - h = 2 covers: every pair is one lane's count, so the cost is the list: n = 500
 //    G = 5000 d 0.1 3.2 | 4.9, d 0.2 3.5 | 2.7; G = 20000 d 0.1 20 | 26, d 0.2 33 |
 //    14; G = 2500 d 0.2 1.6 | 1.9.  A single round is left to the table, which
-//    scores every pair in its own epilogue: 115 us against 134 us with the lists
-//    (G = 500).
+//    scores every pair in its own epilogue, us: n = 200 G = 500 71 | 71, n = 1000 G =
+//    5000 122 | 115, n = 500 G = 20000 d 0.02 1021 | 640 (only large sparse cohorts
+//    would gain: n = 1000 G = 20000 d 0.003 161 | 326).
 //  - one round (or a few) has only its own opens to save: h = 3, n = 1200 G = 300
 //    m 12 0.42 | 0.32, G = 1000 m 12 0.83 | 1.4, m 108 4.8 | 1.8, n = 700
 //    G = 2500 m 63 25 | 15, n = 1200 G = 5000 m 48 96 | 154; h = 4, n = 500 G = 300 m 5 0.32 | 0.33, n = 1200 G = 300 m 12 0.62 | 0.45.
@@ -360,6 +361,11 @@ bool lazy_runs_at(int h, int prune_mode) { return h >= 2 && prune_mode != PDFS_P
 //    the row's words too: h = 4, G = 100 n = 1200 m 12 0.58 | 0.29, n = 100 m 9 0.24 |
 //    0.23 (at h = 3 the same line would lose as much on heavy-tailed cohorts, n = 700
 //    G = 150 m 16 0.13 | 0.23, as it gains on even ones).
+//    Under the literal reading of T- a leaf loses every normal of its genes, which
+//    no bound below it knows, so the first round opens nearly every pair: h = 3,
+//    n = 300 G = 1500 m 0.8 6.1 | 1.5, h = 4, n = 1000 G = 400 m 0.4 0.18 | 0.43, m
+//    2.5 4.3 | 1.6; with counters h = 3, n = 1000 G = 1500 m 0.4 1.1 | 0.4 (12 rounds take
+//    less as lazy ones everywhere).
 //  - counters of an empty-intersection run are 6 launches more (70 us): it takes a
 //    walk of some size to be worth them.  One round: h = 3, G = 400 m 0.1 0.18 |
 //    0.16, G = 2500 m 0.5 0.31 | 1.6; h = 5, G = 60 m 0.1 0.18 | 0.09, G = 400 m 0.5
@@ -375,6 +381,7 @@ bool lazy_pays(const RunShape& s, int h, int prune_mode, int max_rounds, bool co
   const int few = max_rounds >= 1 && max_rounds <= 4 ? max_rounds : 0;
   const double visits = counters ? walk_visits(h, nA, n, d) : 0.0;
   if (few) {
+    if (s.literal && m >= (counters ? 0.1 : 0.6)) return false;
     if (!counters) {
       if (h == 3) return m < 16.0 || 50.0 * m < nA;
       return m < 10.0 && (h >= 5 || nA >= 500 || m * words(n) < 100.0);
@@ -395,7 +402,7 @@ constexpr size_t kMaxCountBytes = (size_t)1 << 30;
 
 bool runs_lazy(const pdfs_ctx* c, int h, int max_rounds, int n_unc) {
   if (c->route != Route::kByRule) return c->route == Route::kLazy && lazy_runs_at(h, c->prune_mode);
-  const RunShape s = {c->nA_max, c->n_tumor, n_unc, c->tumor_bits};
+  const RunShape s = {c->nA_max, c->n_tumor, n_unc, c->tumor_bits, c->tn_literal};
   if (c->prune_mode == PDFS_PRUNE_EMPTY && c->want_counters &&
       c->tumor_bits * (8 * count_sums(h) + 2) > kMaxCountBytes)
     return false;

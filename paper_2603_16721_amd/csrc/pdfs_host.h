@@ -35,6 +35,7 @@ struct RunShape {
   int nA;                    // genes with a tumour mutation
   int n_tumor, n_unc;        // samples, and the uncovered ones at the run's start
   unsigned long long bits;   // tumour mutations
+  bool literal = false;      // FP = normals carrying any of the genes
 };
 
 // Progress of one greedy run on a context, advanced without blocking.  The

@@ -232,7 +232,8 @@ int32_t pdfs_best_combo_noalloc(pdfs_ctx* c, int32_t h, uint32_t p, uint32_t q,
       n = 0;
       for (int k = 0; k < c->wt; ++k) n += __builtin_popcountll(uncovered[k]);
     }
-    lazy = lazy_pays({c->nA_max, c->n_tumor, n, c->tumor_bits}, h, c->prune_mode, 1, false) ||
+    lazy = lazy_pays({c->nA_max, c->n_tumor, n, c->tumor_bits, c->tn_literal}, h, c->prune_mode, 1,
+                     false) ||
            !plan(c, h, false, L, &need) || L.pair_cap < all_pairs(c->nA_max);
   }
   if (!plan(c, h, lazy, L, &need))

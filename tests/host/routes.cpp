@@ -110,6 +110,13 @@ int main() {
     }
     ++n;
   }
+  // the literal reading of T-: a single round's opens are not pruned
+  for (int h = 3; h <= 5; ++h) {
+    const pdfs::RunShape lit = {1500, 300, 300, 22500, true}, plain = {1500, 300, 300, 22500};
+    if (pdfs::lazy_pays(lit, h, kBound, 1, false) || !pdfs::lazy_pays(plain, h, kBound, 1, false) ||
+        !pdfs::lazy_pays(lit, h, kBound, 0, false))
+      stub::die("literal reading");
+  }
   for (int h = 1; h <= PDFS_MAX_H; ++h)
     for (int rounds = 0; rounds < 6; ++rounds) {
       // no gene, no uncovered sample, the largest cohort

@@ -173,6 +173,28 @@ def test_served_walked(pdfs, case, mode):  # noqa: F811
         pdfs.pdfs_server_destroy(srv)
 
 
+# The literal reading of T-: single rounds walked, covers and sparse rounds lazy.
+@pytest.mark.parametrize("G,nt,d,h", [(200, 300, 0.06, 3), (120, 300, 0.06, 4), (60, 200, 0.1, 5),
+                                      (300, 200, 0.01, 3)])
+@pytest.mark.parametrize("mode", ["bound", "empty"])
+def test_literal_rounds(pdfs, G, nt, d, h, mode):  # noqa: F811
+    I = synth.random_tiny(23, G, nt, 50, d, h)
+    T, N = I.packed()
+    with pdfs.Solver(T, N, nt, 50, mode, tn_literal=True) as s:
+        for u in (None, mask_of_bits(np.arange(nt) % 3 != 1)):
+            for mr in (1, 8):
+                exp = cpu.wsc(T, N, nt, 50, h, 1, 10, mode=mode, max_rounds=mr, U0=u, tn="literal")
+                got, st, final = s.wsc(h, 1, 10, 0, mr, u)
+                _same_rounds(got, exp.rounds)
+                assert np.array_equal(final, exp.final_uncovered)
+                if mode == "empty":
+                    _counters_equal(st, exp.counters, h)
+            if h < 5:
+                exp = cpu.wsc(T, N, nt, 50, h, 1, 10, mode=mode, max_rounds=1, U0=u, tn="literal")
+                got, _ = s.best_noalloc(h, 1, 10, u)
+                _same_rounds([got], exp.rounds)
+
+
 # The allocation-free round against the oracle: walked where the cohort is dense,
 # lazy elsewhere, and lazy where the walk's lists would not hold every pair (2850
 # genes, nearly all of whose 4.06 M pairs share a sample: a lazy round holds 4.12 M,
