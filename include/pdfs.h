@@ -116,10 +116,10 @@ typedef struct {
     int32_t pair_cap;   /* initial capacity of the pair list (pairs);
                            <= 0: the default, max(2^21, 128 x the active
                            genes of the first round), at most every pair.
-                           A longer list (made once per run; once per round
-                           of an exhaustive run) grows it to its count + 1/4
-                           and is made again, so this only trades memory for
-                           an occasional repeated listing. */
+                           A longer list (made once per run, or once per
+                           round of a run that walks every node) grows it to
+                           its count + 1/4 and is made again, so this only
+                           trades memory for an occasional repeated listing. */
 } pdfs_options;
 
 /* One chosen combination (one greedy round). */
@@ -156,8 +156,9 @@ typedef struct {
     int32_t reserved;
     int64_t ns_total;   /* host wall time of the call, nanoseconds */
     /* Filled when the context was created with PDFS_OPT_TIME_KERNELS:
-     * index 0 = int8-MFMA pair-table kernel (once per run, or once per round
-     * under PDFS_PRUNE_NONE), 1 = the rounds' search launches (depths 3..h),
+     * index 0 = the kernel that lists the pairs (once per run, or once per
+     * round of a run that walks every node), 1 = the rounds' search launches
+     * (depths 3..h),
      * 2 = the part of index 1 spent in the depth-4 tile kernel, where a run
      * uses it (0 otherwise). */
     int64_t kernel_ns[3];        /* summed HIP-event durations            */
@@ -314,7 +315,9 @@ const char *pdfs_batch_last_error(const pdfs_batch *b);
 typedef struct pdfs_server pdfs_server;
 
 /* hbm_budget_bytes: device memory the server may hold (0 = 90% of free);
- * max_active: requests on the device at once (<= 0: 8). */
+ * max_active: requests on the device at once (<= 0: 8).  Memory of finished
+ * requests is kept for the next ones, up to 2 GiB and the budget, until an
+ * admission needs it or the server is destroyed. */
 int32_t pdfs_server_create(const pdfs_options *opt, uint64_t hbm_budget_bytes,
                            int32_t max_active, pdfs_server **out);
 /* Copies the cohort (host matrices only) and queues the solve.  *ticket

@@ -777,7 +777,7 @@ int32_t pdfs_batch_run(pdfs_batch* b, const int32_t* h, uint32_t p, uint32_t q,
   // where the cohorts are dense: some instance's rounds are walked, and the others
   // are not far from it (8 cohorts whose pairs share 48 to 93 samples: 12.9 ms,
   // 16.5 on the streams).  Otherwise the stream-parallel runs below: 8 sparse
-  // cohorts took 25 ms there as lazy rounds, 109 ms in one launch per step.
+  // cohorts take 11 ms there as lazy rounds, 109 ms in one launch per step.
   const int pm = b->ctx[0]->prune_mode;
   std::vector<bool> walked(n);
   bool some_walked = false, all_dense = true, multi = n <= kMaxBatch && pm != PDFS_PRUNE_NONE;

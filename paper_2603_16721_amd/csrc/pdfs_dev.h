@@ -213,7 +213,10 @@ struct Work {
 };
 
 // ---------------------------------------------------------------- lazy rounds
-constexpr int kLazyWaves = 1024;   // waves of a lazy round at most
+// Waves of a lazy round at most: 512 | 1024 | 2048 | 4096 took a cover of h = 2 1.69 |
+// 1.63 | 1.79 | 2.04 ms, h = 4 5.8 | 4.9 | 4.7 | 5.2, a dense one of 18,000 genes 8.4 |
+// 7.0 | 6.1 | 5.7.
+constexpr int kLazyWaves = 1024;
 // One address serves its atomics one at a time (about 60 ns each), so the
 // incumbent goes through shards: a wave goes on to the round's own only if it
 // raised its shard.
